@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "librbe2d.so")
-SOURCES = ["api.hip", "kspace.hip", "realspace.hip", "misc.hip"]
+SOURCES = ["api.hip", "kspace.hip", "realspace.hip", "tiles.hip", "misc.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

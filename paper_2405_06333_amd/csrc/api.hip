@@ -12,7 +12,7 @@
 
 #include "rbe2d_internal.h"
 
-// cells per r_c along y of the pair kernel's cell grid
+// cells per r_c along y of the FP32 pair kernel's cell grid
 #ifndef RBE2D_REACH_Y
 #define RBE2D_REACH_Y 6
 #endif
@@ -116,6 +116,82 @@ double auto_lz(const rbe2d_params *p) {
     return (p->M + 1) * p->H + std::max(std::max(p->Lx, p->Ly) / (2.0 * kPi) * lg, std::sqrt(lg) / p->alpha);
 }
 
+// Cell grid of the FP32 pair kernel: cells >= r_c / reach in x (searched
+// +-reach columns), layers >= r_c / 2 in z and cells >= r_c / reach_y along y,
+// where the kernel scans contiguous runs of cells (finer cells trim the runs'
+// ends); coarsened if there would be too many cells.  Where a cutoff sphere
+// holds few particles (n_max / volume * r_c^3 < 20) the runs are short and
+// their set-up dominates: x-cells of r_c (three columns), and at most two
+// layers in a slab thinner than 2 r_c (measured on the 64-replica batch: 4 %
+// faster steps than r_c / 2 in both)
+void scan_grid(const rbe2d_params &p, SysDesc &d, int *pncx, int *pncy, int *pncz) {
+    const double per_rc3 = (double)p.n_max / (p.Lx * p.Ly * p.H) * p.r_c * p.r_c * p.r_c;
+    d.reach = per_rc3 < 20.0 ? 1 : 2;
+    d.reach_y = RBE2D_REACH_Y;
+    int ncx = std::max(1, (int)std::floor(d.reach * p.Lx / p.r_c));
+    int ncy = std::max(1, (int)std::floor(d.reach_y * p.Ly / p.r_c));
+    int ncz = std::max(1, (int)std::floor(2.0 * p.H / p.r_c));
+    if (per_rc3 < 20.0 && p.H < 2.0 * p.r_c) ncz = std::min(ncz, 2);
+    const int64_t cell_cap = std::max<int64_t>(2 * p.n_max, 4096);
+    while ((int64_t)ncx * ncy * ncz > cell_cap && (ncx > 5 || ncy > 5 || ncz > 1)) {
+        if (ncz > 1) ncz = (ncz + 1) / 2;
+        else { ncx = std::max(5, ncx / 2); ncy = std::max(5, ncy / 2); }
+    }
+    *pncx = ncx; *pncy = ncy; *pncz = ncz;
+}
+
+// Cell grid of the tile kernel (FP64).  A tile of 64 targets fills a stretch of a
+// column (x-cell and z-layer); its candidates are the columns within r_c, cut
+// along y.  Wide columns make short tiles but include more of the slab around
+// them, narrow ones make long tiles and many runs: the expected candidates and
+// runs of a tile are added up for a few widths, in instructions (about 150 per
+// chunk of 64 candidates, 12 per run), and the cheapest is taken.  (1e6-ion
+// slab: columns of r_c in x and z, 1390 candidates and 12 runs per tile against
+// 2010 and 43 for r_c / 2.)  Along y a cell is r_c / 6 or holds about 6
+// particles, whichever is finer: cells bound the ends of the runs, and
+// particles are ranked within them.
+void tile_grid(const rbe2d_params &p, bool images, int *ncx, int *ncy, int *ncz) {
+    const double rc = p.r_c, rho = std::max<double>(1.0, (double)p.n_max) / (p.Lx * p.Ly * p.H);
+    auto cells_y = [&](int nx, int nz) {
+        const double hy = std::min(rc / 6.0, 6.0 / (rho * (p.Lx / nx) * (p.H / nz)));
+        return std::max(1.0, std::min(1e6, std::floor(p.Ly / hy)));
+    };
+    double best = 1e300;
+    *ncx = *ncy = *ncz = 1;
+    for (double f : {0.5, 0.75, 1.0, 1.5, 2.0, 3.0}) {
+        const int nx = (int)std::max(1.0, std::min(1e6, std::floor(p.Lx / (f * rc))));
+        const int nz_max = (int)std::max(1.0, std::min(32.0, std::ceil(2.0 * p.H / rc)));
+        for (int nz = 1; nz <= nz_max; nz++) {
+            const double hx = p.Lx / nx, hz = p.H / nz, hy = p.Ly / cells_y(nx, nz);
+            const double stretch = 64.0 / (rho * hx * hz), len = std::min(stretch, p.Ly);
+            const double columns = std::max(1.0, stretch / p.Ly);   // of the tile itself
+            double cand = 0.0, runs = 0.0;
+            for (int l = 0; l < nz; l++)
+                for (int m = images ? -nz : 0; m < (images ? 2 * nz : nz); m++) {
+                    const double dz = std::max(0, std::abs(m - l) - 1) * hz;
+                    if (dz >= rc) continue;
+                    for (int i = 0; i == 0 || (i - 1) * hx < rc; i++) {
+                        const double dx = std::max(0, i - 1) * hx, y2 = rc * rc - dx * dx - dz * dz;
+                        if (y2 <= 0.0) continue;
+                        const double n = i == 0 ? columns : 2.0;
+                        cand += n * rho * hx * hz * (len + 2.0 * std::sqrt(y2) + hy);
+                        runs += n;
+                    }
+                }
+            const double cost = (cand / 64.0 * 150.0 + runs * 12.0) / nz;
+            if (cost < best) { best = cost; *ncx = nx; *ncz = nz; }
+        }
+    }
+    *ncy = (int)cells_y(*ncx, *ncz);
+    // no more cells than the workspace plan allows for this many particles
+    const int64_t cap = std::max<int64_t>(2 * p.n_max, 4096);
+    while ((int64_t)*ncx * *ncy * *ncz > cap) {
+        int *big = *ncx > *ncy ? ncx : ncy;
+        if (*ncz > *big) big = ncz;
+        *big = (*big + 1) / 2;
+    }
+}
+
 void surface_setup(SysHost &sh);
 
 // Derived constants, image tables, real-space families, sampler tables and
@@ -206,26 +282,11 @@ rbe2d_status setup_system(const rbe2d_params *pin, SysHost &sh) {
     if (p.precision == RBE2D_PREC_FP32_PHASE && bits > 20)
         return fail(nullptr, RBE2D_E_INVAL, "k-range too wide for FP32 phases (alpha L too large)");
 
-    // cell grid: cells >= r_c / reach in x (searched +-reach columns),
-    // layers >= r_c / 2 in z and cells >= r_c / reach_y along y, where the
-    // pair kernel scans contiguous runs of cells (finer cells trim the runs'
-    // ends); coarsened if there would be too many cells.  Where a cutoff
-    // sphere holds few particles (n_max / volume * r_c^3 < 20) the runs are
-    // short and their set-up dominates: x-cells of r_c (three columns), and
-    // at most two layers in a slab thinner than 2 r_c (measured on the
-    // 64-replica batch: 4 % faster steps than r_c / 2 in both)
-    const double per_rc3 = (double)p.n_max / (p.Lx * p.Ly * p.H) * p.r_c * p.r_c * p.r_c;
-    d.reach = per_rc3 < 20.0 ? 1 : 2;
-    d.reach_y = RBE2D_REACH_Y;
-    int ncx = std::max(1, (int)std::floor(d.reach * p.Lx / p.r_c));
-    int ncy = std::max(1, (int)std::floor(d.reach_y * p.Ly / p.r_c));
-    int ncz = std::max(1, (int)std::floor(2.0 * p.H / p.r_c));
-    if (per_rc3 < 20.0 && p.H < 2.0 * p.r_c) ncz = std::min(ncz, 2);
-    const int64_t cell_cap = std::max<int64_t>(2 * p.n_max, 4096);
-    while ((int64_t)ncx * ncy * ncz > cell_cap && (ncx > 5 || ncy > 5 || ncz > 1)) {
-        if (ncz > 1) ncz = (ncz + 1) / 2;
-        else { ncx = std::max(5, ncx / 2); ncy = std::max(5, ncy / 2); }
-    }
+    const bool fp32 = p.precision == RBE2D_PREC_FP32_PHASE;
+    int ncx, ncy, ncz;
+    d.snake = !fp32;
+    if (fp32) scan_grid(p, d, &ncx, &ncy, &ncz);
+    else tile_grid(p, d.nfam > 0, &ncx, &ncy, &ncz);
     d.ncx = ncx; d.ncy = ncy; d.ncz = ncz;
     d.hx = p.Lx / ncx; d.hy = p.Ly / ncy; d.hz = p.H / ncz;
     d.inv_hx = 1.0 / d.hx; d.inv_hy = 1.0 / d.hy; d.inv_hz = 1.0 / d.hz;
@@ -378,17 +439,19 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     const int64_t nc = std::max<int64_t>(h->n_cap, 1);
     A(&w.cell, nc); A(&w.slot, nc); A(&w.tmp, nc);
     A(&w.count, cells); A(&w.start, cells + 1); A(&w.scanbuf, cells / 1024 + 2);
-    // source records get one wave of padding: the pair kernel reads the first
+    A(&w.sorted, h->cap_sorted); A(&w.sidx, h->cap_sorted);
+    const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
+    // the FP32 records get one wave of padding: the pair kernel reads the first
     // record of an empty run, which may start at the end of the array
-    A(&w.sorted, h->cap_sorted + kWave); A(&w.sidx, h->cap_sorted); A(&w.scell, h->cap_sorted);
-    if (h->precision == RBE2D_PREC_FP32_PHASE) A(&w.src16, h->cap_sorted + kWave);
+    if (fp32) { A(&w.src16, h->cap_sorted + kWave); A(&w.scell, h->cap_sorted); }
     A(&w.freal, nc); A(&w.dgreal, nc);
     A(&w.rpart, 3 * (h->cap_sorted / kWave));
-    // the split is only used when there are too few targets to fill the chip
-    h->split_cap = std::min<int64_t>(nc, 1 << 18);
+    // FP32 pair kernel: the split is only used when there are too few targets
+    // to fill the chip
+    h->split_cap = fp32 ? std::min<int64_t>(nc, 1 << 18) : 0;
     A(&w.freal_s, kMaxRealSplit * h->split_cap);
     A(&w.dgreal_s, kMaxRealSplit * h->split_cap);
-    A(&w.rpart_s, kMaxRealSplit * 3 * (h->cap_sorted / kWave));
+    A(&w.rpart_s, fp32 ? kMaxRealSplit * 3 * (h->cap_sorted / kWave) : 0);
     A(&w.spart, 2 * (h->cap_sorted / kWave));
     A(&w.err, 4);
     A(&w.step, 1);
@@ -1397,9 +1460,11 @@ rbe2d_status rbe2d_autotune(rbe2d_handle h, const int64_t *offsets, const double
         if (st == RBE2D_OK && t < tbest) { tbest = t; best_ks = ks; }
     }
     h->force_ksplit = 0;
-    // 3. column-group split of the pair work (small systems only)
+    // 3. split of the pair work: column groups (FP32, small systems only) or
+    // waves per tile (FP64)
     tbest = 1e30f;
-    for (int rs = 1; st == RBE2D_OK && rs <= kMaxRealSplit && total > 0 && total <= h->split_cap; rs++) {
+    for (int rs = 1; st == RBE2D_OK && rs <= (h->split_cap > 0 ? kMaxRealSplit : kTileSplits) && total > 0 &&
+         (h->split_cap == 0 || total <= h->split_cap); rs++) {
         h->force_rsplit = rs;
         float t = 0.0f;
         st = time([&] { return launch_real(h, pos, q, false, s); }, 3, &t);

@@ -2,6 +2,8 @@
 // revolutions, wave and block reductions with a fixed summation order.
 #pragma once
 
+#include <climits>
+
 #include "rbe2d_internal.h"
 #include "sincos_fit.h"
 
@@ -114,6 +116,37 @@ __device__ __forceinline__ T wave_sum(T v) {
     for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
+
+// Wave-uniform values computed by vector instructions, moved to scalar
+// registers (the compiler keeps them in vector registers otherwise).
+__device__ __forceinline__ float uniform(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+__device__ __forceinline__ double uniform(double v) {
+    const int2 h = make_int2(__builtin_amdgcn_readfirstlane(__double2loint(v)),
+                             __builtin_amdgcn_readfirstlane(__double2hiint(v)));
+    return __hiloint2double(h.y, h.x);
+}
+
+// Wave-wide max / min of an int with DPP lane moves (no LDS round trips):
+// within quads, within rows of 16 (half-mirror, mirror), then row 3 takes
+// rows 0-2 by the row broadcasts; the result is read from lane 63 into a
+// scalar register.  Every lane of the wave must be active.
+template <bool MAX>
+__device__ __forceinline__ int wave_reduce(int v) {
+    // lanes outside the row mask see the identity of the operation
+    constexpr int id = MAX ? INT_MIN : INT_MAX;
+    auto op = [](int x, int y) { return MAX ? max(x, y) : min(x, y); };
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0xb1, 0xf, 0xf, false));    // quad_perm [1,0,3,2]
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x4e, 0xf, 0xf, false));    // quad_perm [2,3,0,1]
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x141, 0xf, 0xf, false));   // row_half_mirror
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x140, 0xf, 0xf, false));   // row_mirror
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x142, 0xa, 0xf, false));   // row_bcast:15 -> rows 1, 3
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x143, 0xc, 0xf, false));   // row_bcast:31 -> rows 2, 3
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ int wave_max(int v) { return wave_reduce<true>(v); }
+__device__ __forceinline__ int wave_min(int v) { return wave_reduce<false>(v); }
 
 // deterministic block sum (blockDim.x = kBlock) of one double; result valid in thread 0
 __device__ __forceinline__ double block_sum(double v, double *sh) {

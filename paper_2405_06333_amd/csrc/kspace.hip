@@ -80,8 +80,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
             }
             x = rr[0]; y = rr[1]; z = rr[2];
             if (a.count) {
-                double xw, yw;
-                const int c = d.cbase + cell_of(x, y, z, d, &xw, &yw);
+                const int c = d.cbase + cell_of(x, y, z, d);
                 a.cell[g] = c;
                 a.slot[g] = atomicAdd(&a.count[c], 1);
             }

@@ -26,7 +26,8 @@ constexpr int kKChunk64 = 8;         // k-vectors per structure-factor block, FP
 constexpr int kPPad = 16;            // P is padded to a multiple of this
 constexpr int kMaxFamilies = 128;    // real-space image families (order, side) per system
 constexpr int kWave = 64;
-constexpr int kMaxRealSplit = 5;     // real space: column groups a target's pair work may be split into
+constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
+constexpr int kTileSplits = 4;       // FP64 real space: 1, 2, 4 or 8 waves share the pair work of 64 targets
 constexpr double kPi = 3.14159265358979323846;
 
 // One family of image sources for the real-space sum, seen from the target:
@@ -78,6 +79,7 @@ struct SysDesc {
     double sig_top, sig_bot;
     double Es[3], Cs[3], Gs[3], A1[3], A0[3];
     int surf;
+    int snake;                                 // numbering of the cells (column_of)
 };
 
 // Per-system scalars of the IBC and surface terms (kspace.hip: ibc_scalars)
@@ -133,15 +135,15 @@ struct Workspace {
     int *cell = nullptr, *slot = nullptr, *count = nullptr, *start = nullptr;
     int2 *tmp = nullptr;        // unordered cell lists: (caller index, global cell)
     int *scanbuf = nullptr;     // per-scan-block totals of the cell counts
-    double4 *sorted = nullptr;  // (x - x0(cell), y, z, q) in cell order, padded per system
+    double4 *sorted = nullptr;  // (x, y, z, q), x and y wrapped, in cell order, padded per system
     uint4 *src16 = nullptr;     // the same particles as fixed-point (x, y, z) and FP32 q (FP32 kernel)
     int *sidx = nullptr;        // caller index of sorted particle
-    int *scell = nullptr;       // local cell of sorted particle
+    int *scell = nullptr;       // local cell of sorted particle (FP32 kernel)
     double4 *freal = nullptr;   // per caller particle: F_real (x, y, z), phi_real
     double2 *dgreal = nullptr;  // per caller particle: d phi_real / d gamma_{top,bot}
     double *rpart = nullptr;    // per real-space wave: sum q phi, sum q dphi/dg_top, .../dg_bot
     // partial real-space outputs when the pair work of each target is split
-    // over several blocks (small N): [split][split_cap] / [split][waves]
+    // over several blocks (small N, FP32): [split][split_cap] / [split][waves]
     double4 *freal_s = nullptr;
     double2 *dgreal_s = nullptr;
     double *rpart_s = nullptr;
@@ -249,6 +251,7 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s);
 hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);
 hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);
+hipError_t launch_tile_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);   // FP64
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s);
 // short-range forces added to F, or with into_real to the pair kernel's
 // per-particle output (then folded into F with the real-space forces)
@@ -289,17 +292,31 @@ inline void prof_end(rbe2d_ctx *h, int slot, hipStream_t s) {
         (void)hipEventRecord(p.ev[slot][1][p.used[slot]++], s);
 }
 
-// Local cell of a particle: z-layer slowest, then x, then y (rows along y
-// are contiguous); xw, yw receive the wrapped lateral position.
-__device__ __forceinline__ int cell_of(double x, double y, double z, const SysDesc &d, double *xw, double *yw) {
-    double fx = x / d.Lx; fx -= floor(fx);
-    double fy = y / d.Ly; fy -= floor(fy);
-    *xw = fx * d.Lx;
-    *yw = fy * d.Ly;
-    const int cx = min(d.ncx - 1, max(0, (int)(*xw / d.hx)));
-    const int cy = min(d.ncy - 1, max(0, (int)(*yw / d.hy)));
+// x wrapped into [0, L)
+__device__ __forceinline__ double wrapped(double x, double L) {
+    double f = x / L;
+    f -= floor(f);
+    return f * L;
+}
+
+// Cells are numbered by layer in z, column in x within a layer and along y
+// within a column.  With `snake` (the tile kernel's grid) every second layer
+// and column runs backwards, so that the numbering is one path through the
+// slab: 64 consecutive particles stay close together also where they pass
+// from one column to the next.
+__device__ __forceinline__ int column_of(const SysDesc &d, int cx, int cz) {
+    return cz * d.ncx + ((d.snake & cz) ? d.ncx - 1 - cx : cx);
+}
+// first of the cells [lo, hi] along y of a column
+__device__ __forceinline__ int cells_from(const SysDesc &d, int col, int lo, int hi) {
+    return col * d.ncy + ((d.snake & col) ? d.ncy - 1 - hi : lo);
+}
+// Local cell of a particle.
+__device__ __forceinline__ int cell_of(double x, double y, double z, const SysDesc &d) {
+    const int cx = min(d.ncx - 1, max(0, (int)(wrapped(x, d.Lx) / d.hx)));
+    const int cy = min(d.ncy - 1, max(0, (int)(wrapped(y, d.Ly) / d.hy)));
     const int cz = min(d.ncz - 1, max(0, (int)(z / d.hz)));   // z outside (0,H) is flagged by prep
-    return (cz * d.ncx + cx) * d.ncy + cy;
+    return cells_from(d, column_of(d, cx, cz), cy, cy);
 }
 
 // Largest r in [0, n) with a[r] <= x, for a nondecreasing prefix array a[0..n].
