@@ -40,21 +40,55 @@ __device__ __forceinline__ void sincos_rev64(double r, double *s_out, double *c_
     *c_out = __hiloint2double(__double2hiint(c0) ^ csign, __double2loint(c0));
 }
 
-// sin of 2 pi r alone: r is reduced to the nearest half turn (exact, as
-// above), then the half-turn polynomial of sincos_fit.h on |t| <= pi/2,
-// within 2.3e-16 of sin; an odd half turn flips the sign.
+// r rounded to a multiple of 1/n (n a power of two, |n r| < 2^31): adding
+// 1.5 2^52 to n r leaves the rounded count in the low bits of the sum
+__device__ __forceinline__ double round_parts(double r, double n, uint32_t *count) {
+    constexpr double big = 6755399441055744.0;
+    const double t = fma(r, n, big);
+    *count = (uint32_t)__double2loint(t);
+    return fma(t - big, -1.0 / n, r);       // exact (Sterbenz)
+}
+
+// sin of 2 pi r alone: r is reduced to the nearest half turn, then the
+// half-turn polynomial of sincos_fit.h on |f| <= 1/4, within 3.4e-16 of sin;
+// an odd half turn flips the sign.
 __device__ __forceinline__ double sin_rev64(double r) {
-    const double kd = rint(2.0 * r);
-    const double f = fma(-0.5, kd, r);
-    const double t = f * (2.0 * kPi);
-    const double t2 = t * t;
+    uint32_t k;
+    const double f = round_parts(r, 2.0, &k);
+    const double u = f * f;
     double p = kSinHalf[kSinHalfTerms - 1];
 #pragma unroll
-    for (int k = kSinHalfTerms - 2; k >= 0; k--) p = fma(p, t2, kSinHalf[k]);
-    const double s = fma(t * t2, p, t);
-    // an odd half turn flips the sign bit (|2 r| < 2^31, as above)
-    const int sign = ((int)kd & 1) << 31;
-    return __hiloint2double(__double2hiint(s) ^ sign, __double2loint(s));
+    for (int i = kSinHalfTerms - 2; i >= 0; i--) p = fma(p, u, kSinHalf[i]);
+    const double s = f * p;
+    // (adding 2^31 flips the sign bit: one shift-and-add)
+    return __hiloint2double((int)((uint32_t)__double2hiint(s) + (k << 31)), __double2loint(s));
+}
+
+// a b + k with the constant k in scalar registers (the compiler copies it to
+// the vector register of a two-address form otherwise)
+__device__ __forceinline__ double fma_const(double a, double b, double k) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(k));
+    return d;
+}
+
+// sin and cos of 2 pi r from a table of 128 parts of the revolution (`tab`, a
+// copy of kPartTable in LDS), within 1.8e-16: 17 instructions where the
+// polynomials above take 31.  |128 r| < 2^31, as above.
+__device__ __forceinline__ void sincos_table64(double r, const double2 *tab, double *s_out, double *c_out) {
+    uint32_t m;
+    const double f = round_parts(r, (double)kParts, &m);
+    const double2 sc = tab[m & (kParts - 1)];
+    const double u = f * f;
+    double a = kSinPart[kSinPartTerms - 1];
+#pragma unroll
+    for (int k = kSinPartTerms - 2; k >= 0; k--) a = fma_const(a, u, kSinPart[k]);
+    double b = kCosPart[kCosPartTerms - 1];
+#pragma unroll
+    for (int k = kCosPartTerms - 2; k >= 0; k--) b = fma_const(b, u, kCosPart[k]);
+    const double s = f * a, c = fma(u, b, 1.0);
+    *s_out = fma(sc.y, s, sc.x * c);
+    *c_out = fma(sc.y, c, -(sc.x * s));
 }
 
 // x += dt v, then x, y wrapped into the box and z folded into [zlo, zhi]:
@@ -161,6 +195,20 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
     return r;
 }
 
-__device__ __forceinline__ double block_sum_r(double v, double *sh) { return block_sum(v, sh); }
+// exclusive scan of one int per thread over the block
+__device__ __forceinline__ int block_scan(int t, int *sh) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int incl = t;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += u;
+    }
+    if (lane == 63) sh[wid] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wid; w++) before += sh[w];
+    return before + incl - t;
+}
 
 }  // namespace rbe2d

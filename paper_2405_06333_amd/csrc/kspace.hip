@@ -12,7 +12,7 @@
 //    phase fract(nx fxh + ny fyh) + nx fxl + ny fyl (and likewise in z)
 //    keeps ~1e-8 revolution accuracy, and the hardware v_sin_f32/v_cos_f32
 //    take revolutions directly.
-//  * FP64 path: plain FP64 phase and a quarter-turn-reduced Taylor sincos.
+//  * FP64 path: plain FP64 phases, sine and cosine from devmath.h.
 #include <algorithm>
 
 #include "devmath.h"
@@ -174,7 +174,8 @@ __device__ void ibc_scalars(const ScalArgs &a, int r, int lane) {
 
 __global__ __launch_bounds__(64) void k_scalars(ScalArgs a) { ibc_scalars(a, blockIdx.x, threadIdx.x); }
 
-__global__ void k_ktable(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32, double4 *kn64);
+__global__ void k_ktable32(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32);
+__global__ void k_ktable64(const int32_t *kset, int P, int P_pad, double4 *kn64);
 
 static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
     PrepArgs a{};
@@ -185,8 +186,11 @@ static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
 
 void launch_ktable(rbe2d_ctx *h, hipStream_t s) {
     const int nk = h->n_sys * h->P_pad;
-    hipLaunchKernelGGL(k_ktable, dim3((nk + 63) / 64), dim3(64), 0, s, h->w.kset, h->n_sys, h->P, h->P_pad,
-                       h->w.kn32, h->w.kn64);
+    if (h->precision == RBE2D_PREC_FP32_PHASE)
+        hipLaunchKernelGGL(k_ktable32, dim3((nk + 63) / 64), dim3(64), 0, s, h->w.kset, h->n_sys, h->P, h->P_pad,
+                           h->w.kn32);
+    else
+        hipLaunchKernelGGL(k_ktable64, dim3(h->n_sys), dim3(kBlock), 0, s, h->w.kset, h->P, h->P_pad, h->w.kn64);
 }
 
 static ScalArgs scal_args(rbe2d_ctx *h) {
@@ -235,10 +239,10 @@ hipError_t launch_prep_md(rbe2d_ctx *h, double *pos, double *vel, const double *
 }
 
 // ---------------------------------------------------------------------------
-// 2. k-vector table (nx, ny, nz as floats / doubles, padded with zeros)
+// 2. k-vector tables (nx, ny, nz as floats / doubles, padded with zeros)
 // ---------------------------------------------------------------------------
 
-__global__ void k_ktable(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32, double4 *kn64) {
+__global__ void k_ktable32(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32) {
     const int kg = blockIdx.x * blockDim.x + threadIdx.x;
     if (kg >= n_sys * P_pad) return;
     const int r = kg / P_pad, l = kg - r * P_pad;
@@ -248,7 +252,42 @@ __global__ void k_ktable(const int32_t *kset, int n_sys, int P, int P_pad, float
         nx = n[0]; ny = n[1]; nz = n[2];
     }
     kn32[kg] = make_float4((float)nx, (float)ny, (float)nz, 0.0f);
-    kn64[kg] = make_double4((double)nx, (double)ny, (double)nz, 0.0);
+}
+
+// FP64: the k-vectors sorted by |nz|, (nx, ny, |nz|, +-(1 + index in the
+// k-set) with the sign of nz), by a counting sort in LDS, one block per system.
+// |nz| beyond the last bucket are left unsorted: the structure-factor pass
+// compares neighbours and only saves less.  (The order within a bucket is
+// that of the LDS atomics; no sum depends on it.)
+constexpr int kZBuckets = 2048;
+__global__ __launch_bounds__(kBlock) void k_ktable64(const int32_t *kset, int P, int P_pad, double4 *kn64) {
+    __shared__ int count[kZBuckets];
+    __shared__ int sh[kBlock / 64];
+    const int r = blockIdx.x;
+    const int32_t *n = kset + 3 * (int64_t)r * P;
+    constexpr int kPer = kZBuckets / kBlock;
+#pragma unroll
+    for (int b = 0; b < kPer; b++) count[b * kBlock + threadIdx.x] = 0;
+    __syncthreads();
+    for (int l = threadIdx.x; l < P; l += kBlock) atomicAdd(&count[min(abs(n[3 * l + 2]), kZBuckets - 1)], 1);
+    __syncthreads();
+    int v[kPer], t = 0;
+#pragma unroll
+    for (int b = 0; b < kPer; b++) { v[b] = count[kPer * threadIdx.x + b]; t += v[b]; }
+    int run = block_scan(t, sh);
+#pragma unroll
+    for (int b = 0; b < kPer; b++) { count[kPer * threadIdx.x + b] = run; run += v[b]; }
+    __syncthreads();
+    for (int l = threadIdx.x; l < P_pad; l += kBlock) {
+        const int64_t o = (int64_t)r * P_pad;
+        if (l < P) {
+            const int nx = n[3 * l], ny = n[3 * l + 1], nz = n[3 * l + 2];
+            const int k = atomicAdd(&count[min(abs(nz), kZBuckets - 1)], 1);
+            kn64[o + k] = make_double4((double)nx, (double)ny, fabs((double)nz), nz < 0 ? -1.0 - l : 1.0 + l);
+        } else {
+            kn64[o + l] = make_double4(0.0, 0.0, 0.0, 0.0);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -331,35 +370,49 @@ __global__ __launch_bounds__(kBlock) void k_sf32(const float4 *__restrict__ p32,
     }
 }
 
+// FP64: the phases' xy and z parts are taken separately, with e = q e^{2 pi i
+// phi_xy} and z = 2 pi phi_z, into the four sums of (Re e, Im e) x (cos z, sin z)
+// whose sums and differences are rho and rhohat.  The k-vectors come sorted by
+// |nz| (k_ktable64), and sin z and cos z are kept from one to the next while
+// |nz| stays the same; both come from the table of devmath.h.  Bound by VALU
+// issue (0.98 of the slots): 26 instructions per (particle, k) and 20 more
+// where |nz| changes, instead of 70 for two full sine-cosine pairs.  1e6 ions,
+// P = 500, half of the |nz| repeated: 0.60 ms instead of 0.96.
 template <int KC>
-__global__ __launch_bounds__(kBlock) void k_sf64(const double4 *__restrict__ p64,
-                                                 const double4 *__restrict__ kn, const int *tbase,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_sf64(const double4 *__restrict__ p64,
+                                                 const double4 *__restrict__ ks, const int *tbase,
                                                  int n_sys, int per_thread, int P_pad, int n_tiles,
                                                  double *__restrict__ part) {
     __shared__ double sh[kBlock / 64][4 * KC];
+    __shared__ double2 tab[kParts];
     const TileChunk tc = tile_chunk((int)blockIdx.x, P_pad / KC);
     if (tc.tile >= n_tiles) return;
+    if (threadIdx.x < kParts) tab[threadIdx.x] = make_double2(kPartTable[threadIdx.x][0], kPartTable[threadIdx.x][1]);
+    __syncthreads();
     const int r = find_sys(tbase, n_sys, tc.tile);
-    const double4 *knr = kn + (int64_t)r * P_pad + tc.kc * KC;
+    const double4 *ksr = ks + (int64_t)r * P_pad + tc.kc * KC;
     double acc[4 * KC];
 #pragma unroll
     for (int v = 0; v < 4 * KC; v++) acc[v] = 0.0;
     const int64_t base = (int64_t)tc.tile * kBlock * per_thread + threadIdx.x;
     for (int m = 0; m < per_thread; m++) {
-        const int64_t i = base + (int64_t)m * kBlock;
-        const double4 a = p64[i];
+        const double4 a = p64[base + (int64_t)m * kBlock];
+        double sz, cz;
 #pragma unroll
         for (int kk = 0; kk < KC; kk++) {
-            const double4 n = knr[kk];
-            const double pxy = fma(n.y, a.y, n.x * a.x);
-            const double pz = n.z * a.z;
-            double c1, s1, c2, s2;
-            sincos_rev64(pxy + pz, &s1, &c1);
-            sincos_rev64(pxy - pz, &s2, &c2);
-            acc[4 * kk + 0] = fma(a.w, c1, acc[4 * kk + 0]);
-            acc[4 * kk + 1] = fma(a.w, s1, acc[4 * kk + 1]);
-            acc[4 * kk + 2] = fma(a.w, c2, acc[4 * kk + 2]);
-            acc[4 * kk + 3] = fma(a.w, s2, acc[4 * kk + 3]);
+            const double4 n = ksr[kk];
+            if (kk == 0 || __double_as_longlong(n.z) != __double_as_longlong(ksr[kk - 1].z))
+                sincos_table64(n.z * a.z, tab, &sz, &cz);
+            double s, c;
+            sincos_table64(fma(n.y, a.y, n.x * a.x), tab, &s, &c);
+            const double qc = a.w * c, qs = a.w * s;
+            acc[4 * kk + 0] = fma(qc, cz, acc[4 * kk + 0]);
+            acc[4 * kk + 1] = fma(qs, sz, acc[4 * kk + 1]);
+            acc[4 * kk + 2] = fma(qs, cz, acc[4 * kk + 2]);
+            acc[4 * kk + 3] = fma(qc, sz, acc[4 * kk + 3]);
+            // keeps the sums of this k ahead of the next one's branch (the
+            // compiler gathers them at the end otherwise, with 182 registers)
+            asm volatile("" : "+v"(acc[4 * kk]), "+v"(acc[4 * kk + 1]), "+v"(acc[4 * kk + 2]), "+v"(acc[4 * kk + 3]));
         }
     }
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -367,10 +420,21 @@ __global__ __launch_bounds__(kBlock) void k_sf64(const double4 *__restrict__ p64
     if (lane < 4 * KC) sh[wid][lane] = acc[0];
     __syncthreads();
     if (threadIdx.x < 4 * KC) {
-        double t = 0.0;
+        // rho (re, im) and rhohat (re, im) of one k; for nz < 0 the two change places
+        const int kk = threadIdx.x >> 2, v = threadIdx.x & 3;
+        const double id = ksr[kk].w;    // +-(1 + index in the k-set), the sign of nz; 0: padding
+        if (id != 0.0) {
+            const int l = (int)fabs(id) - 1;
+            double t = 0.0, u = 0.0;
 #pragma unroll
-        for (int w = 0; w < kBlock / 64; w++) t += sh[w][threadIdx.x];
-        part[((int64_t)tc.tile * P_pad + tc.kc * KC) * 4 + threadIdx.x] = t;
+            for (int w = 0; w < kBlock / 64; w++) {
+                t += sh[w][4 * kk + 2 * (v & 1)];
+                u += sh[w][4 * kk + 2 * (v & 1) + 1];
+            }
+            // rho: cc - ss, sc + cs; rhohat: cc + ss, sc - cs
+            const bool hat = (v >= 2) != (id < 0.0);
+            part[((int64_t)tc.tile * P_pad + l) * 4 + v] = hat == ((v & 1) != 0) ? t - u : t + u;
+        }
     }
 }
 
@@ -391,6 +455,7 @@ struct AssembleArgs {
     const ImgTable *img;
     double *krec;
     float4 *kf32;
+    double *kf64;              // FP64: the force pass's records
     int n_sys, with_scalars;   // with_scalars: n_sys more blocks compute the IBC scalars
     ScalArgs sc;
 };
@@ -508,6 +573,13 @@ __global__ __launch_bounds__(64) void k_assemble(AssembleArgs a) {
     rec[10] = nx; rec[11] = ny; rec[12] = nz;
     rec[13] = rr; rec[14] = ri; rec[15] = kx * kx + ky * ky;
     rec[16] = magA; rec[17] = argA; rec[18] = magB; rec[19] = argB;
+    if (a.kf64) {
+        double *f = a.kf64 + kg * kKF64;
+        f[0] = nx; f[1] = ny; f[2] = nz;
+        f[4] = magA; f[5] = argA; f[6] = magB; f[7] = argB;
+        f[8] = c * Ar; f[9] = c * Ai; f[10] = c * Br; f[11] = c * Bi;
+        return;
+    }
     a.kf32[3 * kg] = make_float4((float)kx, (float)ky, (float)kz, (float)(kx * kx + ky * ky));
     a.kf32[3 * kg + 1] = make_float4((float)(c * Ar), (float)(c * Ai), (float)(c * Br), (float)(c * Bi));
     a.kf32[3 * kg + 2] = make_float4((float)magA, (float)argA, (float)magB, (float)argB);
@@ -544,7 +616,7 @@ hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool 
     AssembleArgs a;
     a.part = (const double *)h->w.sfpart; a.P = h->P; a.P_pad = h->P_pad;
     a.tbase = h->w.lay.tbase; a.kset = h->w.kset; a.sys = h->w.sys; a.img = h->w.img;
-    a.krec = h->w.krec; a.kf32 = h->w.kf32;
+    a.krec = h->w.krec; a.kf32 = h->w.kf32; a.kf64 = fp32 ? nullptr : h->w.kf64;
     a.n_sys = h->n_sys; a.with_scalars = with_scalars; a.sc = scal_args(h);
     prof_begin(h, 2, s);
     const dim3 ga(h->n_sys * h->P + (with_scalars ? h->n_sys : 0));
@@ -564,9 +636,8 @@ struct ForceArgs {
     const float4 *p32;
     const double4 *p64;
     const float4 *kn32;
-    const double4 *kn64;
     const float4 *kf32;
-    const double *krec;
+    const double *kf64;
     Layout lay;
     const SysDesc *sys;
     int n_sys, P, P_pad, k_per_split, n_threads;   // n_threads = particle blocks * kBlock
@@ -706,8 +777,20 @@ __global__ __launch_bounds__(kBlock) void k_force32(ForceArgs a) {
     }
 }
 
+// FP64.  The wave vectors enter as integers, n = (nx, ny, nz), and the sums are
+// scaled by 2 pi / L at the end: one 64-byte record per k (MODE 1: and 32 bytes
+// of amplitudes) comes by scalar loads, where k, n and the amplitudes of the
+// per-k records took 112 bytes from two arrays.  Bound by VALU issue, 40
+// instructions per (particle, k), two sines; 1e6 ions, P = 500: 0.61 ms
+// instead of 0.72 (46 instructions).
 template <int MODE>
 __global__ __launch_bounds__(kBlock) void k_force64(ForceArgs a) {
+    __shared__ double2 tab[MODE == 1 ? kParts : 1];
+    if (MODE == 1) {
+        if (threadIdx.x < kParts)
+            tab[threadIdx.x] = make_double2(kPartTable[threadIdx.x][0], kPartTable[threadIdx.x][1]);
+        __syncthreads();
+    }
     const int b = blockIdx.x;
     const int r = find_sys(a.lay.bbase, a.n_sys, b);
     const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
@@ -715,39 +798,43 @@ __global__ __launch_bounds__(kBlock) void k_force64(ForceArgs a) {
     const int64_t ii = (int64_t)a.lay.pbase[r] + iloc;
     const int64_t g = (int64_t)a.lay.off[r] + iloc;
     const double4 p = a.p64[ii];
-    const double4 *kn = a.kn64 + (int64_t)r * a.P_pad;
-    const double *kr = a.krec + (int64_t)r * a.P * kKRec;
+    const double *kf = a.kf64 + (int64_t)r * a.P * kKF64;
     const int l0 = blockIdx.y * a.k_per_split;
     const int l1 = min(a.P, l0 + a.k_per_split);
+    const SysDesc &d = a.sys[r];
+    const double wx = 2.0 * kPi * d.inv_Lx, wy = 2.0 * kPi * d.inv_Ly, wz = 2.0 * kPi * d.inv_Lz;
     double fx = 0, fy = 0, fz = 0, pt = 0;
     if (a.do_kspace) {
         for (int l = l0; l < l1; l++) {
-            const double4 n = kn[l];
-            const double *rec = kr + (int64_t)l * kKRec;
-            const double pxy = fma(n.y, p.y, n.x * p.x);
-            const double pz = n.z * p.z;
+            const double *f = kf + (int64_t)l * kKF64;
+            const double nx = f[0], ny = f[1], nz = f[2];
+            const double pxy = fma(ny, p.y, nx * p.x);
             double X, Y;   // Im(e^{-i ph} cA), Im(e^{-i phh} cB)
             if (MODE == 1) {
                 // the potential needs the real parts too
                 double c1, s1, c2, s2;
-                sincos_rev64(pxy + pz, &s1, &c1);
-                sincos_rev64(pxy - pz, &s2, &c2);
-                X = fma(rec[4], c1, -rec[3] * s1);
-                Y = fma(rec[6], c2, -rec[5] * s2);
-                pt = fma(rec[3], c1, pt); pt = fma(rec[4], s1, pt);
-                pt = fma(rec[5], c2, pt); pt = fma(rec[6], s2, pt);
+                sincos_table64(fma(nz, p.z, pxy), tab, &s1, &c1);
+                sincos_table64(fma(-nz, p.z, pxy), tab, &s2, &c2);
+                X = fma(f[9], c1, -f[8] * s1);
+                Y = fma(f[11], c2, -f[10] * s2);
+                pt = fma(f[8], c1, pt); pt = fma(f[9], s1, pt);
+                pt = fma(f[10], c2, pt); pt = fma(f[11], s2, pt);
             } else {
                 // polar form: one sine per product
-                X = rec[16] * sin_rev64((rec[17] - pxy) - pz);
-                Y = rec[18] * sin_rev64((rec[19] - pxy) + pz);
+                X = f[4] * sin_rev64(fma(-nz, p.z, f[5] - pxy));
+                Y = f[6] * sin_rev64(fma(nz, p.z, f[7] - pxy));
             }
             const double sp = X + Y, sm = X - Y;
-            fx = fma(rec[0], sp, fx);
-            fy = fma(rec[1], sp, fy);
-            fz = fma(rec[2], sm, fz);
-            if (MODE == 2) pt = fma(rec[15] * sp, sp, fma(rec[2] * sm, rec[2] * sm, pt));
+            fx = fma(nx, sp, fx);
+            fy = fma(ny, sp, fy);
+            fz = fma(nz, sm, fz);
+            if (MODE == 2) {
+                const double tx = wx * nx * sp, ty = wy * ny * sp, tz = wz * nz * sm;
+                pt = fma(tx, tx, fma(ty, ty, fma(tz, tz, pt)));
+            }
         }
     }
+    fx *= wx; fy *= wy; fz *= wz;
     if (a.split) {
         double *o = a.fpart + ((int64_t)blockIdx.y * a.n_threads + (int64_t)b * kBlock + threadIdx.x) * 4;
         o[0] = fx; o[1] = fy; o[2] = fz; o[3] = pt;
@@ -782,8 +869,8 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
                          hipStream_t s, double *var) {
     if (h->n_total == 0) return hipSuccess;
     ForceArgs a;
-    a.p32 = h->w.p32; a.p64 = h->w.p64; a.kn32 = h->w.kn32; a.kn64 = h->w.kn64;
-    a.kf32 = h->w.kf32; a.krec = h->w.krec; a.lay = h->w.lay; a.sys = h->w.sys;
+    a.p32 = h->w.p32; a.p64 = h->w.p64; a.kn32 = h->w.kn32;
+    a.kf32 = h->w.kf32; a.kf64 = h->w.kf64; a.lay = h->w.lay; a.sys = h->w.sys;
     a.n_sys = h->n_sys; a.P = h->P; a.P_pad = h->P_pad; a.n_threads = h->n_blocks * kBlock;
     a.pos = pos; a.q = q; a.scal = h->w.scal; a.freal = h->w.freal;
     a.fpart = h->w.fpart; a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = var;

@@ -92,6 +92,10 @@ constexpr int kScal = 20;
 //   [16..19] polar form |cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi
 constexpr int kKRec = 20;
 
+// Per-k record of the FP64 force pass: [0..2] nx, ny, nz  [4..7] polar form
+// [8..11] c*A, c*B, as above; 128 bytes apart.
+constexpr int kKF64 = 16;
+
 // Layout of the particles of all systems in the internal arrays (device
 // copies, n_sys + 1 entries each, prefix form: entry r is the start of
 // system r, entry n_sys the total).
@@ -125,11 +129,12 @@ struct Workspace {
     // k-space (P_pad k-vectors per system)
     int32_t *kset = nullptr;    // n_sys x P x 3
     float4 *kn32 = nullptr;     // per k: (nx, ny, nz, 0) as floats
-    double4 *kn64 = nullptr;    // per k: (nx, ny, nz, 0) as doubles
+    double4 *kn64 = nullptr;    // per k, sorted by |nz|: (nx, ny, |nz|, +-(1 + index)) (kspace.hip)
     void *sfpart = nullptr;     // structure-factor partials [tile][P_pad][4] (FP64)
     double *krec = nullptr;     // per-k records, kKRec doubles each (n_sys x P)
     float4 *kf32 = nullptr;     // per k: (kx, ky, kz, kx^2 + ky^2), (cAr, cAi, cBr, cBi),
                                 // (|cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi)
+    double *kf64 = nullptr;     // per k: kKF64 doubles (FP64)
     double *fpart = nullptr;    // force-pass partials [ksplit][blocks * kBlock][4]
     // real space
     int *cell = nullptr, *slot = nullptr, *count = nullptr, *start = nullptr;
