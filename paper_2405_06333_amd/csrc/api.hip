@@ -450,9 +450,11 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     // FP32 pair kernel: the split is only used when there are too few targets
     // to fill the chip
     h->split_cap = fp32 ? std::min<int64_t>(nc, 1 << 18) : 0;
-    A(&w.freal_s, kMaxRealSplit * h->split_cap);
-    A(&w.dgreal_s, kMaxRealSplit * h->split_cap);
-    A(&w.rpart_s, fp32 ? kMaxRealSplit * 3 * (h->cap_sorted / kWave) : 0);
+    const int64_t fam_cap = fp32 ? std::min<int64_t>(nc, kFamilySplitMax) : 0;
+    const int64_t parts = std::max(kMaxRealSplit * h->split_cap, kMaxRealSplit * kMaxFamilySplit * fam_cap);
+    A(&w.freal_s, parts);
+    A(&w.dgreal_s, h->one_stream ? 0 : parts);   // (the call without a handle forms no derivatives)
+    A(&w.rpart_s, fp32 ? kMaxRealSplit * kMaxFamilySplit * 3 * (h->cap_sorted / kWave) : 0);
     A(&w.spart, 2 * (h->cap_sorted / kWave));
     A(&w.err, 4);
     A(&w.step, 1);

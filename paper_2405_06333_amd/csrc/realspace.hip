@@ -334,6 +334,12 @@ struct LaneRings : TargetSums<DG> {
             *reinterpret_cast<float4 *>(base + at) = make_float4(dx, dy, dz, qs);
         }
     }
+    // without a branch: rejected pairs go to the slot behind the ring
+    __device__ void push_masked(bool acc, float dx, float dy, float dz, float qs) {
+        const uint32_t at = acc ? wpos & kMask : (uint32_t)(threadIdx.x * sizeof(float4)) + Q * kSlot;
+        *reinterpret_cast<float4 *>(base + at) = make_float4(dx, dy, dz, qs);
+        wpos += acc ? kSlot : 0u;
+    }
     __device__ bool full() const { return __ballot(wpos - rpos > kRoom) != 0; }
     // one round: evaluate the oldest entry of every lane with fill f > 0
     __device__ void round(uint32_t f) {
@@ -386,13 +392,21 @@ struct LaneRings : TargetSums<DG> {
 // records.  It evaluates erfc/exp and the per-drain partial sums in FP32 and
 // accumulates the drains in FP64.  The order of every sum is fixed by the
 // data, so the results are bitwise reproducible.
-template <bool WANT_DG, bool ISO>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RBE2D_REAL_WAVES32, 8)))
+//
+// SPLIT: too few targets to fill the chip.  Block row y takes every nsplit-th
+// column and block layer z one group of image families (0: the real charges);
+// a wave is then alone on its SIMD and bound by its own chain of instructions,
+// branches above all: the candidates of a batch are tested without one, and the
+// target itself is not sent through the FP64 geometry.  (Two rounds at a time,
+// or two and four batches of sources in flight, took 4 to 10 % longer.)  The FP32 sums are those of
+// the same drains either way.  3,000 ions, 300 pairs each: 63 us instead of 99.
+template <bool WANT_DG, bool ISO, bool SPLIT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SPLIT ? 2 : RBE2D_REAL_WAVES32, 8)))
 void k_real(RealArgs a) {
     constexpr int U = RBE2D_REAL_U32;      // source loads in flight per lane, twice
     constexpr int kRingQ = RBE2D_RING_Q;   // ring entries per lane
     using Queue = LaneRings<kRingQ, U, ISO, WANT_DG>;
-    __shared__ __align__(16) unsigned char lds[sizeof(float4) * kRingQ * kBlock];
+    __shared__ __align__(16) unsigned char lds[sizeof(float4) * (kRingQ + (SPLIT ? 1 : 0)) * kBlock];
     const double4 *src = a.src;
     const int tid = threadIdx.x;
     // Blocks are dealt round-robin to the 8 XCDs.  Each XCD runs C contiguous
@@ -437,8 +451,11 @@ void k_real(RealArgs a) {
     // claims all 128 registers a wave may hold at 4 waves per SIMD (the kernel
     // uses 119): waves of the force pass (32 registers) would join the four
     // otherwise and slow both, MD step of the 1e6-ion slab 1.25 instead of 1.22 ms
-    asm volatile("" ::: "v127");
-    for (int f = 0; f <= d.nfam; f++) {
+    if constexpr (!SPLIT) asm volatile("" ::: "v127");
+    // with more than one layer of blocks: layer 0 the real charges, layers z >
+    // 0 the families z, z + (layers - 1), ...
+    const int fstep = SPLIT && gridDim.z > 1 ? (blockIdx.z == 0 ? kMaxFamilies + 1 : (int)gridDim.z - 1) : 1;
+    for (int f = SPLIT ? (int)blockIdx.z : 0; f <= d.nfam; f += fstep) {
         double sz = 1.0, czs = 0.0, w = 1.0, zsign = 1.0, dwt = 0.0, dwb = 0.0;
         if (f > 0) {
             const Family fm = fams[f - 1];
@@ -479,35 +496,76 @@ void k_real(RealArgs a) {
                 // each to FP32; exact FP64 geometry for pairs within `near`
                 const float rc2s = ISO ? d.rc2q : d.rc2f;
                 const float near2s = ISO ? d.near2q : d.near2f;
+                // exact FP64 displacement from sorted source js; false for zero
+                // (the target itself in the direct family)
+                auto near_pair = [&](int js, float &dx, float &dy, float &dz) {
+                    const double4 s64 = src[js];
+                    double ex = me.x - s64.x, ey = me.y - s64.y;
+                    // the true displacement is below `near`, far from half a
+                    // period, so rounding by the reciprocal finds the same image
+                    ex -= d.Lx * rint(ex * d.inv_Lx);
+                    ey -= d.Ly * rint(ey * d.inv_Ly);
+                    const double ez = tz - s64.z;
+                    const bool apart = ex != 0.0 || ey != 0.0 || ez != 0.0;
+                    if (ISO) { ex *= d.fxs; ey *= d.fxs; }
+                    dx = (float)ex; dy = (float)ey; dz = (float)(ISO ? ez * d.fxs : ez);
+                    return apart;
+                };
                 auto body = [&](const uint4 (&sv)[U], int m0) {
                     if (qu.full()) qu.drain();
                     const bool inA = m0 < c4a;
                     const int lim = inA ? lenA : tot;          // candidates m < lim
+                    if constexpr (SPLIT) {
+                        // the four tests without a branch, one for the close
+                        // pairs; the target itself is told by its index
+                        const int j0 = jbA + m0;               // (no run B)
+                        float dx[U], dy[U], dz[U];
+                        bool acc[U], close[U], any = false;
 #pragma unroll
-                    for (int k = 0; k < U; k++) {
-                        const int m = m0 + k;
-                        float dx = (float)(int)(xtf - sv[k].x);
-                        float dy = (float)(int)(ytf - sv[k].y);
-                        float dz = (float)(int)(tzf - sv[k].z);
-                        if (!ISO) { dx *= d.ux; dy *= d.uy; dz *= d.uz; }
-                        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                        bool acc = m < lim && r2 < rc2s;
-                        if (acc && r2 < near2s) {
-                            const double4 s64 = src[inA ? jbA + m : jbB + (m - c4a)];
-                            double ex = me.x - s64.x, ey = me.y - s64.y;
-                            // the true displacement is below `near`, far from half a
-                            // period, so rounding by the reciprocal finds the same image
-                            ex -= d.Lx * rint(ex * d.inv_Lx);
-                            ey -= d.Ly * rint(ey * d.inv_Ly);
-                            const double ez = tz - s64.z;
-                            // zero displacement only for the target itself (direct family)
-                            acc = ex != 0.0 || ey != 0.0 || ez != 0.0;
-                            if (ISO) { ex *= d.fxs; ey *= d.fxs; }
-                            dx = (float)ex; dy = (float)ey; dz = (float)(ISO ? ez * d.fxs : ez);
+                        for (int k = 0; k < U; k++) {
+                            dx[k] = (float)(int)(xtf - sv[k].x);
+                            dy[k] = (float)(int)(ytf - sv[k].y);
+                            dz[k] = (float)(int)(tzf - sv[k].z);
+                            if (!ISO) { dx[k] *= d.ux; dy[k] *= d.uy; dz[k] *= d.uz; }
+                            const float r2 = fmaf(dx[k], dx[k], fmaf(dy[k], dy[k], dz[k] * dz[k]));
+                            acc[k] = m0 + k < lenA && r2 < rc2s;
+                            if (f == 0 && j0 + k == t) acc[k] = false;
+                            close[k] = acc[k] && r2 < near2s;
+                            any = any || close[k];
                         }
-                        qu.push(acc, dx, dy, dz, __uint_as_float(sv[k].w));
+                        if (__ballot(any) != 0) {
+#pragma unroll
+                            for (int k = 0; k < U; k++)
+                                if (close[k]) acc[k] = near_pair(j0 + k, dx[k], dy[k], dz[k]);
+                        }
+#pragma unroll
+                        for (int k = 0; k < U; k++) qu.push_masked(acc[k], dx[k], dy[k], dz[k], __uint_as_float(sv[k].w));
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < U; k++) {
+                            const int m = m0 + k;
+                            float dx = (float)(int)(xtf - sv[k].x);
+                            float dy = (float)(int)(ytf - sv[k].y);
+                            float dz = (float)(int)(tzf - sv[k].z);
+                            if (!ISO) { dx *= d.ux; dy *= d.uy; dz *= d.uz; }
+                            const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                            bool acc = m < lim && r2 < rc2s;
+                            if (acc && r2 < near2s) acc = near_pair(inA ? jbA + m : jbB + (m - c4a), dx, dy, dz);
+                            qu.push(acc, dx, dy, dz, __uint_as_float(sv[k].w));
+                        }
                     }
                 };
+                if constexpr (SPLIT) {
+                    // no prefetch: the chain of instructions is the longer one
+                    for (int m0 = 0; m0 < maxtot; m0 += U) {
+                        uint4 s[U];
+                        const uint4 *pq = a.src16 + rec(m0);
+#pragma unroll
+                        for (int k = 0; k < U; k++) s[k] = pq[k];
+                        body(s, m0);
+                    }
+                    return;
+                }
                 uint4 sa[U], sb[U];
                 {
                     const uint4 *pq = a.src16 + rec(0);
@@ -592,19 +650,25 @@ void k_real(RealArgs a) {
         };
         const int xlo = allx ? 0 : -d.reach, xhi = allx ? d.ncx - 1 : d.reach;
         const int ncol = xhi - xlo + 1;
-        for (int lz = wzlo; lz <= wzhi; lz++) {
-            const bool lay_on = lz >= lzlo && lz <= lzhi;
+        auto layer_runs = [&](int lz, int ox) {
             const float dzmin = (float)fmax(0.0, fmax(lz * d.hz - tz, tz - (lz + 1) * d.hz));
-            if (a.nsplit == 1) {
+            return col_runs(lz >= lzlo && lz <= lzhi, lz, dzmin, ox);
+        };
+        if constexpr (SPLIT) {
+            // layer by layer, this row's columns
+            for (int lz = wzlo; lz <= wzhi; lz++)
+                for (int ox = xlo + (int)blockIdx.y; ox <= xhi; ox += a.nsplit) scan_col(layer_runs(lz, ox));
+        } else {
+            for (int lz = wzlo; lz <= wzhi; lz++) {
                 // columns in the order 0, -1, +1, -2, +2 (every column in
                 // index order when all are searched): the first alone, then
                 // pairs scanned as one sequence per lane
                 auto col = [&](int i) { return allx ? i : (i == 0 ? 0 : ((i & 1) ? -((i + 1) >> 1) : (i >> 1))); };
-                scan_col(col_runs(lay_on, lz, dzmin, col(0)));
+                scan_col(layer_runs(lz, col(0)));
                 for (int i = 1; i < ncol; i += 2) {
-                    const Runs A = col_runs(lay_on, lz, dzmin, col(i));
+                    const Runs A = layer_runs(lz, col(i));
                     if (i + 1 < ncol) {
-                        const Runs B = col_runs(lay_on, lz, dzmin, col(i + 1));
+                        const Runs B = layer_runs(lz, col(i + 1));
                         scan(A.jb1, A.len1, B.jb1, B.len1);
                         if (__ballot(A.len2 > 0) != 0) scan(A.jb2, A.len2, A.jb2, 0);
                         if (__ballot(B.len2 > 0) != 0) scan(B.jb2, B.len2, B.jb2, 0);
@@ -612,13 +676,11 @@ void k_real(RealArgs a) {
                         scan_col(A);
                     }
                 }
-            } else {
-                for (int ox = xlo + (int)blockIdx.y; ox <= xhi; ox += a.nsplit)
-                    scan_col(col_runs(lay_on, lz, dzmin, ox));
             }
         }
         qu.flush();
     }
+    const int split = (int)(blockIdx.y + blockIdx.z * gridDim.y);
     const double fx = qu.fx, fy = qu.fy, fz = qu.fz, phi = qu.phi, dpt = qu.dpt, dpb = qu.dpb;
     double qphi = 0.0, qdt = 0.0, qdb = 0.0;
     if (active) {
@@ -626,8 +688,8 @@ void k_real(RealArgs a) {
         const double qi = me.w * d.pref;
         const double4 fo = make_double4(qi * fx, qi * fy, qi * fz, d.pref * phi);
         const double2 go = make_double2(d.pref * dpt, d.pref * dpb);
-        if (a.nsplit > 1) {
-            const int64_t o = (int64_t)blockIdx.y * a.split_stride + i;
+        if (SPLIT) {
+            const int64_t o = (int64_t)split * a.split_stride + i;
             a.freal_s[o] = fo;
             if (WANT_DG) a.dgreal_s[o] = go;
         } else {
@@ -645,36 +707,54 @@ void k_real(RealArgs a) {
     if (WANT_DG) { qdt = wave_sum(qdt); qdb = wave_sum(qdb); }
     if ((tid & (kWave - 1)) == 0 && t / kWave < a.n_waves) {
         const int wv = t / kWave;
-        double *o = a.nsplit > 1 ? a.rpart_s + 3 * ((int64_t)blockIdx.y * a.rsplit_stride + wv) : a.rpart + 3 * wv;
+        double *o = SPLIT ? a.rpart_s + 3 * ((int64_t)split * a.rsplit_stride + wv) : a.rpart + 3 * wv;
         o[0] = qphi;
         o[1] = qdt;
         o[2] = qdb;
     }
 }
 
-// sum of the split partial outputs, in split order
-__global__ __launch_bounds__(kBlock) void k_real_combine(RealArgs a, int n_total, int want_dg) {
+// sum of the split partial outputs, in split order; the loads of five parts
+// at a time are in flight together
+__global__ __launch_bounds__(kBlock) void k_real_combine(RealArgs a, int nparts, int n_total, int want_dg) {
     const int g = blockIdx.x * kBlock + threadIdx.x;
+    constexpr int B = kMaxRealSplit;
     if (g < n_total) {
-        double4 f = a.freal_s[g];
-        double2 dg = want_dg ? a.dgreal_s[g] : make_double2(0.0, 0.0);
-        for (int s = 1; s < a.nsplit; s++) {
-            const double4 v = a.freal_s[(int64_t)s * a.split_stride + g];
-            f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
-            if (want_dg) {
-                const double2 u = a.dgreal_s[(int64_t)s * a.split_stride + g];
-                dg.x += u.x; dg.y += u.y;
+        double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
+        double2 dg = make_double2(0.0, 0.0);
+        for (int s0 = 0; s0 < nparts; s0 += B) {
+            double4 v[B];
+            double2 u[B];
+#pragma unroll
+            for (int k = 0; k < B; k++) {
+                const int64_t o = (int64_t)min(s0 + k, nparts - 1) * a.split_stride + g;
+                v[k] = a.freal_s[o];
+                if (want_dg) u[k] = a.dgreal_s[o];
             }
+#pragma unroll
+            for (int k = 0; k < B; k++)
+                if (s0 + k < nparts) {
+                    f.x += v[k].x; f.y += v[k].y; f.z += v[k].z; f.w += v[k].w;
+                    if (want_dg) { dg.x += u[k].x; dg.y += u[k].y; }
+                }
         }
         a.freal[g] = f;
         if (want_dg) a.dgreal[g] = dg;
     }
     if (g < a.n_waves) {
-        for (int c = 0; c < 3; c++) {
-            double v = 0.0;
-            for (int s = 0; s < a.nsplit; s++) v += a.rpart_s[3 * ((int64_t)s * a.rsplit_stride + g) + c];
-            a.rpart[3 * g + c] = v;
+        double w[3] = {0.0, 0.0, 0.0};
+        for (int s0 = 0; s0 < nparts; s0 += B) {
+            double v[B][3];
+#pragma unroll
+            for (int k = 0; k < B; k++)
+                for (int c = 0; c < 3; c++)
+                    v[k][c] = a.rpart_s[3 * ((int64_t)min(s0 + k, nparts - 1) * a.rsplit_stride + g) + c];
+#pragma unroll
+            for (int k = 0; k < B; k++)
+                if (s0 + k < nparts)
+                    for (int c = 0; c < 3; c++) w[c] += v[k][c];
         }
+        for (int c = 0; c < 3; c++) a.rpart[3 * g + c] = w[c];
     }
 }
 
@@ -718,7 +798,7 @@ hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
     r.sys = h->w.sys; r.fam = h->w.fam; r.lay = h->w.lay; r.n_sys = h->n_sys; r.n_waves = h->n_swaves;
     r.freal = h->w.freal; r.dgreal = h->w.dgreal; r.rpart = h->w.rpart;
     r.freal_s = h->w.freal_s; r.dgreal_s = h->w.dgreal_s; r.rpart_s = h->w.rpart_s;
-    r.split_stride = h->split_cap;
+    r.split_stride = h->n_total;
     r.rsplit_stride = (int)(h->cap_sorted / kWave);
     // too few targets to fill the chip: split each target's x-columns over
     // several blocks (about 4096 waves in flight is enough)
@@ -733,19 +813,27 @@ hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
     r.nblocks = nbs;
     const int nch = 8 * RBE2D_REAL_CHUNKS;
     const int nbc = (nbs + nch - 1) / nch * nch;
-    const dim3 grid(nbc, r.nsplit);
+    // few targets: the image families in two more layers of blocks
+    int nfam = 0;
+    for (const SysHost &sh : h->sys) nfam = std::max(nfam, sh.d.nfam);
+    const int layers = r.nsplit > 1 && h->n_total <= kFamilySplitMax ? std::min(kMaxFamilySplit, 1 + nfam) : 1;
+    const dim3 grid(nbc, r.nsplit, layers);
     prof_begin(h, 4, s);
-    if (h->iso) {
-        if (want_dg) hipLaunchKernelGGL((k_real<true, true>), grid, dim3(kBlock), 0, s, r);
-        else hipLaunchKernelGGL((k_real<false, true>), grid, dim3(kBlock), 0, s, r);
-    } else {
-        if (want_dg) hipLaunchKernelGGL((k_real<true, false>), grid, dim3(kBlock), 0, s, r);
-        else hipLaunchKernelGGL((k_real<false, false>), grid, dim3(kBlock), 0, s, r);
+    const int variant = (want_dg ? 1 : 0) + (h->iso ? 2 : 0) + (r.nsplit > 1 ? 4 : 0);
+    switch (variant) {
+    case 0: hipLaunchKernelGGL((k_real<false, false, false>), grid, dim3(kBlock), 0, s, r); break;
+    case 1: hipLaunchKernelGGL((k_real<true, false, false>), grid, dim3(kBlock), 0, s, r); break;
+    case 2: hipLaunchKernelGGL((k_real<false, true, false>), grid, dim3(kBlock), 0, s, r); break;
+    case 3: hipLaunchKernelGGL((k_real<true, true, false>), grid, dim3(kBlock), 0, s, r); break;
+    case 4: hipLaunchKernelGGL((k_real<false, false, true>), grid, dim3(kBlock), 0, s, r); break;
+    case 5: hipLaunchKernelGGL((k_real<true, false, true>), grid, dim3(kBlock), 0, s, r); break;
+    case 6: hipLaunchKernelGGL((k_real<false, true, true>), grid, dim3(kBlock), 0, s, r); break;
+    default: hipLaunchKernelGGL((k_real<true, true, true>), grid, dim3(kBlock), 0, s, r);
     }
     if (r.nsplit > 1) {
         const int64_t n = std::max<int64_t>(h->n_total, h->n_swaves);
         hipLaunchKernelGGL(k_real_combine, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, r,
-                           (int)h->n_total, (int)want_dg);
+                           r.nsplit * layers, (int)h->n_total, (int)want_dg);
     }
     prof_end(h, 4, s);
     return hipGetLastError();
