@@ -402,14 +402,13 @@ void free_all(rbe2d_ctx *h) {
     if (h->lay_ev) (void)hipEventDestroy(h->lay_ev);
     if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
     if (h->join_ev) (void)hipEventDestroy(h->join_ev);
-    if (h->tail_ev) (void)hipEventDestroy(h->tail_ev);
     if (h->side) (void)hipStreamDestroy(h->side);
 }
 
 // Every device workspace of a handle, in one fixed order: A(&ptr, count) is
 // called once per buffer (count elements of *ptr's type).  The handle's
 // capacities (n_sys, n_cap, cap_particles, cap_sorted, total_cells, P,
-// fpart_blocks) must be set.  own_kset: the handle holds its k-set (else the
+// precision) must be set.  own_kset: the handle holds its k-set (else the
 // caller's device array is used in place).
 template <typename Alloc>
 void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
@@ -436,7 +435,6 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     A(&w.krec, (size_t)n * h->P * kKRec);
     A(&w.kf32, 3 * (size_t)n * h->P);
     A(&w.kf64, kKF64 * (size_t)n * h->P);
-    A(&w.fpart, (size_t)h->fpart_blocks * kBlock * 4);
     const int64_t nc = std::max<int64_t>(h->n_cap, 1);
     A(&w.cell, nc); A(&w.slot, nc); A(&w.tmp, nc);
     A(&w.count, cells); A(&w.start, cells + 1); A(&w.scanbuf, cells / 1024 + 2);
@@ -490,6 +488,7 @@ rbe2d_status create_handle(int n, const rbe2d_params *ps, bool batch, rbe2d_hand
         SysDesc &d = h->sys[r].d;
         d.cbase = cells;
         cells += d.ncx * d.ncy * d.ncz;
+        h->max_cells = std::max(h->max_cells, d.ncx * d.ncy * d.ncz);
         for (int ax = 0; ax < 3; ax++) {
             d.cdf_off[ax] = (int)cdf_total;
             cdf_total += h->sys[r].cdf[ax].size();
@@ -511,7 +510,7 @@ rbe2d_status create_handle(int n, const rbe2d_params *ps, bool batch, rbe2d_hand
     h->cap_particles = std::max<int64_t>(cap_p, kTileMax);
     h->cap_sorted = std::max<int64_t>(cap_s, kWave);
     h->total_cells = cells;
-    h->fpart_blocks = std::min<int64_t>(64 * (h->cap_particles / kBlock), 4096);
+    h->split_blocks = 4096;
     (void)hipGetDevice(&h->device);
 
     hipError_t e = hipSuccess;
@@ -541,7 +540,6 @@ rbe2d_status create_handle(int n, const rbe2d_params *ps, bool batch, rbe2d_hand
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&h->tail_ev, hipEventDisableTiming);
     if (e != hipSuccess) {
         const bool oom = e == hipErrorOutOfMemory;
         free_all(h);
@@ -593,6 +591,7 @@ rbe2d_status compute_layout(rbe2d_ctx *h, const int64_t *counts, int *lay) {
     for (int r = 0; r <= n; r++) { bb[r] = pb[r] / kBlock; tb[r] = pb[r] / tile; }
     h->per = per;
     h->n_total = total;
+    h->max_n = n > 0 ? (int)*std::max_element(counts, counts + n) : 0;
     h->n_blocks = bb[n];
     h->n_tiles = tb[n];
     h->n_swaves = sb[n] / kWave;
@@ -638,11 +637,30 @@ rbe2d_status check_arrays(rbe2d_ctx *h, const double *pos, const double *q) {
     return RBE2D_OK;
 }
 
-// prep + structure factors + real space: everything the outputs depend on
+// One stream for the whole call?  Two let the k-space chain and the pair
+// kernel share the chip, but cost four event calls (15 to 20 us on the host,
+// as much as three launches) and the waits between streams.  Force calls
+// follow each other without a wait between them: up to kOneStreamForces ions
+// the host is what they wait for (N = 500, P = 100: 51 us on one stream, 70 on
+// two; from N = 1500 on two streams are 2 to 8 % faster).  An energy is read,
+// or differentiated, by the program that asked for it before its next one, so
+// that host and GPU take turns (energy and gradient of 20000 ions: 223 against
+// 253 us FP64, 229 against 256 FP32; of 60000: 321 against 362, 304 against
+// 301).
+constexpr int64_t kOneStreamForces = 1024, kOneStreamEnergy = 49152;
+bool on_one_stream(const rbe2d_ctx *h, int64_t limit) { return h->one_stream || h->n_total <= limit; }
+
+// `to` waits for what `from` has been given so far
+rbe2d_status stream_wait(rbe2d_ctx *h, hipStream_t to, hipStream_t from, hipEvent_t ev) {
+    RBE2D_TRY(h, hipEventRecord(ev, from), "stream event");
+    RBE2D_TRY(h, hipStreamWaitEvent(to, ev, 0), "stream wait");
+    return RBE2D_OK;
+}
+
 // prep + structure factors + real space: everything the outputs depend on.
-// With both halves requested, the k-space chain (prep, structure factors,
-// per-k assembly) runs on the side stream while the cell list and the pair
-// kernel run on `s`; `s` waits for both.  The cell build is latency- and
+// With both halves requested, the k-space chain (structure factors, per-k
+// assembly) runs on the side stream while the cell list and the pair kernel
+// run on `s`; `s` waits for both.  The cell build is latency- and
 // atomic-bound and the pair kernel latency-limited, so the VALU-bound
 // structure-factor pass fills their idle issue slots (1.79 instead of
 // 1.93 ms per step of the 1e6-ion slab).  The fork and join are events, so
@@ -651,58 +669,73 @@ rbe2d_status run_common(rbe2d_ctx *h, const double *pos, const double *q, uint32
                         hipStream_t s) {
     const bool kside = (flags & (RBE2D_KSPACE | RBE2D_IBC)) != 0;
     const bool real = (flags & RBE2D_REAL) != 0;
-    hipStream_t ks = s;
-    if (kside && real && h->n_total > 0 && !h->one_stream) {
-        ks = h->side;
-        RBE2D_TRY(h, hipEventRecord(h->fork_ev, s), "fork event");
-        RBE2D_TRY(h, hipStreamWaitEvent(ks, h->fork_ev, 0), "fork wait");
+    // with k-space the assembly launch computes the IBC scalars
+    const bool sc_asm = (flags & RBE2D_KSPACE) != 0;
+    if (kside) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
+    const bool two = sc_asm && real && h->n_total > 0 && !on_one_stream(h, kOneStreamEnergy);
+    if (two) {
+        rbe2d_status st = stream_wait(h, h->side, s, h->fork_ev);
+        if (st) return st;
     }
-    // with two streams, real space is enqueued first (its cell list starts
-    // ahead of the structure factors); on one stream the order is as listed
-    if (real && ks != s) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s), "real-space launch");
-    if (kside) RBE2D_TRY(h, launch_prep(h, pos, q, ks), "prep launch");
-    if (flags & RBE2D_KSPACE) RBE2D_TRY(h, launch_kcoef_sf(h, ks, false, want_dg), "structure-factor launch");
-    if (real && ks == s) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s), "real-space launch");
-    if (ks != s) {
-        RBE2D_TRY(h, hipEventRecord(h->join_ev, ks), "join event");
-        RBE2D_TRY(h, hipStreamWaitEvent(s, h->join_ev, 0), "join wait");
-    }
-    return RBE2D_OK;
+    // real space is enqueued first: its cell list starts ahead of the structure factors
+    if (real) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s), "real-space launch");
+    if (sc_asm) RBE2D_TRY(h, launch_kcoef_sf(h, two ? h->side : s, true, want_dg), "structure-factor launch");
+    return two ? stream_wait(h, s, h->side, h->join_ev) : RBE2D_OK;
 }
+
+// What compute_forces does besides the forces: the closing half kick
+// v += dt/2 F of an MD step (vel), the MD's short-range forces (mx), the
+// energies and a copy of the error word.
+struct ForceJob {
+    double *vel = nullptr;
+    double dt = 0.0;
+    const MdExtra *mx = nullptr;
+    double *energy = nullptr;
+    int32_t *err_out = nullptr;
+    bool prepared = false;        // an MD pass has prepared particles, cells and k-set (parts: all)
+    long long *step = nullptr;    // MD step counter to advance once the k-set's step is over
+};
 
 // Forces of `parts` into F (added to F with `accumulate`).  With real space
 // and k-space/IBC both requested, the whole k-space chain including its force
-// scatter runs on the side stream (writing F) while the cell list and pair
-// kernel run on `s`; after the join one pass adds the real-space forces and,
-// when vel is set, applies the closing half kick v += dt/2 F of an MD step.
-// With mxs set, the MD's short-range forces are added too (on `s`, into the
-// pair kernel's output while the k-space chain runs).
+// scatter runs on the side stream (writing F) while the cell list, the pair
+// kernel and the short-range kernel run on `s`; after the join one pass adds
+// their forces, with the half kick and the energies as part of it.  On one
+// stream the force scatter comes last and does all of that.
 rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, double *F, uint32_t parts,
-                            bool accumulate, double *vel, double dt, hipStream_t s, const MdExtra *mxs) {
-    const bool kside = (parts & (RBE2D_KSPACE | RBE2D_IBC)) != 0;
-    if (kside && (parts & RBE2D_REAL) && h->n_total > 0 && !h->one_stream) {
-        hipStream_t ks = h->side;
-        RBE2D_TRY(h, hipEventRecord(h->fork_ev, s), "fork event");
-        RBE2D_TRY(h, hipStreamWaitEvent(ks, h->fork_ev, 0), "fork wait");
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s), "real-space launch");
-        if (mxs) RBE2D_TRY(h, launch_short(h, *mxs, nullptr, nullptr, s, true), "short-range launch");
-        // with k-space the assembly launch computes the IBC scalars
-        const bool sc_asm = (parts & RBE2D_KSPACE) != 0;
-        RBE2D_TRY(h, launch_prep(h, pos, q, ks, !sc_asm), "prep launch");
-        if (parts & RBE2D_KSPACE) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true), "structure-factor launch");
-        RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, parts & ~(uint32_t)RBE2D_REAL, accumulate, false, false,
-                                   nullptr, ks), "force launch");
-        RBE2D_TRY(h, hipEventRecord(h->join_ev, ks), "join event");
-        RBE2D_TRY(h, hipStreamWaitEvent(s, h->join_ev, 0), "join wait");
-        RBE2D_TRY(h, launch_add_real(h, F, vel, 0.5 * dt, s), "real-space add");
-        return RBE2D_OK;
+                            bool accumulate, const ForceJob &job, hipStream_t s) {
+    const bool kside = (parts & (RBE2D_KSPACE | RBE2D_IBC)) != 0, real = (parts & RBE2D_REAL) != 0;
+    const bool sc_asm = (parts & RBE2D_KSPACE) != 0;
+    const bool two = kside && real && h->n_total > 0 && !on_one_stream(h, kOneStreamForces);
+    if (kside && !job.prepared) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
+    hipStream_t ks = two ? h->side : s;
+    if (two) {
+        rbe2d_status st = stream_wait(h, ks, s, h->fork_ev);
+        if (st) return st;
     }
-    rbe2d_status st = run_common(h, pos, q, parts, false, s);
-    if (st) return st;
-    RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, parts, accumulate, false, (parts & RBE2D_REAL) != 0, nullptr,
-                               s), "force launch");
-    if (mxs) RBE2D_TRY(h, launch_short(h, *mxs, F, nullptr, s), "short-range launch");
-    if (vel) RBE2D_TRY(h, launch_md_kick(h, vel, F, dt, s), "md kick");
+    // real space first: its latency-bound cell list then starts ahead of the
+    // structure factors (also in a captured graph, whose nodes follow this order)
+    if (real) {
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s), "real-space launch");
+        if (job.mx) RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, s, true), "short-range launch");
+    }
+    if (sc_asm) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");
+    ForceExtra x;
+    if (!two) {
+        x.vel = job.vel; x.half_dt = 0.5 * job.dt; x.energy = job.energy; x.err_out = job.err_out;
+    }
+    RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, two ? parts & ~(uint32_t)RBE2D_REAL : parts, accumulate, false,
+                               real && !two, nullptr, ks, x), "force launch");
+    if (two) {
+        rbe2d_status st = stream_wait(h, s, ks, h->join_ev);
+        if (st) return st;
+        RBE2D_TRY(h, launch_add_real(h, F, job.vel, 0.5 * job.dt, s, job.energy, parts), "real-space add");
+        if (job.err_out) launch_copy_err(h, job.err_out, s);
+    }
+    if (h->n_total == 0) {   // (no force pass)
+        if (job.energy) RBE2D_TRY(h, launch_energy(h, job.energy, parts, nullptr, nullptr, s), "energy launch");
+        if (job.err_out) launch_copy_err(h, job.err_out, s);
+    }
     return RBE2D_OK;
 }
 
@@ -712,11 +745,9 @@ rbe2d_status run_forces(rbe2d_ctx *h, const double *pos, const double *q, double
     rbe2d_status st = check_arrays(h, pos, q);
     if (st) return st;
     if (h->n_total > 0 && !F) return fail(h, RBE2D_E_INVAL, "F is NULL");
-    const uint32_t parts = flags & RBE2D_ALL;
-    st = compute_forces(h, pos, q, F, parts, (flags & RBE2D_ACCUMULATE) != 0, nullptr, 0.0, s, nullptr);
-    if (st) return st;
-    if (energy) RBE2D_TRY(h, launch_energy(h, energy, parts, nullptr, nullptr, s), "energy launch");
-    return RBE2D_OK;
+    ForceJob job;
+    job.energy = energy;
+    return compute_forces(h, pos, q, F, flags & RBE2D_ALL, (flags & RBE2D_ACCUMULATE) != 0, job, s);
 }
 
 rbe2d_status md_extra(rbe2d_ctx *h, const rbe2d_md_params *mp, double dt, MdExtra *mx) {
@@ -748,28 +779,22 @@ rbe2d_status md_extra(rbe2d_ctx *h, const rbe2d_md_params *mp, double dt, MdExtr
     return RBE2D_OK;
 }
 
-// one step: velocity Verlet, or BAOAB with short-range forces when mx is
-// set; the k-set (and the thermostat noise) use the device step counter when
-// dev_step is set (graph replays), else stream id `step`
+// one BAOAB step of mx with its short-range forces (without mx: a step of an
+// empty layout, which only draws its k-set); the k-set and the thermostat
+// noise use the device step counter when dev_step is set (graph replays),
+// else stream id `step`
 rbe2d_status md_step(rbe2d_ctx *h, double *pos, double *vel, const double *q, double *F, double dt,
                      double zlo, double zhi_from_top, uint64_t seed, int64_t step, bool dev_step,
                      const MdExtra *mx, hipStream_t s) {
     const uint64_t sbase = (uint64_t)step * (uint64_t)h->n_sys;
-    // (without mx this runs only for an empty layout: plain velocity Verlet
-    // with particles takes vv_run, which applies the wall bounds)
-    (void)zlo;
-    (void)zhi_from_top;
-    if (mx)
-        RBE2D_TRY(h, launch_md_kick_drift_langevin(h, pos, vel, F, dt, *mx, seed, sbase,
-                                                   dev_step ? h->w.step : nullptr, s), "md drift");
-    RBE2D_TRY(h, launch_sample(h, seed, sbase, dev_step ? h->w.step : nullptr, s), "md sample");
-    // short-range forces and the closing half kick are fused into the force
-    // evaluation
-    const bool shortr = mx && mx->short_on();
-    rbe2d_status st = compute_forces(h, pos, q, F, RBE2D_ALL, false, vel, dt, s, shortr ? mx : nullptr);
-    if (st) return st;
-    if (dev_step) RBE2D_TRY(h, launch_step_inc(h, s), "md step counter");
-    return RBE2D_OK;
+    if (mx) zlo = zhi_from_top = mx->margin;
+    RBE2D_TRY(h, launch_prep_md(h, mx ? 3 : 1, pos, vel, F, q, dt, zlo, zhi_from_top, mx, seed, sbase,
+                                dev_step ? h->w.step : nullptr, s), "md drift");
+    ForceJob job;
+    job.vel = vel; job.dt = dt; job.prepared = true;
+    job.mx = mx && mx->short_on() ? mx : nullptr;
+    job.step = dev_step ? h->w.step : nullptr;
+    return compute_forces(h, pos, q, F, RBE2D_ALL, false, job, s);
 }
 
 // Force evaluation and closing kick of one plain velocity-Verlet step at
@@ -778,38 +803,27 @@ rbe2d_status md_step(rbe2d_ctx *h, double *pos, double *vel, const double *q, do
 // wrote).  The k-space chain (structure factors, assembly with the IBC
 // scalars, force scatter) runs on the side stream, real space on s.  After
 // the forces, either the closing half kick (last step of the run) or one
-// pass with the closing and next opening half kicks, the next drift and the
-// next records.  Meanwhile the side stream draws the next step's k-set
-// (device step counter: incremented there first) and builds its table.
-// The next step's fork orders that draw before the next k-space chain; a
-// captured step joins it back explicitly (join_tail).
+// pass with the closing and next opening half kicks, the next drift, the next
+// records and the next k-set (device step counter: advanced by the assembly).
 rbe2d_status vv_unit(rbe2d_ctx *h, double *pos, double *vel, const double *q, double *F, double dt, double zlo,
-                     double zhi_from_top, uint64_t seed, int64_t step, bool dev_step, bool last, bool join_tail,
-                     hipStream_t s) {
+                     double zhi_from_top, uint64_t seed, int64_t step, bool dev_step, bool last, hipStream_t s) {
     hipStream_t ks = h->side;
-    RBE2D_TRY(h, hipEventRecord(h->fork_ev, s), "fork event");
-    RBE2D_TRY(h, hipStreamWaitEvent(ks, h->fork_ev, 0), "fork wait");
+    rbe2d_status st = stream_wait(h, ks, s, h->fork_ev);
+    if (st) return st;
     // real space first: its latency-bound cell list then starts ahead of the
     // structure factors (also in a captured graph, whose nodes follow this order)
     RBE2D_TRY(h, launch_real(h, pos, q, false, s), "real-space launch");
-    RBE2D_TRY(h, launch_kcoef_sf(h, ks, true), "structure-factor launch");
+    RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, dev_step ? h->w.step : nullptr), "structure-factor launch");
     RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, RBE2D_KSPACE | RBE2D_IBC, false, false, false, nullptr, ks),
               "force launch");
-    RBE2D_TRY(h, hipEventRecord(h->join_ev, ks), "join event");
-    RBE2D_TRY(h, hipStreamWaitEvent(s, h->join_ev, 0), "join wait");
-    if (!last) {
-        if (dev_step) RBE2D_TRY(h, launch_step_inc(h, ks), "md step counter");
-        RBE2D_TRY(h, launch_sample(h, seed, (uint64_t)(step + 1) * (uint64_t)h->n_sys, dev_step ? h->w.step : nullptr,
-                                   ks), "md sample");
-        launch_ktable(h, ks);
-        RBE2D_TRY(h, launch_prep_md(h, pos, vel, F, q, dt, zlo, zhi_from_top, true, s), "md leapfrog");
-    } else {
+    st = stream_wait(h, s, ks, h->join_ev);
+    if (st) return st;
+    if (!last)
+        RBE2D_TRY(h, launch_prep_md(h, 2, pos, vel, F, q, dt, zlo, zhi_from_top, nullptr, seed,
+                                    (uint64_t)(step + 1) * (uint64_t)h->n_sys, dev_step ? h->w.step : nullptr, s),
+                  "md leapfrog");
+    else
         RBE2D_TRY(h, launch_add_real(h, F, vel, 0.5 * dt, s), "real-space add");
-    }
-    if (join_tail) {
-        RBE2D_TRY(h, hipEventRecord(h->tail_ev, ks), "tail event");
-        RBE2D_TRY(h, hipStreamWaitEvent(s, h->tail_ev, 0), "tail wait");
-    }
     return RBE2D_OK;
 }
 
@@ -820,9 +834,8 @@ rbe2d_status vv_unit(rbe2d_ctx *h, double *pos, double *vel, const double *q, do
 rbe2d_status vv_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, double *F, double dt, double zlo,
                     double zhi_from_top, uint64_t seed, int64_t step0, int32_t n_steps, bool use_graph,
                     hipStream_t s) {
-    RBE2D_TRY(h, launch_prep_md(h, pos, vel, F, q, dt, zlo, zhi_from_top, false, s), "md drift");
-    RBE2D_TRY(h, launch_sample(h, seed, (uint64_t)step0 * (uint64_t)h->n_sys, nullptr, s), "md sample");
-    launch_ktable(h, s);
+    RBE2D_TRY(h, launch_prep_md(h, 1, pos, vel, F, q, dt, zlo, zhi_from_top, nullptr, seed,
+                                (uint64_t)step0 * (uint64_t)h->n_sys, nullptr, s), "md drift");
     int32_t it = 0;
     if (use_graph) {
         auto bits = [](double x) { uint64_t u; std::memcpy(&u, &x, 8); return u; };
@@ -842,7 +855,7 @@ rbe2d_status vv_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
             hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
             rbe2d_status st = RBE2D_OK;
             if (e == hipSuccess) {
-                st = vv_unit(h, pos, vel, q, F, dt, zlo, zhi_from_top, seed, 0, true, false, true, cs);
+                st = vv_unit(h, pos, vel, q, F, dt, zlo, zhi_from_top, seed, 0, true, false, cs);
                 hipGraph_t g = nullptr;
                 const hipError_t e2 = hipStreamEndCapture(cs, &g);
                 if (st == RBE2D_OK && e2 != hipSuccess) st = hipfail(h, e2, "end capture");
@@ -867,7 +880,7 @@ rbe2d_status vv_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
     }
     for (; it < n_steps; it++) {
         rbe2d_status st = vv_unit(h, pos, vel, q, F, dt, zlo, zhi_from_top, seed, step0 + it, false,
-                                  it == n_steps - 1, false, s);
+                                  it == n_steps - 1, s);
         if (st) return st;
     }
     return RBE2D_OK;
@@ -903,6 +916,7 @@ rbe2d_status md_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
         RBE2D_TRY(h, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking), "capture stream");
         const int prof_n = h->prof.n;
         h->prof.n = 0;   // no profiling events inside the graph
+        const bool counted0 = h->cells_counted;   // (a failed capture has counted nothing)
         hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
         rbe2d_status st = RBE2D_OK;
         if (e == hipSuccess) {
@@ -922,6 +936,7 @@ rbe2d_status md_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
         }
         h->prof.n = prof_n;
         (void)hipStreamDestroy(cs);
+        h->cells_counted = counted0;
         if (st) { free_graph(h); return st; }
         h->md_key = key;
     }
@@ -938,7 +953,7 @@ rbe2d_status md_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
 
 constexpr int64_t kStaticMaxN = 32768;     // largest n_max of the static path
 constexpr int kStaticMaxP = 1024;          // largest P of the static path
-constexpr int kStaticFparts = 1024;        // particle blocks' worth of force-pass partials
+constexpr int kStaticSplitBlocks = 1024;   // k-range parts x particle blocks of the force pass
 constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr int kMaxDevices = 64;
 
@@ -972,9 +987,12 @@ struct PutFam {
     int first, count;
 };
 
-__global__ void k_put_desc(PutDesc a, SysDesc *sys, int *off, int *pbase, int *bbase, int *tbase, int *sbase,
-                           int *err) {
-    if (threadIdx.x != 0) return;
+// (the cell counts start at zero in every build: the array may hold another
+// call's values)
+__global__ __launch_bounds__(kBlock) void k_put_desc(PutDesc a, SysDesc *sys, int *off, int *pbase, int *bbase,
+                                                     int *tbase, int *sbase, int *err, int *count, int n_count) {
+    for (int c = blockIdx.x * kBlock + threadIdx.x; c < n_count; c += gridDim.x * kBlock) count[c] = 0;
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
     *sys = a.d;
     int *dst[5] = {off, pbase, bbase, tbase, sbase};
     for (int k = 0; k < 5; k++) {
@@ -988,9 +1006,6 @@ __global__ void k_put_img(ImgTable a, ImgTable *img) {
 }
 __global__ void k_put_fam(PutFam a, Family *fam) {
     if ((int)threadIdx.x < a.count) fam[a.first + threadIdx.x] = a.f[threadIdx.x];
-}
-__global__ void k_copy_err(const int *src, int32_t *dst) {
-    if (threadIdx.x == 0) *dst = *src;
 }
 
 rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t N, const double *pos,
@@ -1039,9 +1054,9 @@ rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t 
         h->n_cap = pp.n_max;
         h->cap_particles = std::max<int64_t>((pp.n_max + kTileMax - 1) / kTileMax * kTileMax, kTileMax);
         h->cap_sorted = std::max<int64_t>((pp.n_max + kWave - 1) / kWave * kWave, kWave);
-        h->total_cells = d.ncx * d.ncy * d.ncz;
+        h->total_cells = h->max_cells = d.ncx * d.ncy * d.ncz;
         h->iso = d.iso != 0;
-        h->fpart_blocks = std::min<int64_t>(64 * (h->cap_particles / kBlock), kStaticFparts);
+        h->split_blocks = kStaticSplitBlocks;
         h->one_stream = true;
         h->side = nullptr;
         // carve the workspaces from the array (256-byte aligned)
@@ -1069,8 +1084,9 @@ rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t 
     // last call's contents; every call rewrites what it reads)
     const SysHost &sh = h->sys[0];
     pd.d = sh.d;
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, pd, h->w.sys, h->w.lay.off, h->w.lay.pbase,
-                       h->w.lay.bbase, h->w.lay.tbase, h->w.lay.sbase, h->w.err);
+    const int ncb = std::min((h->total_cells + kBlock - 1) / kBlock, 256);
+    hipLaunchKernelGGL(k_put_desc, dim3(ncb), dim3(kBlock), 0, s, pd, h->w.sys, h->w.lay.off, h->w.lay.pbase,
+                       h->w.lay.bbase, h->w.lay.tbase, h->w.lay.sbase, h->w.err, h->w.count, h->total_cells);
     hipLaunchKernelGGL(k_put_img, dim3(1), dim3(64), 0, s, sh.img, h->w.img);
     for (int f0 = 0; f0 < (int)sh.fam.size(); f0 += kFamPerPut) {
         PutFam pf;
@@ -1079,16 +1095,13 @@ rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t 
         for (int i = 0; i < pf.count; i++) pf.f[i] = sh.fam[f0 + i];
         hipLaunchKernelGGL(k_put_fam, dim3(1), dim3(64), 0, s, pf, h->w.fam);
     }
-    // the cell counts start at zero in every build (the array may hold
-    // another call's values)
-    RBE2D_TRY(nullptr, launch_fill(h->w.count, (int64_t)h->total_cells * 4, s), "count clear");
     h->cells_counted = false;
     RBE2D_TRY(nullptr, hipGetLastError(), "table upload");
-    const uint32_t parts = flags & RBE2D_ALL;
-    st = compute_forces(h, pos, q, F, parts, (flags & RBE2D_ACCUMULATE) != 0, nullptr, 0.0, s, nullptr);
+    ForceJob job;
+    job.energy = energy;
+    job.err_out = err_word;
+    st = compute_forces(h, pos, q, F, flags & RBE2D_ALL, (flags & RBE2D_ACCUMULATE) != 0, job, s);
     if (st) return fail(nullptr, st, "%s", h->err.c_str());
-    if (energy) RBE2D_TRY(nullptr, launch_energy(h, energy, parts, nullptr, nullptr, s), "energy launch");
-    if (err_word) hipLaunchKernelGGL(k_copy_err, dim3(1), dim3(64), 0, s, h->w.err, err_word);
     RBE2D_TRY(nullptr, hipGetLastError(), "launch");
     return RBE2D_OK;
 }
@@ -1270,9 +1283,12 @@ rbe2d_status rbe2d_energy_backward(rbe2d_handle h, int64_t N, const double *pos,
         st = run_common(h, pos, q, RBE2D_ALL, dEdgamma != nullptr, s);
         if (st) return st;
     }
-    if (dEdr || dEdq)
-        RBE2D_TRY(h, launch_kforce(h, pos, q, dEdr, dEdq, RBE2D_ALL, false, true, true, gE, s), "adjoint launch");
-    if (dEdgamma) RBE2D_TRY(h, launch_energy(h, nullptr, RBE2D_ALL, gE, dEdgamma, s), "dgamma launch");
+    const bool adjoint = (dEdr || dEdq) && N > 0;
+    ForceExtra x;
+    x.dEdgamma = dEdgamma;
+    if (adjoint)
+        RBE2D_TRY(h, launch_kforce(h, pos, q, dEdr, dEdq, RBE2D_ALL, false, true, true, gE, s, x), "adjoint launch");
+    else if (dEdgamma) RBE2D_TRY(h, launch_energy(h, nullptr, RBE2D_ALL, gE, dEdgamma, s), "dgamma launch");
     return RBE2D_OK;
 }
 
@@ -1316,7 +1332,9 @@ rbe2d_status rbe2d_force_variance(rbe2d_handle h, const int64_t *offsets, const 
     if (h->n_total > 0 && !var) return fail(h, RBE2D_E_INVAL, "var is NULL");
     st = run_common(h, pos, q, RBE2D_KSPACE, false, s);
     if (st) return st;
-    RBE2D_TRY(h, launch_kforce(h, pos, q, nullptr, nullptr, RBE2D_KSPACE, false, false, false, nullptr, s, var),
+    ForceExtra x;
+    x.var = var;
+    RBE2D_TRY(h, launch_kforce(h, pos, q, nullptr, nullptr, RBE2D_KSPACE, false, false, false, nullptr, s, x),
               "variance launch");
     return RBE2D_OK;
 }
@@ -1452,7 +1470,7 @@ rbe2d_status rbe2d_autotune(rbe2d_handle h, const int64_t *offsets, const double
     }
     tbest = 1e30f;
     for (int ks = 1; st == RBE2D_OK && ks <= 64 && total > 0; ks <<= 1) {
-        if ((int64_t)ks * h->n_blocks > h->fpart_blocks) break;
+        if ((int64_t)ks * h->n_blocks > h->split_blocks) break;
         h->force_ksplit = ks;
         float t = 0.0f;
         // the real-space output array serves as scratch for the forces

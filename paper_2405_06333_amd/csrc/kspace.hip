@@ -14,11 +14,82 @@
 //    take revolutions directly.
 //  * FP64 path: plain FP64 phases, sine and cosine from devmath.h.
 #include <algorithm>
+#include <type_traits>
 
 #include "devmath.h"
+#include "energy.h"
 #include "rbe2d_internal.h"
+#include "sampler.h"
 
 namespace rbe2d {
+
+// ---------------------------------------------------------------------------
+// k-vector tables (nx, ny, nz as floats / doubles, padded with zeros), of the
+// k-set at hand or of one drawn here
+// ---------------------------------------------------------------------------
+
+struct TableArgs {
+    SampleArgs sample;       // the k-set, and how to draw it when `draw` is set
+    int draw, P_pad;
+    float4 *kn32;
+    double4 *kn64;
+};
+
+__device__ __forceinline__ int3 table_kvec(const TableArgs &a, int r, int l) {
+    int32_t *k = a.sample.kset + 3 * ((int64_t)r * a.sample.P + l);
+    if (!a.draw) return make_int3(k[0], k[1], k[2]);
+    const int3 n = draw_kvec(a.sample, r, l);
+    k[0] = n.x; k[1] = n.y; k[2] = n.z;
+    return n;
+}
+
+// FP32: kBlock entries of the systems' tables
+__device__ __forceinline__ void table32(const TableArgs &a, int blk) {
+    const int kg = blk * kBlock + threadIdx.x;
+    if (kg >= a.sample.n_sys * a.P_pad) return;
+    const int r = kg / a.P_pad, l = kg - r * a.P_pad;
+    int3 n = make_int3(0, 0, 0);
+    if (l < a.sample.P) n = table_kvec(a, r, l);
+    a.kn32[kg] = make_float4((float)n.x, (float)n.y, (float)n.z, 0.0f);
+}
+
+// FP64: the k-vectors of system r sorted by |nz|, (nx, ny, |nz|, +-(1 + index
+// in the k-set) with the sign of nz), by a counting sort in LDS, one block.
+// |nz| beyond the last bucket are left unsorted: the structure-factor pass
+// compares neighbours and only saves less.  (The order within a bucket is
+// that of the LDS atomics; no sum depends on it.)
+constexpr int kZBuckets = 2048;
+__device__ void table64(const TableArgs &a, int r) {
+    __shared__ int count[kZBuckets];
+    __shared__ int sh[kBlock / 64];
+    const int P = a.sample.P;
+    const int32_t *k = a.sample.kset + 3 * (int64_t)r * P;
+    constexpr int kPer = kZBuckets / kBlock;
+#pragma unroll
+    for (int b = 0; b < kPer; b++) count[b * kBlock + threadIdx.x] = 0;
+    __syncthreads();
+    for (int l = threadIdx.x; l < P; l += kBlock)
+        atomicAdd(&count[min(abs(table_kvec(a, r, l).z), kZBuckets - 1)], 1);
+    __syncthreads();
+    int v[kPer], t = 0;
+#pragma unroll
+    for (int b = 0; b < kPer; b++) { v[b] = count[kPer * threadIdx.x + b]; t += v[b]; }
+    int run = block_scan(t, sh);
+#pragma unroll
+    for (int b = 0; b < kPer; b++) { count[kPer * threadIdx.x + b] = run; run += v[b]; }
+    __syncthreads();
+    double4 *o = a.kn64 + (int64_t)r * a.P_pad;
+    for (int l = threadIdx.x; l < a.P_pad; l += kBlock) {
+        if (l < P) {
+            // (a drawn k-vector was written by this thread)
+            const int nx = k[3 * l], ny = k[3 * l + 1], nz = k[3 * l + 2];
+            const int at = atomicAdd(&count[min(abs(nz), kZBuckets - 1)], 1);
+            o[at] = make_double4((double)nx, (double)ny, fabs((double)nz), nz < 0 ? -1.0 - l : 1.0 + l);
+        } else {
+            o[l] = make_double4(0.0, 0.0, 0.0, 0.0);
+        }
+    }
+}
 
 // ---------------------------------------------------------------------------
 // 1. particle preparation
@@ -38,19 +109,64 @@ struct PrepArgs {
     const double *F;
     const double4 *freal;       // MD == 2: the pair kernel's part of the force
     double dt, zlo, zhi_from_top;
-    // MD > 0 with count set: the cell and in-cell slot of each moved
-    // particle for the next cell-list build (the counts start at zero)
+    // with count set: the cell and in-cell slot of each (moved) particle for
+    // the next cell-list build (the counts start at zero)
     int *cell, *slot, *count;
+    // MD == 3: the Langevin update's parameters
+    double c1, c2;
+    uint64_t seed, stream_base;
+    const long long *dev_step;
+    int n_tblocks;              // the first blocks write the k-vector tables (one draw is a long chain)
+    TableArgs tab;
 };
+
+// r += dt/2 v; v = c1 v + c2 xi; r += dt/2 v; wrap / reflect, after the kick
+// v += dt/2 F (Langevin equation, unit masses).  xi: Box-Muller normals from
+// the SplitMix64 stream (seed, 2^63 + step n_sys + system), uniforms 2(3i+c)
+// and 2(3i+c)+1 for particle i of its system.
+__device__ __forceinline__ void langevin_drift(const SysDesc &d, const PrepArgs &a, int r, int local, double (&v)[3],
+                                               double (&x)[3]) {
+    const uint64_t base = a.dev_step ? (uint64_t)(*a.dev_step) * (uint64_t)a.n_sys : a.stream_base;
+    const uint64_t key = stream_key(a.seed, kThermoStream + base + (uint64_t)r);
+    const double h = 0.5 * a.dt;
+    for (int c = 0; c < 3; c++) {
+        x[c] = fma(h, v[c], x[c]);
+        const uint64_t k = 3 * (uint64_t)local + c;
+        const double u1 = uniform01(key, 2 * k), u2 = uniform01(key, 2 * k + 1);
+        const double xi = sqrt(-2.0 * log(1.0 - u1)) * cos(2.0 * kPi * u2);
+        v[c] = fma(a.c1, v[c], a.c2 * xi);
+        x[c] = fma(h, v[c], x[c]);
+    }
+    x[0] -= d.Lx * floor(x[0] / d.Lx);
+    x[1] -= d.Ly * floor(x[1] / d.Ly);
+    const double zlo = a.zlo, zhi = d.H - a.zhi_from_top;
+    const double W = zhi - zlo;
+    const double u = x[2] - zlo;
+    const double m = floor(u / W);
+    const double rem = u - m * W;
+    const bool odd = fmod(fabs(m), 2.0) == 1.0;
+    x[2] = odd ? zhi - rem : zlo + rem;
+    if (odd) v[2] = -v[2];
+    x[2] = fmin(fmax(x[2], zlo), zhi);
+}
 
 // MD: 0 none; 1 opening half kick with F and drift; 2 closing half kick and
 // the next opening half kick, both with F + freal (the same force, the same
-// roundings as two separate kicks), and drift.  Then the k-space particle
-// records of the (new) positions and the block sums of the IBC.
+// roundings as two separate kicks), and drift; 3 the Langevin update up to the
+// force evaluation (BAOAB).  Then the k-space particle records of the (new)
+// positions, their cells and the block sums of the IBC.  The k-vector tables,
+// and with an MD update the draw of the k-set, are blocks of the same launch:
+// a call of a few thousand particles lasts about as long as its launches take
+// to issue (6 to 7 us each).
 template <bool FP32, int MD>
 __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
     __shared__ double sh[4][kBlock / 64];
-    const int b = blockIdx.x;
+    if ((int)blockIdx.x < a.n_tblocks) {
+        if (FP32) table32(a.tab, blockIdx.x);
+        else table64(a.tab, blockIdx.x);
+        return;
+    }
+    const int b = blockIdx.x - a.n_tblocks;
     const int r = find_sys(a.lay.bbase, a.n_sys, b);
     const SysDesc &d = a.sys[r];
     const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
@@ -73,19 +189,20 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
                 if (MD == 2) v[c] = fma(0.5 * a.dt, f, v[c]);
                 rr[c] = a.pos_md[3 * g + c];
             }
-            drift_fold(d, a.dt, a.zlo, a.zhi_from_top, v, rr);
+            if (MD == 3) langevin_drift(d, a, r, iloc, v, rr);
+            else drift_fold(d, a.dt, a.zlo, a.zhi_from_top, v, rr);
             for (int c = 0; c < 3; c++) {
                 a.vel[3 * g + c] = v[c];
                 a.pos_md[3 * g + c] = rr[c];
             }
             x = rr[0]; y = rr[1]; z = rr[2];
-            if (a.count) {
-                const int c = d.cbase + cell_of(x, y, z, d);
-                a.cell[g] = c;
-                a.slot[g] = atomicAdd(&a.count[c], 1);
-            }
         } else {
             x = a.pos[3 * g]; y = a.pos[3 * g + 1]; z = a.pos[3 * g + 2];
+        }
+        if (a.count) {
+            const int c = d.cbase + cell_of(x, y, z, d);
+            a.cell[g] = c;
+            a.slot[g] = atomicAdd(&a.count[c], 1);
         }
         qi = a.q[g];
         if (!(z > 0.0 && z < d.H)) atomicOr(a.err, 1);
@@ -174,23 +291,15 @@ __device__ void ibc_scalars(const ScalArgs &a, int r, int lane) {
 
 __global__ __launch_bounds__(64) void k_scalars(ScalArgs a) { ibc_scalars(a, blockIdx.x, threadIdx.x); }
 
-__global__ void k_ktable32(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32);
-__global__ void k_ktable64(const int32_t *kset, int P, int P_pad, double4 *kn64);
-
 static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
     PrepArgs a{};
     a.pos = pos; a.q = q; a.sys = h->w.sys; a.lay = h->w.lay; a.n_sys = h->n_sys;
     a.p32 = h->w.p32; a.p64 = h->w.p64; a.bpart = h->w.bpart; a.err = h->w.err;
+    a.cell = h->w.cell; a.slot = h->w.slot;
+    a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock : h->n_sys;
+    a.tab.sample = sample_args(h, 0, 0, nullptr);
+    a.tab.P_pad = h->P_pad; a.tab.kn32 = h->w.kn32; a.tab.kn64 = h->w.kn64;
     return a;
-}
-
-void launch_ktable(rbe2d_ctx *h, hipStream_t s) {
-    const int nk = h->n_sys * h->P_pad;
-    if (h->precision == RBE2D_PREC_FP32_PHASE)
-        hipLaunchKernelGGL(k_ktable32, dim3((nk + 63) / 64), dim3(64), 0, s, h->w.kset, h->n_sys, h->P, h->P_pad,
-                           h->w.kn32);
-    else
-        hipLaunchKernelGGL(k_ktable64, dim3(h->n_sys), dim3(kBlock), 0, s, h->w.kset, h->P, h->P_pad, h->w.kn64);
 }
 
 static ScalArgs scal_args(rbe2d_ctx *h) {
@@ -205,93 +314,52 @@ static void launch_scalars(rbe2d_ctx *h, hipStream_t s) {
 
 template <int MD>
 static void launch_prep_kernel(rbe2d_ctx *h, const PrepArgs &a, hipStream_t s) {
-    if (h->n_blocks <= 0) return;
-    if (h->precision == RBE2D_PREC_FP32_PHASE)
-        hipLaunchKernelGGL((k_prep<true, MD>), dim3(h->n_blocks), dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_prep<false, MD>), dim3(h->n_blocks), dim3(kBlock), 0, s, a);
+    const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
+    const dim3 g(a.n_tblocks + h->n_blocks);
+    if (fp32) hipLaunchKernelGGL((k_prep<true, MD>), g, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_prep<false, MD>), g, dim3(kBlock), 0, s, a);
 }
 
-hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s, bool scalars) {
-    // the k-vector table needs only the k-set: first, off the particles' path
-    launch_ktable(h, s);
+hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s, bool scalars, bool count) {
     prof_begin(h, 0, s);
-    launch_prep_kernel<0>(h, prep_args(h, pos, q), s);
+    PrepArgs a = prep_args(h, pos, q);
+    if (count) a.count = h->w.count;
+    launch_prep_kernel<0>(h, a, s);
+    if (count) {
+        h->cells_counted = h->n_total > 0;
+        h->records_moved = false;
+    }
     if (scalars) launch_scalars(h, s);
     prof_end(h, 0, s);
     return hipGetLastError();
 }
 
-hipError_t launch_prep_md(rbe2d_ctx *h, double *pos, double *vel, const double *F, const double *q, double dt,
-                          double zlo, double zhi_from_top, bool with_real, hipStream_t s) {
+hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const double *F, const double *q, double dt,
+                          double zlo, double zhi_from_top, const MdExtra *mx, uint64_t seed, uint64_t stream_base,
+                          const long long *dev_step, hipStream_t s) {
     PrepArgs a = prep_args(h, pos, q);
     a.pos_md = pos; a.vel = vel; a.F = F; a.freal = h->w.freal;
     a.dt = dt; a.zlo = zlo; a.zhi_from_top = zhi_from_top;
     // a force evaluation with real space follows: count the particles per
     // cell here, where their new positions are at hand
-    a.cell = h->w.cell; a.slot = h->w.slot; a.count = h->w.count;
+    a.count = h->w.count;
+    a.tab.sample = sample_args(h, seed, stream_base, dev_step);
+    a.tab.draw = 1;
+    if (md == 3) {
+        a.c1 = mx->c1; a.c2 = mx->c2; a.seed = seed; a.stream_base = stream_base; a.dev_step = dev_step;
+    }
     prof_begin(h, 7, s);
-    if (with_real) launch_prep_kernel<2>(h, a, s);
-    else launch_prep_kernel<1>(h, a, s);
+    if (md == 1) launch_prep_kernel<1>(h, a, s);
+    else if (md == 2) launch_prep_kernel<2>(h, a, s);
+    else launch_prep_kernel<3>(h, a, s);
     prof_end(h, 7, s);
     h->cells_counted = h->n_total > 0;
+    h->records_moved = md != 3;
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// 2. k-vector tables (nx, ny, nz as floats / doubles, padded with zeros)
-// ---------------------------------------------------------------------------
-
-__global__ void k_ktable32(const int32_t *kset, int n_sys, int P, int P_pad, float4 *kn32) {
-    const int kg = blockIdx.x * blockDim.x + threadIdx.x;
-    if (kg >= n_sys * P_pad) return;
-    const int r = kg / P_pad, l = kg - r * P_pad;
-    int nx = 0, ny = 0, nz = 0;
-    if (l < P) {
-        const int32_t *n = kset + 3 * ((int64_t)r * P + l);
-        nx = n[0]; ny = n[1]; nz = n[2];
-    }
-    kn32[kg] = make_float4((float)nx, (float)ny, (float)nz, 0.0f);
-}
-
-// FP64: the k-vectors sorted by |nz|, (nx, ny, |nz|, +-(1 + index in the
-// k-set) with the sign of nz), by a counting sort in LDS, one block per system.
-// |nz| beyond the last bucket are left unsorted: the structure-factor pass
-// compares neighbours and only saves less.  (The order within a bucket is
-// that of the LDS atomics; no sum depends on it.)
-constexpr int kZBuckets = 2048;
-__global__ __launch_bounds__(kBlock) void k_ktable64(const int32_t *kset, int P, int P_pad, double4 *kn64) {
-    __shared__ int count[kZBuckets];
-    __shared__ int sh[kBlock / 64];
-    const int r = blockIdx.x;
-    const int32_t *n = kset + 3 * (int64_t)r * P;
-    constexpr int kPer = kZBuckets / kBlock;
-#pragma unroll
-    for (int b = 0; b < kPer; b++) count[b * kBlock + threadIdx.x] = 0;
-    __syncthreads();
-    for (int l = threadIdx.x; l < P; l += kBlock) atomicAdd(&count[min(abs(n[3 * l + 2]), kZBuckets - 1)], 1);
-    __syncthreads();
-    int v[kPer], t = 0;
-#pragma unroll
-    for (int b = 0; b < kPer; b++) { v[b] = count[kPer * threadIdx.x + b]; t += v[b]; }
-    int run = block_scan(t, sh);
-#pragma unroll
-    for (int b = 0; b < kPer; b++) { count[kPer * threadIdx.x + b] = run; run += v[b]; }
-    __syncthreads();
-    for (int l = threadIdx.x; l < P_pad; l += kBlock) {
-        const int64_t o = (int64_t)r * P_pad;
-        if (l < P) {
-            const int nx = n[3 * l], ny = n[3 * l + 1], nz = n[3 * l + 2];
-            const int k = atomicAdd(&count[min(abs(nz), kZBuckets - 1)], 1);
-            kn64[o + k] = make_double4((double)nx, (double)ny, fabs((double)nz), nz < 0 ? -1.0 - l : 1.0 + l);
-        } else {
-            kn64[o + l] = make_double4(0.0, 0.0, 0.0, 0.0);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// 3. structure-factor pass: per (particle tile, k-chunk) partial sums of
+// 2. structure-factor pass: per (particle tile, k-chunk) partial sums of
 //    rho(k) = sum q e^{2 pi i phi} and rhohat(k) = sum q e^{2 pi i phihat}
 //    with phi = phi_xy + phi_z, phihat = phi_xy - phi_z.
 //    Lanes own particles, the k-chunk is wave-uniform (scalar loads).
@@ -439,7 +507,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 }
 
 // ---------------------------------------------------------------------------
-// 4. reduce over tiles (FP64, fixed order) and recalibrate (Sec. 3.4):
+// 3. reduce over tiles (FP64, fixed order) and recalibrate (Sec. 3.4):
 //    rho^M = (1 + Y_even) rho + Y_odd rhohat,
 //    A = rho^M + (1 + conj Y_even) rho,  B = conj(Y_odd) rho,
 //    c = 2 pi S pref / (V P |k|^2),  e = c Re(rho conj(rho^M)).
@@ -458,6 +526,7 @@ struct AssembleArgs {
     double *kf64;              // FP64: the force pass's records
     int n_sys, with_scalars;   // with_scalars: n_sys more blocks compute the IBC scalars
     ScalArgs sc;
+    long long *step;           // MD step counter to advance, or null
 };
 
 __device__ __forceinline__ double dmono(int e_self, double g_self, int e_other, double g_other) {
@@ -480,7 +549,9 @@ __device__ __forceinline__ double lane_value(double v, int src) {
 template <bool DG>
 __global__ __launch_bounds__(64) void k_assemble(AssembleArgs a) {
     if ((int)blockIdx.x >= a.n_sys * a.P) {
-        ibc_scalars(a.sc, blockIdx.x - a.n_sys * a.P, threadIdx.x);
+        const int r = blockIdx.x - a.n_sys * a.P;
+        ibc_scalars(a.sc, r, threadIdx.x);
+        if (a.step && r == 0 && threadIdx.x == 0) *a.step += 1;
         return;
     }
     const int r = blockIdx.x / a.P, l = blockIdx.x - r * a.P;
@@ -597,7 +668,7 @@ int choose_tile(int64_t N, int n_kchunks) {
     return per;
 }
 
-hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool want_dg) {
+hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool want_dg, long long *step) {
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
     prof_begin(h, 1, s);
     if (h->n_tiles > 0) {
@@ -618,6 +689,7 @@ hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool 
     a.tbase = h->w.lay.tbase; a.kset = h->w.kset; a.sys = h->w.sys; a.img = h->w.img;
     a.krec = h->w.krec; a.kf32 = h->w.kf32; a.kf64 = fp32 ? nullptr : h->w.kf64;
     a.n_sys = h->n_sys; a.with_scalars = with_scalars; a.sc = scal_args(h);
+    a.step = step;
     prof_begin(h, 2, s);
     const dim3 ga(h->n_sys * h->P + (with_scalars ? h->n_sys : 0));
     if (want_dg) hipLaunchKernelGGL(k_assemble<true>, ga, dim3(64), 0, s, a);
@@ -627,7 +699,7 @@ hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool 
 }
 
 // ---------------------------------------------------------------------------
-// 5. force scatter: one thread per particle, all k (or a k-range) uniform:
+// 4. force scatter: one thread per particle, all k (or a k-range) uniform:
 //    F_i = -q_i sum_l [k_l Im(e^{-i phi} cA_l) + khat_l Im(e^{-i phihat} cB_l)]
 //    pot_i = sum_l [Re(e^{-i phi} cA_l) + Re(e^{-i phihat} cB_l)]   (dE_k/dq_i)
 // ---------------------------------------------------------------------------
@@ -640,17 +712,25 @@ struct ForceArgs {
     const double *kf64;
     Layout lay;
     const SysDesc *sys;
-    int n_sys, P, P_pad, k_per_split, n_threads;   // n_threads = particle blocks * kBlock
+    int n_sys, P, P_pad;
+    int split, k_per_split;  // the k-range in `split` parts of k_per_split
     const double *pos;       // for the IBC potential (z_i)
     const double *q;
     const double *scal;
     const double4 *freal;    // added when add_real
-    double *fpart;           // [split][n_threads][4] when splitting
     double *F;               // final output (caller order, N x 3)
     double *dEdq;            // final dE/dq when want_pot
     double *var;             // force-variance estimate per particle (variance mode)
     const double *gE;        // scale of the backward outputs (device scalar) or null
-    int accumulate, add_real, want_pot, want_var, do_kspace, do_ibc, split;
+    int accumulate, add_real, want_pot, want_var, do_kspace, do_ibc;
+    double *vel;             // closing half kick of an MD step, or null
+    double half_dt;
+    // SPLIT: blocks from n_groups on form the systems' energies; *err goes to
+    // err_out when set
+    int n_groups;
+    EnergyArgs en;
+    const int *err;
+    int32_t *err_out;
 };
 
 __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64_t g, double fx,
@@ -693,31 +773,82 @@ __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64
         if (a.dEdq) a.dEdq[g] = gs * ph;
         return;
     }
-    if (a.accumulate) {
-        a.F[3 * g] += Fx; a.F[3 * g + 1] += Fy; a.F[3 * g + 2] += Fz;
+    const double f[3] = {Fx, Fy, Fz};
+    for (int c = 0; c < 3; c++) {
+        const double v = a.accumulate ? a.F[3 * g + c] + f[c] : f[c];
+        a.F[3 * g + c] = v;
+        if (a.vel) a.vel[3 * g + c] = fma(a.half_dt, v, a.vel[3 * g + c]);
+    }
+}
+
+// The per-k records of a force pass are the same for a whole wave: read as
+// constant memory they come by scalar loads also where the compiler cannot
+// tell that the launch's other stores (the split pass's LDS, the energies)
+// leave them alone; as vector loads they took 40 more registers.
+typedef float vec4f __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(4))) vec4f ConstFloat4;
+typedef __attribute__((address_space(4))) double ConstDouble;
+__device__ __forceinline__ float4 record(const float4 *p) {
+    const vec4f v = *(const ConstFloat4 *)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Blocks of the force pass.  SPLIT (too few particles to fill the chip): the
+// waves of a block share 64 particles and take the parts of the k-range in
+// turn, and their sums meet in LDS: 32 KB at most, where sums kept in memory
+// for a second launch cost that launch (6 us of a call of 60 to 100 us).
+constexpr int kMaxForceWaves = 16;
+template <bool SPLIT, typename Sum>
+__device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
+    extern __shared__ __align__(16) double fsh[];
+    if constexpr (SPLIT) {
+        if ((int)blockIdx.x >= a.n_groups) {
+            energy_block(a.en, blockIdx.x - a.n_groups, fsh);
+            return;
+        }
+        const int lane = threadIdx.x & (kWave - 1);
+        const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (the k-records come by scalar loads)
+        const int b = blockIdx.x / (kBlock / kWave);
+        const int r = find_sys(a.lay.bbase, a.n_sys, b);
+        const int first = (b - a.lay.bbase[r]) * kBlock + (blockIdx.x % (kBlock / kWave)) * kWave;
+        const int Nr = a.lay.off[r + 1] - a.lay.off[r];
+        if (first >= Nr) return;
+        const int64_t ii = (int64_t)a.lay.pbase[r] + first + lane;   // (the records are padded)
+        double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (a.do_kspace)
+            for (int k = wid; k < a.split; k += blockDim.x / kWave)
+                sum(r, ii, k * a.k_per_split, min(a.P, (k + 1) * a.k_per_split), f);
+        // (stores only from here on: the loads above stay scalar)
+        if (a.err_out && blockIdx.x == 0 && threadIdx.x == 0) *a.err_out = *a.err;
+        double4 *part = reinterpret_cast<double4 *>(fsh);
+        part[threadIdx.x] = f;
+        __syncthreads();
+        if (wid != 0 || first + lane >= Nr) return;
+        for (int w = 1; w < (int)blockDim.x / kWave; w++) {
+            const double4 v = part[w * kWave + lane];
+            f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
+        }
+        finish_particle(a, r, (int64_t)a.lay.off[r] + first + lane, f.x, f.y, f.z, f.w);
     } else {
-        a.F[3 * g] = Fx; a.F[3 * g + 1] = Fy; a.F[3 * g + 2] = Fz;
+        const int b = blockIdx.x;
+        const int r = find_sys(a.lay.bbase, a.n_sys, b);
+        const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
+        if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
+        double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (a.do_kspace) sum(r, (int64_t)a.lay.pbase[r] + iloc, 0, a.P, f);
+        finish_particle(a, r, (int64_t)a.lay.off[r] + iloc, f.x, f.y, f.z, f.w);
     }
 }
 
 // MODE 0: forces; 1: forces and potentials (adjoint); 2: forces and the sum
 // of the squared per-k force terms (variance estimate)
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_force32(ForceArgs a) {
-    const int b = blockIdx.x;
-    const int r = find_sys(a.lay.bbase, a.n_sys, b);
-    const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
-    if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
-    const int64_t ii = (int64_t)a.lay.pbase[r] + iloc;
-    const int64_t g = (int64_t)a.lay.off[r] + iloc;
-    const float4 pa = a.p32[2 * ii];
-    const float4 pb = a.p32[2 * ii + 1];
-    const float4 *kn = a.kn32 + (int64_t)r * a.P_pad;
-    const float4 *kf = a.kf32 + 3 * (int64_t)r * a.P;
-    const int l0 = blockIdx.y * a.k_per_split;
-    const int l1 = min(a.P, l0 + a.k_per_split);
-    double Fx = 0, Fy = 0, Fz = 0, Pt = 0;
-    if (a.do_kspace) {
+template <int MODE, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kMaxForceWaves * kWave : kBlock) void k_force32(ForceArgs a) {
+    force_block<SPLIT>(a, [&](int r, int64_t ii, int l0, int l1, double4 &F) {
+        const float4 pa = a.p32[2 * ii];
+        const float4 pb = a.p32[2 * ii + 1];
+        const float4 *kn = a.kn32 + (int64_t)r * a.P_pad;
+        const float4 *kf = a.kf32 + 3 * (int64_t)r * a.P;
         // per k: n (kn), k and |k_xy|^2 (kv), and the amplitudes (ab for the
         // potentials, else their polar form)
         constexpr int kExtra = MODE == 1 ? 1 : 2;
@@ -758,23 +889,17 @@ __global__ __launch_bounds__(kBlock) void k_force32(ForceArgs a) {
                 float4 n[4], kv[4], ex[4];
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
-                    n[j] = kn[l + j];
-                    kv[j] = kf[3 * (l + j)];
-                    ex[j] = kf[3 * (l + j) + kExtra];
+                    n[j] = record(kn + l + j);
+                    kv[j] = record(kf + 3 * (l + j));
+                    ex[j] = record(kf + 3 * (l + j) + kExtra);
                 }
 #pragma unroll
                 for (int j = 0; j < 4; j++) one(n[j], kv[j], ex[j]);
             }
-            for (; l < c1; l++) one(kn[l], kf[3 * l], kf[3 * l + kExtra]);
-            Fx += fx; Fy += fy; Fz += fz; Pt += pt;
+            for (; l < c1; l++) one(record(kn + l), record(kf + 3 * l), record(kf + 3 * l + kExtra));
+            F.x += fx; F.y += fy; F.z += fz; F.w += pt;
         }
-    }
-    if (a.split) {
-        double *o = a.fpart + ((int64_t)blockIdx.y * a.n_threads + (int64_t)b * kBlock + threadIdx.x) * 4;
-        o[0] = Fx; o[1] = Fy; o[2] = Fz; o[3] = Pt;
-    } else {
-        finish_particle(a, r, g, Fx, Fy, Fz, Pt);
-    }
+    });
 }
 
 // FP64.  The wave vectors enter as integers, n = (nx, ny, nz), and the sums are
@@ -783,30 +908,23 @@ __global__ __launch_bounds__(kBlock) void k_force32(ForceArgs a) {
 // per-k records took 112 bytes from two arrays.  Bound by VALU issue, 40
 // instructions per (particle, k), two sines; 1e6 ions, P = 500: 0.61 ms
 // instead of 0.72 (46 instructions).
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_force64(ForceArgs a) {
+template <int MODE, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kMaxForceWaves * kWave : kBlock) void k_force64(ForceArgs a) {
+    using Record = std::conditional_t<SPLIT, ConstDouble, double>;
     __shared__ double2 tab[MODE == 1 ? kParts : 1];
     if (MODE == 1) {
         if (threadIdx.x < kParts)
             tab[threadIdx.x] = make_double2(kPartTable[threadIdx.x][0], kPartTable[threadIdx.x][1]);
         __syncthreads();
     }
-    const int b = blockIdx.x;
-    const int r = find_sys(a.lay.bbase, a.n_sys, b);
-    const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
-    if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
-    const int64_t ii = (int64_t)a.lay.pbase[r] + iloc;
-    const int64_t g = (int64_t)a.lay.off[r] + iloc;
-    const double4 p = a.p64[ii];
-    const double *kf = a.kf64 + (int64_t)r * a.P * kKF64;
-    const int l0 = blockIdx.y * a.k_per_split;
-    const int l1 = min(a.P, l0 + a.k_per_split);
-    const SysDesc &d = a.sys[r];
-    const double wx = 2.0 * kPi * d.inv_Lx, wy = 2.0 * kPi * d.inv_Ly, wz = 2.0 * kPi * d.inv_Lz;
-    double fx = 0, fy = 0, fz = 0, pt = 0;
-    if (a.do_kspace) {
+    force_block<SPLIT>(a, [&](int r, int64_t ii, int l0, int l1, double4 &F) {
+        const double4 p = a.p64[ii];
+        const double *kf = a.kf64 + (int64_t)r * a.P * kKF64;
+        const SysDesc &d = a.sys[r];
+        const double wx = 2.0 * kPi * d.inv_Lx, wy = 2.0 * kPi * d.inv_Ly, wz = 2.0 * kPi * d.inv_Lz;
+        double fx = 0, fy = 0, fz = 0, pt = 0;
         for (int l = l0; l < l1; l++) {
-            const double *f = kf + (int64_t)l * kKF64;
+            const Record *f = (const Record *)(kf + (int64_t)l * kKF64);
             const double nx = f[0], ny = f[1], nz = f[2];
             const double pxy = fma(ny, p.y, nx * p.x);
             double X, Y;   // Im(e^{-i ph} cA), Im(e^{-i phh} cB)
@@ -833,28 +951,8 @@ __global__ __launch_bounds__(kBlock) void k_force64(ForceArgs a) {
                 pt = fma(tx, tx, fma(ty, ty, fma(tz, tz, pt)));
             }
         }
-    }
-    fx *= wx; fy *= wy; fz *= wz;
-    if (a.split) {
-        double *o = a.fpart + ((int64_t)blockIdx.y * a.n_threads + (int64_t)b * kBlock + threadIdx.x) * 4;
-        o[0] = fx; o[1] = fy; o[2] = fz; o[3] = pt;
-    } else {
-        finish_particle(a, r, g, fx, fy, fz, pt);
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_force_combine(ForceArgs a, int nsplit) {
-    const int b = blockIdx.x;
-    const int r = find_sys(a.lay.bbase, a.n_sys, b);
-    const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
-    if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
-    const int64_t g = (int64_t)a.lay.off[r] + iloc;
-    double fx = 0, fy = 0, fz = 0, pt = 0;
-    for (int sidx = 0; sidx < nsplit; sidx++) {
-        const double *o = a.fpart + ((int64_t)sidx * a.n_threads + (int64_t)b * kBlock + threadIdx.x) * 4;
-        fx += o[0]; fy += o[1]; fz += o[2]; pt += o[3];
-    }
-    finish_particle(a, r, g, fx, fy, fz, pt);
+        F.x = fma(wx, fx, F.x); F.y = fma(wy, fy, F.y); F.z = fma(wz, fz, F.z); F.w += pt;
+    });
 }
 
 int choose_ksplit(int64_t nb, int P) {
@@ -866,39 +964,47 @@ int choose_ksplit(int64_t nb, int P) {
 
 hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, double *F, double *dEdq,
                          uint32_t flags, bool accumulate, bool want_pot, bool add_real, const double *gE,
-                         hipStream_t s, double *var) {
+                         hipStream_t s, const ForceExtra &x) {
     if (h->n_total == 0) return hipSuccess;
-    ForceArgs a;
+    ForceArgs a{};
     a.p32 = h->w.p32; a.p64 = h->w.p64; a.kn32 = h->w.kn32;
     a.kf32 = h->w.kf32; a.kf64 = h->w.kf64; a.lay = h->w.lay; a.sys = h->w.sys;
-    a.n_sys = h->n_sys; a.P = h->P; a.P_pad = h->P_pad; a.n_threads = h->n_blocks * kBlock;
+    a.n_sys = h->n_sys; a.P = h->P; a.P_pad = h->P_pad;
     a.pos = pos; a.q = q; a.scal = h->w.scal; a.freal = h->w.freal;
-    a.fpart = h->w.fpart; a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = var;
-    a.accumulate = accumulate; a.add_real = add_real; a.want_pot = want_pot; a.want_var = var != nullptr;
+    a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = x.var; a.vel = x.vel; a.half_dt = x.half_dt;
+    a.accumulate = accumulate; a.add_real = add_real; a.want_pot = want_pot; a.want_var = x.var != nullptr;
     a.do_kspace = (flags & RBE2D_KSPACE) != 0; a.do_ibc = (flags & RBE2D_IBC) != 0;
-    int split = 1;
+    a.split = 1;
     if (a.do_kspace) {
-        split = h->force_ksplit ? h->force_ksplit
-                                : (h->tuned_now && h->tune.ksplit ? h->tune.ksplit : choose_ksplit(h->n_blocks, h->P));
-        // the partial buffer holds fpart_blocks blocks' worth
-        while (split > 1 && (int64_t)split * h->n_blocks > h->fpart_blocks) split >>= 1;
+        a.split = h->force_ksplit ? h->force_ksplit
+                                  : (h->tuned_now && h->tune.ksplit ? h->tune.ksplit : choose_ksplit(h->n_blocks, h->P));
+        while (a.split > 1 && (int64_t)a.split * h->n_blocks > h->split_blocks) a.split >>= 1;
     }
-    a.k_per_split = (h->P + split - 1) / split;
-    a.split = split > 1;
+    a.k_per_split = (h->P + a.split - 1) / a.split;
+    const bool split = a.split > 1, energies = x.energy || x.dEdgamma;
+    if (energies) a.en = energy_args(h, x.energy, flags, gE, x.dEdgamma);
+    a.err = h->w.err; a.err_out = x.err_out;
+    a.n_groups = h->n_blocks * (kBlock / kWave);
+    const int waves = std::min(a.split, kMaxForceWaves);
+    const dim3 g(split ? a.n_groups + (energies ? h->n_sys : 0) : h->n_blocks), b(split ? waves * kWave : kBlock);
+    const int lds = split ? waves * kWave * (int)sizeof(double4) : 0;
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
-    dim3 g(h->n_blocks, split);
+    const int mode = x.var ? 2 : want_pot ? 1 : 0;
     prof_begin(h, 5, s);
-    if (fp32) {
-        if (var) hipLaunchKernelGGL(k_force32<2>, g, dim3(kBlock), 0, s, a);
-        else if (want_pot) hipLaunchKernelGGL(k_force32<1>, g, dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL(k_force32<0>, g, dim3(kBlock), 0, s, a);
-    } else {
-        if (var) hipLaunchKernelGGL(k_force64<2>, g, dim3(kBlock), 0, s, a);
-        else if (want_pot) hipLaunchKernelGGL(k_force64<1>, g, dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL(k_force64<0>, g, dim3(kBlock), 0, s, a);
+#define RBE2D_FORCE(M, S)                                                              \
+    if (mode == M && split == S) {                                                     \
+        if (fp32) hipLaunchKernelGGL((k_force32<M, S>), g, b, lds, s, a);              \
+        else hipLaunchKernelGGL((k_force64<M, S>), g, b, lds, s, a);                   \
     }
-    if (a.split) hipLaunchKernelGGL(k_force_combine, dim3(h->n_blocks), dim3(kBlock), 0, s, a, split);
+    RBE2D_FORCE(0, false) RBE2D_FORCE(1, false) RBE2D_FORCE(2, false)
+    RBE2D_FORCE(0, true) RBE2D_FORCE(1, true) RBE2D_FORCE(2, true)
+#undef RBE2D_FORCE
     prof_end(h, 5, s);
+    if (!split) {
+        // a launch of its own: the energies of an unsplit pass are a small part of the call
+        if (energies) (void)launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
+        if (x.err_out) launch_copy_err(h, x.err_out, s);
+    }
     return hipGetLastError();
 }
 

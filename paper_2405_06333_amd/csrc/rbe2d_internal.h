@@ -137,7 +137,6 @@ struct Workspace {
     float4 *kf32 = nullptr;     // per k: (kx, ky, kz, kx^2 + ky^2), (cAr, cAi, cBr, cBi),
                                 // (|cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi)
     double *kf64 = nullptr;     // per k: kKF64 doubles (FP64)
-    double *fpart = nullptr;    // force-pass partials [ksplit][blocks * kBlock][4]
     // real space
     int *cell = nullptr, *slot = nullptr, *count = nullptr, *start = nullptr;
     int2 *tmp = nullptr;        // unordered cell lists: (caller index, global cell)
@@ -193,15 +192,17 @@ struct rbe2d_ctx {
     int total_cells = 0;
     bool iso = false;                // every system has the isotropic fixed-point frame
     int64_t split_cap = 0;           // targets per split of the partial real-space outputs
-    int64_t fpart_blocks = 0;        // particle blocks' worth of force-pass partials (k-range splits)
+    int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most
     bool one_stream = false;         // run the k-space chain on the caller's stream too (no side stream)
-    bool cells_counted = false;      // the last MD pass counted the particles per cell (next build skips it)
+    bool cells_counted = false;      // the preparation counted the particles per cell (next build skips it)
+    bool records_moved = false;      // ... in an MD pass, whose particle records the build reads
     bool kset_valid = false;
     // current layout (host mirror); a layout is uploaded when it changes
     std::vector<int> lay_host;       // 5 x (n_sys + 1): off, pbase, bbase, tbase, sbase
     bool lay_valid = false;
     int per = 0;                     // particles per thread of the structure-factor tiles
     int64_t n_total = 0;
+    int max_n = 0, max_cells = 0;    // of one system
     int n_blocks = 0, n_tiles = 0, n_swaves = 0;
     int *lay_stage = nullptr;        // pinned staging of layout uploads
     hipEvent_t lay_ev = nullptr;
@@ -213,7 +214,7 @@ struct rbe2d_ctx {
     // the k-space chain runs on a second stream beside the real-space chain
     // (default priority), forked from and joined back to the caller's stream
     hipStream_t side = nullptr;
-    hipEvent_t fork_ev = nullptr, join_ev = nullptr, tail_ev = nullptr;
+    hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     bool kev_pending = false;
     // launch parameters: tuned for one particle layout by rbe2d_autotune, else
     // heuristic; force_* override both while the tuner times candidates
@@ -243,45 +244,56 @@ struct rbe2d_ctx {
 namespace rbe2d {
 
 // kernel launchers (return hipSuccess or the launch error); all systems at once
-// k-vector table, particle records and IBC block sums; with scalars, also
-// the IBC scalars (else the assembly launch computes them)
-hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s, bool scalars = true);
+// k-vector tables, particle records and IBC block sums; with scalars, also
+// the IBC scalars (else the assembly launch computes them); with count, also
+// the cell counts of the next cell-list build
+hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s, bool scalars = true,
+                       bool count = false);
 // structure factors and per-k assembly; with_scalars: the assembly launch
-// also computes the IBC scalars (otherwise the prep launch does)
+// also computes the IBC scalars (otherwise the prep launch does) and advances
+// the MD step counter `step` if set
 // want_dg: also the per-k gamma derivatives of the energy (for dE/dgamma)
-hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars = false, bool want_dg = false);
-// k-vector tables of the current k-set (kn32, kn64)
-void launch_ktable(rbe2d_ctx *h, hipStream_t s);
+hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars = false, bool want_dg = false,
+                           long long *step = nullptr);
+// What a force pass may do besides forces: per-particle variances instead,
+// the closing half kick of an MD step, and where all parts precede it on its
+// stream, the energies (energy), the gamma derivatives (dEdgamma) and a copy
+// of the error word
+struct ForceExtra {
+    double *var = nullptr, *vel = nullptr;
+    double half_dt = 0.0;
+    double *energy = nullptr, *dEdgamma = nullptr;
+    int32_t *err_out = nullptr;
+};
 hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, double *F, double *dEdq,
                          uint32_t flags, bool accumulate, bool want_pot, bool add_real, const double *gE,
-                         hipStream_t s, double *var = nullptr);
+                         hipStream_t s, const ForceExtra &x = ForceExtra());
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s);
 hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);
 hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);
 hipError_t launch_tile_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);   // FP64
-hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s);
+// F += F_real (and v += half_dt F); also the energies when energy is set
+hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s,
+                           double *energy = nullptr, uint32_t energy_flags = 0);
+void launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s);
 // short-range forces added to F, or with into_real to the pair kernel's
 // per-particle output (then folded into F with the real-space forces)
 hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s,
                         bool into_real = false);
-hipError_t launch_md_kick_drift_langevin(rbe2d_ctx *h, double *pos, double *vel, const double *F, double dt,
-                                         const MdExtra &mx, uint64_t seed, uint64_t stream_base,
-                                         const long long *dev_step, hipStream_t s);
 hipError_t launch_energy(rbe2d_ctx *h, double *energy, uint32_t flags, const double *gE, double *dEdgamma,
                          hipStream_t s);
 hipError_t launch_sample(rbe2d_ctx *h, uint64_t seed, uint64_t stream_id, const long long *dev_step,
                          hipStream_t s);
-hipError_t launch_md_kick(rbe2d_ctx *h, double *vel, const double *F, double dt, hipStream_t s);
-// MD update fused with the k-space particle preparation (the k-vector table
-// follows each k-draw and the IBC scalars come with the assembly, so the
-// side stream starts with the structure factors): the opening half kick and drift
-// with F (with_real false), or, between two velocity-Verlet steps, the
-// closing and next opening half kicks with F plus the real-space part and
-// the drift (with_real true)
-hipError_t launch_prep_md(rbe2d_ctx *h, double *pos, double *vel, const double *F, const double *q, double dt,
-                          double zlo, double zhi_from_top, bool with_real, hipStream_t s);
+// MD update fused with the k-space particle preparation, the cell counts, the
+// k-draw of its step and the k-vector tables (the IBC scalars come with the
+// assembly).  md 1: the opening half kick and drift with F; 2, between two
+// velocity-Verlet steps: the closing and next opening half kicks with F plus
+// the real-space part, and the drift; 3: the Langevin update of mx up to the
+// force evaluation (zlo = zhi_from_top = its wall margin)
+hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const double *F, const double *q, double dt,
+                          double zlo, double zhi_from_top, const MdExtra *mx, uint64_t seed, uint64_t stream_base,
+                          const long long *dev_step, hipStream_t s);
 hipError_t launch_set_step(rbe2d_ctx *h, long long value, hipStream_t s);
-hipError_t launch_step_inc(rbe2d_ctx *h, hipStream_t s);
 hipError_t launch_fill(void *p, int64_t nbytes_multiple_of_4, hipStream_t s);
 
 int choose_tile(int64_t N_total, int n_kchunks);

@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "devmath.h"
+#include "energy.h"
 #include "erfcx_fit.h"
 #include "rbe2d_internal.h"
 
@@ -170,24 +171,15 @@ __global__ __launch_bounds__(kBlock) void k_cell_scatter(CellArgs a) {
     a.tmp[a.start[c] + a.slot[g]] = make_int2(g, c);
 }
 
-// position within the cell = number of members with a smaller caller index;
-// sorted positions are padded per system to whole waves.  One thread per
-// padded sorted position, so a wave belongs to one system (its constants
-// are scalar loads); the thread takes slot j of the unordered cell lists
-// (tmp), gathers the particle it holds and writes its record within the
-// same cell, so the stores of a wave stay within a few neighbouring cells.
-__global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
-    if (t >= a.n_waves * kWave) return;
-    const int r = __builtin_amdgcn_readfirstlane(find_sys(a.lay.sbase, a.n_sys, t & ~(kWave - 1)));
-    const SysDesc d = a.sys[r];   // a copy: wave-uniform values in scalar registers
-    const int j = t - a.lay.sbase[r] + a.lay.off[r];   // position in the unpadded cell lists
-    if (j >= a.lay.off[r + 1]) return;                   // padding of this system
-    const int2 gc = a.tmp[j];
+// Particle gc.x of cell gc.y, whose members are at positions [b, e) of the
+// unordered cell lists: its position within the cell = number of members with
+// a smaller caller index, and its records there.
+template <typename Tmp>
+__device__ __forceinline__ void place_particle(const CellArgs &a, const SysDesc &d, int r, int2 gc, int b, int e,
+                                               Tmp tmp_index) {
     const int g = gc.x, c = gc.y;
-    const int b = a.start[c], e = a.start[c + 1];
     int rank = 0;
-    for (int k = b; k < e; k++) rank += a.tmp[k].x < g;
+    for (int k = b; k < e; k++) rank += tmp_index(k) < g;
     const int s = b + rank + (a.lay.sbase[r] - a.lay.off[r]);
     double xw, yw, z, qg;
     if (a.p32 || a.p64) {
@@ -219,6 +211,73 @@ __global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a) {
         const double zc = fmin(fmax(z, -d.rc), d.H + d.rc);
         a.src16[s] = make_uint4(to_fixed(xw, d.fxs), to_fixed(yw, d.fys), to_fixed(zc + d.zoff, d.fzs),
                                 __float_as_uint((float)qg));
+    }
+}
+
+// Sorted positions are padded per system to whole waves.  One thread per
+// padded sorted position, so a wave belongs to one system (its constants
+// are scalar loads); the thread takes slot j of the unordered cell lists
+// (tmp), gathers the particle it holds and writes its record within the
+// same cell, so the stores of a wave stay within a few neighbouring cells.
+__global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a) {
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= a.n_waves * kWave) return;
+    const int r = __builtin_amdgcn_readfirstlane(find_sys(a.lay.sbase, a.n_sys, t & ~(kWave - 1)));
+    const SysDesc d = a.sys[r];   // a copy: wave-uniform values in scalar registers
+    const int j = t - a.lay.sbase[r] + a.lay.off[r];   // position in the unpadded cell lists
+    if (j >= a.lay.off[r + 1]) return;                   // padding of this system
+    const int2 gc = a.tmp[j];
+    place_particle(a, d, r, gc, a.start[gc.y], a.start[gc.y + 1], [&](int k) { return a.tmp[k].x; });
+}
+
+// The whole build after the count in one launch, one block per system: a scan
+// of the system's cells (its first position is its particle offset), their
+// lists and the ordered records, through LDS, which has to hold the cells'
+// starts and the lists.  It takes the place of four launches of 5 to 6 us.
+// Beyond kSmallN particles in a system one block is slower than they are: a
+// force call of 10000 ions takes 109 us with it and 90 without, 16 slabs of
+// 300 to 3200 ions 95 with it and 101 without.
+constexpr int kSmallThreads = 1024;
+constexpr size_t kSmallLds = 60 << 10;
+constexpr int kSmallN = 4096;
+__global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a) {
+    extern __shared__ int lds[];
+    __shared__ int sh[kSmallThreads / kWave];
+    const int r = blockIdx.x;
+    const SysDesc &d = a.sys[r];
+    const int off = a.lay.off[r], N = a.lay.off[r + 1] - off;
+    const int c0 = d.cbase, nc = d.ncx * d.ncy * d.ncz;
+    int *start = lds;                                             // positions within the system
+    int *tmp = lds + nc + 1;                                      // cell lists: indices within the system
+    const int per = (nc + kSmallThreads - 1) / kSmallThreads;
+    const int lo = min(nc, (int)threadIdx.x * per), hi = min(nc, lo + per);
+    for (int c = threadIdx.x; c < nc; c += kSmallThreads) {
+        start[c] = a.count[c0 + c];
+        a.count[c0 + c] = 0;                                      // the next build counts from zero
+    }
+    __syncthreads();
+    int t = 0;
+    for (int c = lo; c < hi; c++) t += start[c];
+    int run = block_scan(t, sh);
+    for (int c = lo; c < hi; c++) {
+        const int v = start[c];
+        start[c] = run;
+        run += v;
+    }
+    if (threadIdx.x == 0) start[nc] = N;
+    __syncthreads();
+    // (the next system's first start equals this one's end)
+    for (int c = threadIdx.x; c < nc; c += kSmallThreads) a.start[c0 + c] = off + start[c];
+    if (r == a.n_sys - 1 && threadIdx.x == 0) a.start[c0 + nc] = off + N;
+    for (int i = threadIdx.x; i < N; i += kSmallThreads) {
+        const int c = a.cell[off + i];
+        tmp[start[c - c0] + a.slot[off + i]] = i;
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < N; j += kSmallThreads) {
+        const int g = off + tmp[j], c = a.cell[g];
+        place_particle(a, d, r, make_int2(g, c), off + start[c - c0], off + start[c - c0 + 1],
+                       [&](int k) { return off + tmp[k - off]; });
     }
 }
 
@@ -772,14 +831,21 @@ hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStr
     c.tmp = h->w.tmp; c.n_waves = h->n_swaves; c.sidx = h->w.sidx; c.scell = h->w.scell; c.sorted = h->w.sorted; c.src16 = h->w.src16;
     // counted by the MD pass: its k-space records of these positions precede this build on s
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
-    c.p32 = h->cells_counted && fp32 ? h->w.p32 : nullptr;
-    c.p64 = h->cells_counted && !fp32 ? h->w.p64 : nullptr;
+    const bool records = h->cells_counted && h->records_moved;
+    c.p32 = records && fp32 ? h->w.p32 : nullptr;
+    c.p64 = records && !fp32 ? h->w.p64 : nullptr;
     const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
     prof_begin(h, 3, s);
     // the counts start at zero (the previous build's scan cleared them); the
     // MD pass that moved the particles may have counted them already
     if (!h->cells_counted) hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, s, c);
     h->cells_counted = false;
+    const size_t lds = (h->max_cells + 1 + (size_t)h->max_n) * sizeof(int);
+    if (h->max_n <= kSmallN && lds <= kSmallLds) {
+        hipLaunchKernelGGL(k_cells_small, dim3(h->n_sys), dim3(kSmallThreads), lds, s, c);
+        prof_end(h, 3, s);
+        return hipGetLastError();
+    }
     const int nsb = (h->total_cells + kScanCells - 1) / kScanCells;
     hipLaunchKernelGGL(k_scan_totals, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf);
     hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf,
@@ -841,8 +907,14 @@ hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
 
 // F += F_real (the pair kernel's per-particle output), and in MD steps the
 // closing half kick v += dt/2 F with the completed force
+// (blocks from n_blocks on: the systems' energies)
 __global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, const double4 *freal, double *F, double *vel,
-                                                     double half_dt) {
+                                                     double half_dt, int n_blocks, EnergyArgs en) {
+    __shared__ double sh[kBlock / kWave];
+    if ((int)blockIdx.x >= n_blocks) {
+        energy_block(en, blockIdx.x - n_blocks, sh);
+        return;
+    }
     const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (g >= n) return;
     const double4 fr = freal[g];
@@ -854,11 +926,13 @@ __global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, const double4 *f
     }
 }
 
-hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s) {
+hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s, double *energy,
+                           uint32_t energy_flags) {
     if (h->n_total == 0) return hipSuccess;
     prof_begin(h, 10, s);
-    hipLaunchKernelGGL(k_add_real, dim3((unsigned)((h->n_total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       h->n_total, h->w.freal, F, vel, half_dt);
+    const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(k_add_real, dim3(nb + (energy ? h->n_sys : 0)), dim3(kBlock), 0, s, h->n_total, h->w.freal, F,
+                       vel, half_dt, nb, energy_args(h, energy, energy_flags, nullptr, nullptr));
     prof_end(h, 10, s);
     return hipGetLastError();
 }

@@ -1,0 +1,57 @@
+"""GPU parity of whole calls at the sizes where their launches change: one or
+two streams, the cell list in one launch or four, the force pass split over
+the waves of a block or not (with the energies in its launch or in one of
+their own).
+
+Bounds: the FP64 path's 1e-9 and the FP32 path's 1e-5."""
+import numpy as np
+import pytest
+
+from paper_2405_06333_amd import inputs
+from tests.gpu_common import energy_scale, gpu_slab, oracle_slab, rel_rms, to_dev
+
+pytestmark = pytest.mark.gpu
+TOL = {"fp64": 1e-9, "fp32": 1e-5}
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+@pytest.fixture(scope="module")
+def R():
+    from paper_2405_06333_amd import rbe2d
+    rbe2d.lib()
+    return rbe2d
+
+
+def wl(N, P, M=3):
+    L = max(10.0, (N / 1.2) ** 0.5)
+    return inputs.Workload(f"n{N}_p{P}", N, L, L * 1.1, 6.0, 0.8, -0.7, 1.0, 4.0, P, M, seed=N + P, margin=0.3)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N, P", [(1, 64), (64, 15), (65, 16), (200, 9), (257, 300), (1024, 40), (1025, 40), (4096, 33),
+                                  (4097, 33)])
+def test_force_calls(torch, R, orc, precision, N, P):
+    w = wl(N, P)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    kset = slab.draw_kset(w.seed)
+    slab.set_kset(kset)
+    pd, qd = to_dev(torch, pos), to_dev(torch, q)
+    ref = orc.evaluate(oracle_slab(orc, w, slab.Lz_ext), pos, q, kset, targets=None)
+    for _ in range(3):      # (the cell counts are clear again after each call)
+        F, E = slab.forces(pd, qd, want_energy=True)
+        assert rel_rms(F.cpu().numpy(), ref.F) <= TOL[precision]
+        for eg, er in zip(E.cpu().numpy(), ref.energies()):
+            assert abs(eg - er) <= TOL[precision] * energy_scale(ref)
+    # accumulation, and each half alone: their sum is the whole
+    G = slab.forces(pd, qd, flags=R.REAL)
+    H = torch.full_like(F, 0.5)
+    slab.forces(pd, qd, out=H, flags=R.KSPACE | R.IBC | R.ACCUMULATE)
+    assert torch.allclose(G + H - 0.5, F, rtol=0, atol=1e-13 * float(F.abs().max()) + 1e-13)
+    slab.check()
