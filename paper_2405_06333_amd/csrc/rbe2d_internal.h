@@ -28,7 +28,7 @@ constexpr int kMaxFamilies = 128;    // real-space image families (order, side) 
 constexpr int kWave = 64;
 constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
 constexpr int kMaxFamilySplit = 3;   // ... and its image families into further groups, for at most
-constexpr int64_t kFamilySplitMax = 16384;   // this many targets
+constexpr int64_t kFamilySplitMax = 49152;   // this many targets
 constexpr int kTileSplits = 4;       // FP64 real space: 1, 2, 4 or 8 waves share the pair work of 64 targets
 constexpr double kPi = 3.14159265358979323846;
 

@@ -452,20 +452,25 @@ struct LaneRings : TargetSums<DG> {
 // accumulates the drains in FP64.  The order of every sum is fixed by the
 // data, so the results are bitwise reproducible.
 //
-// SPLIT: too few targets to fill the chip.  Block row y takes every nsplit-th
-// column and block layer z one group of image families (0: the real charges);
-// a wave is then alone on its SIMD and bound by its own chain of instructions,
-// branches above all: the candidates of a batch are tested without one, and the
-// target itself is not sent through the FP64 geometry.  (Two rounds at a time,
-// or two and four batches of sources in flight, took 4 to 10 % longer.)  The FP32 sums are those of
-// the same drains either way.  3,000 ions, 300 pairs each: 63 us instead of 99.
-template <bool WANT_DG, bool ISO, bool SPLIT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SPLIT ? 2 : RBE2D_REAL_WAVES32, 8)))
+// SPLIT: too few targets to fill the chip.  1: block row y takes every
+// nsplit-th column.  2, up to kFamilySplitMax targets: besides, block layer z
+// takes one group of image families (0: the real charges); a wave is then
+// nearly alone on its SIMD and bound by its own chain of instructions,
+// branches above all: the candidates of a batch are tested without one, and
+// the target itself is not sent through the FP64 geometry.  (Two rounds at a
+// time, or two and four batches of sources in flight, took 4 to 10 % longer.)
+// The FP32 sums are those of the same drains in every form.  3,000 ions, 300
+// pairs each: 63 us instead of 99.  Whole force calls of 24,000 ions with
+// 2 against 1: 93 against 111 and 125 against 160 us; of 64,000: 142 against
+// 139 and 192 against 187.
+template <bool WANT_DG, bool ISO, int SPLIT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SPLIT == 2 ? 2 : RBE2D_REAL_WAVES32, 8)))
 void k_real(RealArgs a) {
+    constexpr bool FEW = SPLIT == 2;
     constexpr int U = RBE2D_REAL_U32;      // source loads in flight per lane, twice
     constexpr int kRingQ = RBE2D_RING_Q;   // ring entries per lane
     using Queue = LaneRings<kRingQ, U, ISO, WANT_DG>;
-    __shared__ __align__(16) unsigned char lds[sizeof(float4) * (kRingQ + (SPLIT ? 1 : 0)) * kBlock];
+    __shared__ __align__(16) unsigned char lds[sizeof(float4) * (kRingQ + (FEW ? 1 : 0)) * kBlock];
     const double4 *src = a.src;
     const int tid = threadIdx.x;
     // Blocks are dealt round-robin to the 8 XCDs.  Each XCD runs C contiguous
@@ -510,11 +515,11 @@ void k_real(RealArgs a) {
     // claims all 128 registers a wave may hold at 4 waves per SIMD (the kernel
     // uses 119): waves of the force pass (32 registers) would join the four
     // otherwise and slow both, MD step of the 1e6-ion slab 1.25 instead of 1.22 ms
-    if constexpr (!SPLIT) asm volatile("" ::: "v127");
+    if constexpr (!FEW) asm volatile("" ::: "v127");
     // with more than one layer of blocks: layer 0 the real charges, layers z >
     // 0 the families z, z + (layers - 1), ...
-    const int fstep = SPLIT && gridDim.z > 1 ? (blockIdx.z == 0 ? kMaxFamilies + 1 : (int)gridDim.z - 1) : 1;
-    for (int f = SPLIT ? (int)blockIdx.z : 0; f <= d.nfam; f += fstep) {
+    const int fstep = FEW && gridDim.z > 1 ? (blockIdx.z == 0 ? kMaxFamilies + 1 : (int)gridDim.z - 1) : 1;
+    for (int f = FEW ? (int)blockIdx.z : 0; f <= d.nfam; f += fstep) {
         double sz = 1.0, czs = 0.0, w = 1.0, zsign = 1.0, dwt = 0.0, dwb = 0.0;
         if (f > 0) {
             const Family fm = fams[f - 1];
@@ -574,7 +579,7 @@ void k_real(RealArgs a) {
                     if (qu.full()) qu.drain();
                     const bool inA = m0 < c4a;
                     const int lim = inA ? lenA : tot;          // candidates m < lim
-                    if constexpr (SPLIT) {
+                    if constexpr (FEW) {
                         // the four tests without a branch, one for the close
                         // pairs; the target itself is told by its index
                         const int j0 = jbA + m0;               // (no run B)
@@ -614,7 +619,7 @@ void k_real(RealArgs a) {
                         }
                     }
                 };
-                if constexpr (SPLIT) {
+                if constexpr (FEW) {
                     // no prefetch: the chain of instructions is the longer one
                     for (int m0 = 0; m0 < maxtot; m0 += U) {
                         uint4 s[U];
@@ -882,20 +887,18 @@ hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
     // few targets: the image families in two more layers of blocks
     int nfam = 0;
     for (const SysHost &sh : h->sys) nfam = std::max(nfam, sh.d.nfam);
-    const int layers = r.nsplit > 1 && h->n_total <= kFamilySplitMax ? std::min(kMaxFamilySplit, 1 + nfam) : 1;
+    const int split = r.nsplit == 1 ? 0 : h->n_total > kFamilySplitMax ? 1 : 2;
+    const int layers = split == 2 ? std::min(kMaxFamilySplit, 1 + nfam) : 1;
     const dim3 grid(nbc, r.nsplit, layers);
     prof_begin(h, 4, s);
-    const int variant = (want_dg ? 1 : 0) + (h->iso ? 2 : 0) + (r.nsplit > 1 ? 4 : 0);
-    switch (variant) {
-    case 0: hipLaunchKernelGGL((k_real<false, false, false>), grid, dim3(kBlock), 0, s, r); break;
-    case 1: hipLaunchKernelGGL((k_real<true, false, false>), grid, dim3(kBlock), 0, s, r); break;
-    case 2: hipLaunchKernelGGL((k_real<false, true, false>), grid, dim3(kBlock), 0, s, r); break;
-    case 3: hipLaunchKernelGGL((k_real<true, true, false>), grid, dim3(kBlock), 0, s, r); break;
-    case 4: hipLaunchKernelGGL((k_real<false, false, true>), grid, dim3(kBlock), 0, s, r); break;
-    case 5: hipLaunchKernelGGL((k_real<true, false, true>), grid, dim3(kBlock), 0, s, r); break;
-    case 6: hipLaunchKernelGGL((k_real<false, true, true>), grid, dim3(kBlock), 0, s, r); break;
-    default: hipLaunchKernelGGL((k_real<true, true, true>), grid, dim3(kBlock), 0, s, r);
-    }
+#define RBE2D_REAL(DG, ISO_, S) \
+    if (want_dg == DG && h->iso == ISO_ && split == S) \
+        hipLaunchKernelGGL((k_real<DG, ISO_, S>), grid, dim3(kBlock), 0, s, r);
+#define RBE2D_REAL_FORMS(S) \
+    RBE2D_REAL(false, false, S) RBE2D_REAL(true, false, S) RBE2D_REAL(false, true, S) RBE2D_REAL(true, true, S)
+    RBE2D_REAL_FORMS(0) RBE2D_REAL_FORMS(1) RBE2D_REAL_FORMS(2)
+#undef RBE2D_REAL_FORMS
+#undef RBE2D_REAL
     if (r.nsplit > 1) {
         const int64_t n = std::max<int64_t>(h->n_total, h->n_swaves);
         hipLaunchKernelGGL(k_real_combine, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, r,

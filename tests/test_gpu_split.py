@@ -35,6 +35,7 @@ def wl(seed, N, Lx, Ly, H, rc, gt=0.8, gb=-0.7, M=4):
 @pytest.mark.parametrize("w", [
     wl(1, 65, 12, 12, 5, 4), wl(2, 700, 14, 14, 0.9, 3.5, gt=1.0, gb=-1.0, M=10), wl(3, 700, 14, 11, 2.0, 3.5, M=3),
     wl(4, 900, 20, 20, 6, 4, gt=0.0, gb=0.0, M=0), wl(5, 16384, 90, 90, 6, 3, M=2), wl(6, 16385, 90, 80, 6, 3, M=2),
+    wl(8, 49152, 150, 150, 6, 3, M=2), wl(9, 49153, 150, 140, 6, 3, M=2),
 ], ids=lambda w: w.name)
 def test_families_and_columns(torch, R, orc, w):
     pos, q = inputs.sample(w)
