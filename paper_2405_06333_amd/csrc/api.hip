@@ -443,7 +443,7 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     // the FP32 records get one wave of padding: the pair kernel reads the first
     // record of an empty run, which may start at the end of the array
     if (fp32) { A(&w.src16, h->cap_sorted + kWave); A(&w.scell, h->cap_sorted); }
-    A(&w.freal, nc); A(&w.dgreal, nc);
+    A(&w.freal, nc);
     A(&w.rpart, 3 * (h->cap_sorted / kWave));
     // FP32 pair kernel: the split is only used when there are too few targets
     // to fill the chip
@@ -451,7 +451,6 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     const int64_t fam_cap = fp32 ? std::min<int64_t>(nc, kFamilySplitMax) : 0;
     const int64_t parts = std::max(kMaxRealSplit * h->split_cap, kMaxRealSplit * kMaxFamilySplit * fam_cap);
     A(&w.freal_s, parts);
-    A(&w.dgreal_s, h->one_stream ? 0 : parts);   // (the call without a handle forms no derivatives)
     A(&w.rpart_s, fp32 ? kMaxRealSplit * kMaxFamilySplit * 3 * (h->cap_sorted / kWave) : 0);
     A(&w.spart, 2 * (h->cap_sorted / kWave));
     A(&w.err, 4);
@@ -638,17 +637,22 @@ rbe2d_status check_arrays(rbe2d_ctx *h, const double *pos, const double *q) {
 }
 
 // One stream for the whole call?  Two let the k-space chain and the pair
-// kernel share the chip, but cost four event calls (15 to 20 us on the host,
-// as much as three launches) and the waits between streams.  Force calls
-// follow each other without a wait between them: up to kOneStreamForces ions
-// the host is what they wait for (N = 500, P = 100: 51 us on one stream, 70 on
-// two; from N = 1500 on two streams are 2 to 8 % faster).  An energy is read,
-// or differentiated, by the program that asked for it before its next one, so
-// that host and GPU take turns (energy and gradient of 20000 ions: 223 against
-// 253 us FP64, 229 against 256 FP32; of 60000: 321 against 362, 304 against
-// 301).
-constexpr int64_t kOneStreamForces = 1024, kOneStreamEnergy = 49152;
-bool on_one_stream(const rbe2d_ctx *h, int64_t limit) { return h->one_stream || h->n_total <= limit; }
+// kernel share the chip, but cost four event calls (10 us each on the host)
+// and the waits between streams; on one, the k-space work rides along with the
+// real-space launches.  us per force call on one stream | two: 1000 ions FP64
+// 62 | 70, 4000 FP32 71 | 79, 16000 FP64 76 | 87, 24000 FP32 86 | 88 and
+// 122 | 124, 48000 FP32 122 | 121 and 185 | 172, 90000 FP64 203 | 215 and
+// 256 | 259.  Energy and gradient, whose caller waits for each: 4000 ions
+// 173 | 232, 90000 FP64 380 | 454, 90000 FP32 380 | 391.
+constexpr int64_t kOneStreamForces32 = 24576, kOneStream = 98304;
+bool on_one_stream(const rbe2d_ctx *h, bool energy) {
+    return h->one_stream ||
+           h->n_total <= (!energy && h->precision == RBE2D_PREC_FP32_PHASE ? kOneStreamForces32 : kOneStream);
+}
+
+// On one stream the structure factors and the assembly ride along with the
+// real-space launches (not while the launches are timed class by class)
+bool rides_along(const rbe2d_ctx *h, bool one_stream) { return one_stream && h->n_total > 0 && h->prof.n == 0; }
 
 // `to` waits for what `from` has been given so far
 rbe2d_status stream_wait(rbe2d_ctx *h, hipStream_t to, hipStream_t from, hipEvent_t ev) {
@@ -672,14 +676,16 @@ rbe2d_status run_common(rbe2d_ctx *h, const double *pos, const double *q, uint32
     // with k-space the assembly launch computes the IBC scalars
     const bool sc_asm = (flags & RBE2D_KSPACE) != 0;
     if (kside) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
-    const bool two = sc_asm && real && h->n_total > 0 && !on_one_stream(h, kOneStreamEnergy);
+    const bool two = sc_asm && real && h->n_total > 0 && !on_one_stream(h, true);
     if (two) {
         rbe2d_status st = stream_wait(h, h->side, s, h->fork_ev);
         if (st) return st;
     }
     // real space is enqueued first: its cell list starts ahead of the structure factors
-    if (real) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s), "real-space launch");
-    if (sc_asm) RBE2D_TRY(h, launch_kcoef_sf(h, two ? h->side : s, true, want_dg), "structure-factor launch");
+    const bool ride = rides_along(h, sc_asm && real && !two);
+    const RideAlong ra;
+    if (real) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s, ride ? &ra : nullptr), "real-space launch");
+    if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, two ? h->side : s, true, want_dg), "structure-factor launch");
     return two ? stream_wait(h, s, h->side, h->join_ev) : RBE2D_OK;
 }
 
@@ -706,7 +712,7 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
                             bool accumulate, const ForceJob &job, hipStream_t s) {
     const bool kside = (parts & (RBE2D_KSPACE | RBE2D_IBC)) != 0, real = (parts & RBE2D_REAL) != 0;
     const bool sc_asm = (parts & RBE2D_KSPACE) != 0;
-    const bool two = kside && real && h->n_total > 0 && !on_one_stream(h, kOneStreamForces);
+    const bool two = kside && real && h->n_total > 0 && !on_one_stream(h, false);
     if (kside && !job.prepared) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
     hipStream_t ks = two ? h->side : s;
     if (two) {
@@ -715,11 +721,14 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     }
     // real space first: its latency-bound cell list then starts ahead of the
     // structure factors (also in a captured graph, whose nodes follow this order)
+    const bool ride = rides_along(h, sc_asm && real && !two);
+    RideAlong ra;
+    ra.step = job.step;
     if (real) {
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s), "real-space launch");
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr), "real-space launch");
         if (job.mx) RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, s, true), "short-range launch");
     }
-    if (sc_asm) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");
+    if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");
     ForceExtra x;
     if (!two) {
         x.vel = job.vel; x.half_dt = 0.5 * job.dt; x.energy = job.energy; x.err_out = job.err_out;

@@ -11,7 +11,9 @@ namespace rbe2d {
 // backward mode, gE * dE/dgamma_{top,bot}.  One block per system, fixed
 // summation order.
 struct EnergyArgs {
-    const double *krec, *rpart, *scal;
+    const double *krec, *scal;
+    const double *rpart;     // real-space sums per wave, in `parts` parts `stride` waves apart
+    int parts, stride;
     const SysDesc *sys;
     Layout lay;
     int P;
@@ -34,10 +36,13 @@ __device__ __forceinline__ void energy_block(const EnergyArgs &a, int r, double 
         }
     const bool has_real = a.do_real && a.lay.off[r + 1] > a.lay.off[r];
     if (has_real)
-        for (int wv = a.lay.sbase[r] / kWave + threadIdx.x; wv < a.lay.sbase[r + 1] / kWave; wv += (int)blockDim.x) {
-            er += a.rpart[3 * wv];
-            drt += a.rpart[3 * wv + 1];
-            drb += a.rpart[3 * wv + 2];
+        for (int p = 0; p < a.parts; p++) {
+            const double *rp = a.rpart + (int64_t)3 * p * a.stride;
+            for (int wv = a.lay.sbase[r] / kWave + threadIdx.x; wv < a.lay.sbase[r + 1] / kWave; wv += (int)blockDim.x) {
+                er += rp[3 * wv];
+                drt += rp[3 * wv + 1];
+                drb += rp[3 * wv + 2];
+            }
         }
     ek = block_sum(ek, sh);
     er = block_sum(er, sh);
@@ -71,8 +76,8 @@ __device__ __forceinline__ void energy_block(const EnergyArgs &a, int r, double 
 
 inline EnergyArgs energy_args(rbe2d_ctx *h, double *energy, uint32_t flags, const double *gE, double *dEdgamma) {
     EnergyArgs a;
-    a.krec = h->w.krec; a.rpart = h->w.rpart; a.scal = h->w.scal; a.sys = h->w.sys; a.lay = h->w.lay;
-    a.P = h->P;
+    a.krec = h->w.krec; a.rpart = h->real_parts > 1 ? h->w.rpart_s : h->w.rpart; a.scal = h->w.scal; a.sys = h->w.sys; a.lay = h->w.lay;
+    a.P = h->P; a.parts = h->real_parts; a.stride = (int)(h->cap_sorted / kWave);
     a.do_real = (flags & RBE2D_REAL) != 0;
     a.do_k = (flags & RBE2D_KSPACE) != 0;
     a.do_ibc = (flags & RBE2D_IBC) != 0;

@@ -18,6 +18,7 @@
 
 #include "devmath.h"
 #include "energy.h"
+#include "kspace_dev.h"
 #include "rbe2d_internal.h"
 #include "sampler.h"
 
@@ -107,7 +108,7 @@ struct PrepArgs {
     // MD update first (MD > 0): positions and velocities are updated in place
     double *pos_md, *vel;
     const double *F;
-    const double4 *freal;       // MD == 2: the pair kernel's part of the force
+    RealParts real;             // MD == 2: the pair kernel's part of the force
     double dt, zlo, zhi_from_top;
     // with count set: the cell and in-cell slot of each (moved) particle for
     // the next cell-list build (the counts start at zero)
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
         if (MD > 0) {
             double v[3], rr[3], add[3] = {0.0, 0.0, 0.0};
             if (MD == 2) {
-                const double4 fr = a.freal[g];
+                const double4 fr = a.real.sum(g);
                 add[0] = fr.x; add[1] = fr.y; add[2] = fr.z;
             }
             for (int c = 0; c < 3; c++) {
@@ -236,59 +237,6 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
     }
 }
 
-// scal layout (kScal per system): 0 mu = sum q z, 1 Q = sum q, 2 sum q^2,
-// 3 muM (image dipole of Theorem 3.3), 4 F_ibc,z / q_i, 5 offset of the
-// IBC potential, 6 dmuM/dgamma_top, 7 dmuM/dgamma_bot, 8 S2 = sum q z^2;
-// with surface charges (zero otherwise): F_z / q_i gains 10 + 9 z, the
-// potential dE/dq_i gains 11 + 12 z + 13 z^2, the energy 14, and
-// dE/dgamma_{top,bot} 15, 16
-struct ScalArgs {
-    const double *bpart;
-    const SysDesc *sys;
-    Layout lay;
-    double *scal;
-};
-
-// IBC scalars of system r from the prep pass's block sums, by one wave
-// (fixed summation order: the same in both launches that use it)
-__device__ void ibc_scalars(const ScalArgs &a, int r, int lane) {
-    const SysDesc &d = a.sys[r];
-    double v[4] = {0, 0, 0, 0};
-    for (int b = a.lay.bbase[r] + lane; b < a.lay.bbase[r + 1]; b += 64)
-        for (int c = 0; c < 4; c++) v[c] += a.bpart[4 * b + c];
-    for (int c = 0; c < 4; c++) v[c] = wave_sum(v[c]);
-    if (lane == 0) {
-        const double mu = v[0], Q = v[1], S2 = v[3];
-        const double muM = d.g1 * mu + d.cgam * Q;
-        const double tv = 2.0 * kPi / d.V * d.pref;
-        double *o = a.scal + kScal * r;
-        o[0] = mu;
-        o[1] = Q;
-        o[2] = v[2];
-        o[3] = muM;
-        o[4] = -tv * (muM + d.g1 * mu);
-        o[5] = tv * mu * d.cgam;
-        o[6] = d.dg1t * mu + d.dcgt * Q;
-        o[7] = d.dg1b * mu + d.dcgb * Q;
-        o[8] = S2;
-        for (int c = 9; c < kScal; c++) o[c] = 0.0;
-        if (d.surf) {
-            // sheets: phi_s = -Es z + Cs; net charge: U_Q = -(tv / 2) Q (2 Gs S2 + 2 A1 mu + A0 Q)
-            const double pe = d.pref;
-            o[9] = 2.0 * tv * Q * d.Gs[0];
-            o[10] = pe * d.Es[0] + tv * Q * d.A1[0];
-            o[11] = pe * d.Cs[0] - tv * (d.Gs[0] * S2 + d.A1[0] * mu + d.A0[0] * Q);
-            o[12] = -pe * d.Es[0] - tv * Q * d.A1[0];
-            o[13] = -tv * Q * d.Gs[0];
-            for (int k = 0; k < 3; k++) {
-                const double e = -0.5 * tv * Q * (2.0 * d.Gs[k] * S2 + 2.0 * d.A1[k] * mu + d.A0[k] * Q) +
-                                 pe * (-d.Es[k] * mu + d.Cs[k] * Q);
-                o[k == 0 ? 14 : 14 + k] = e;
-            }
-        }
-    }
-}
-
 __global__ __launch_bounds__(64) void k_scalars(ScalArgs a) { ibc_scalars(a, blockIdx.x, threadIdx.x); }
 
 static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
@@ -302,7 +250,7 @@ static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
     return a;
 }
 
-static ScalArgs scal_args(rbe2d_ctx *h) {
+ScalArgs scal_args(rbe2d_ctx *h) {
     ScalArgs b;
     b.bpart = h->w.bpart; b.sys = h->w.sys; b.lay = h->w.lay; b.scal = h->w.scal;
     return b;
@@ -338,7 +286,7 @@ hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const 
                           double zlo, double zhi_from_top, const MdExtra *mx, uint64_t seed, uint64_t stream_base,
                           const long long *dev_step, hipStream_t s) {
     PrepArgs a = prep_args(h, pos, q);
-    a.pos_md = pos; a.vel = vel; a.F = F; a.freal = h->w.freal;
+    a.pos_md = pos; a.vel = vel; a.F = F; a.real = real_parts(h);
     a.dt = dt; a.zlo = zlo; a.zhi_from_top = zhi_from_top;
     // a force evaluation with real space follows: count the particles per
     // cell here, where their new positions are at hand
@@ -365,145 +313,26 @@ hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const 
 //    Lanes own particles, the k-chunk is wave-uniform (scalar loads).
 // ---------------------------------------------------------------------------
 
-// Blocks are dealt round-robin to the 8 XCDs.  Map block b to (tile, k-chunk)
-// so that XCD b mod 8 runs all k-chunks of its tiles back to back: a tile is
-// then fetched into one XCD's L2 once instead of once per k-chunk.  The grid
-// has ceil(n_tiles / 8) * 8 * nkc blocks; blocks past the last tile exit.
-struct TileChunk {
-    int tile, kc;
-};
-__device__ __forceinline__ TileChunk tile_chunk(int b, int nkc) {
-    const int j = b >> 3;
-    return TileChunk{(j / nkc) * 8 + (b & 7), j % nkc};
-}
-
-// FP32 phases and transcendentals; each thread sums its (at most 16)
-// particles in FP32, and every sum after that -- across the 64 lanes, the
-// waves of the block and (in the assembly) the tiles -- is in FP64.
+// One block per (tile, k-chunk): kspace_dev.h.
 template <int KC>
 __global__ __launch_bounds__(kBlock) void k_sf32(const float4 *__restrict__ p32,
                                                  const float4 *__restrict__ kn, const int *tbase,
                                                  int n_sys, int per_thread, int P_pad, int n_tiles,
                                                  double *__restrict__ part) {
-    static_assert(4 * KC == 64, "one wave-transposed value per lane");
-    __shared__ double sh[kBlock / 64][64];
+    __shared__ SfLds32<KC> lds;
     const TileChunk tc = tile_chunk((int)blockIdx.x, P_pad / KC);
     if (tc.tile >= n_tiles) return;
-    const int r = find_sys(tbase, n_sys, tc.tile);
-    const float4 *knr = kn + (int64_t)r * P_pad + tc.kc * KC;
-    float acc[4 * KC];
-#pragma unroll
-    for (int v = 0; v < 4 * KC; v++) acc[v] = 0.0f;
-    const int64_t base = (int64_t)tc.tile * kBlock * per_thread + threadIdx.x;
-    for (int m = 0; m < per_thread; m++) {
-        const int64_t i = base + (int64_t)m * kBlock;
-        const float4 a = p32[2 * i];
-        const float4 b = p32[2 * i + 1];
-#pragma unroll
-        for (int kk = 0; kk < KC; kk++) {
-            const float4 n = knr[kk];
-            // nx fxh + ny fyh is exact (see the header comment)
-            float pxy = fractf(fmaf(n.y, a.z, n.x * a.x));
-            pxy = fmaf(n.x, a.y, pxy);
-            pxy = fmaf(n.y, a.w, pxy);
-            const float pz = fmaf(n.z, b.y, fractf(n.z * b.x));
-            const float ph = pxy + pz, phh = pxy - pz;
-            acc[4 * kk + 0] = fmaf(b.z, cos_rev(ph), acc[4 * kk + 0]);
-            acc[4 * kk + 1] = fmaf(b.z, sin_rev(ph), acc[4 * kk + 1]);
-            acc[4 * kk + 2] = fmaf(b.z, cos_rev(phh), acc[4 * kk + 2]);
-            acc[4 * kk + 3] = fmaf(b.z, sin_rev(phh), acc[4 * kk + 3]);
-        }
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    // first butterfly stage of the wave transpose-reduce: the FP32 values are
-    // exchanged, then widened and added in FP64; the other stages run in FP64
-    double v[2 * KC];
-    {
-        const bool upper = (lane & 32) != 0;
-#pragma unroll
-        for (int i = 0; i < 2 * KC; i++) {
-            const float send = upper ? acc[i] : acc[i + 2 * KC];
-            const float keep = upper ? acc[i + 2 * KC] : acc[i];
-            v[i] = (double)keep + (double)__shfl_xor(send, 32, 64);
-        }
-    }
-    TransposeStage<KC, 2 * KC, double>::run(v, lane);
-    sh[wid][lane] = v[0];
-    __syncthreads();
-    if (threadIdx.x < 4 * KC) {
-        double t = 0.0;
-#pragma unroll
-        for (int w = 0; w < kBlock / 64; w++) t += sh[w][threadIdx.x];
-        part[((int64_t)tc.tile * P_pad + tc.kc * KC) * 4 + threadIdx.x] = t;
-    }
+    sf32_block<KC, false>(p32, kn, tbase, n_sys, per_thread, P_pad, part, tc, threadIdx.x, lds.sh);
 }
-
-// FP64: the phases' xy and z parts are taken separately, with e = q e^{2 pi i
-// phi_xy} and z = 2 pi phi_z, into the four sums of (Re e, Im e) x (cos z, sin z)
-// whose sums and differences are rho and rhohat.  The k-vectors come sorted by
-// |nz| (k_ktable64), and sin z and cos z are kept from one to the next while
-// |nz| stays the same; both come from the table of devmath.h.  Bound by VALU
-// issue (0.98 of the slots): 26 instructions per (particle, k) and 20 more
-// where |nz| changes, instead of 70 for two full sine-cosine pairs.  1e6 ions,
-// P = 500, half of the |nz| repeated: 0.60 ms instead of 0.96.
 template <int KC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_sf64(const double4 *__restrict__ p64,
                                                  const double4 *__restrict__ ks, const int *tbase,
                                                  int n_sys, int per_thread, int P_pad, int n_tiles,
                                                  double *__restrict__ part) {
-    __shared__ double sh[kBlock / 64][4 * KC];
-    __shared__ double2 tab[kParts];
+    __shared__ SfLds64<KC> lds;
     const TileChunk tc = tile_chunk((int)blockIdx.x, P_pad / KC);
     if (tc.tile >= n_tiles) return;
-    if (threadIdx.x < kParts) tab[threadIdx.x] = make_double2(kPartTable[threadIdx.x][0], kPartTable[threadIdx.x][1]);
-    __syncthreads();
-    const int r = find_sys(tbase, n_sys, tc.tile);
-    const double4 *ksr = ks + (int64_t)r * P_pad + tc.kc * KC;
-    double acc[4 * KC];
-#pragma unroll
-    for (int v = 0; v < 4 * KC; v++) acc[v] = 0.0;
-    const int64_t base = (int64_t)tc.tile * kBlock * per_thread + threadIdx.x;
-    for (int m = 0; m < per_thread; m++) {
-        const double4 a = p64[base + (int64_t)m * kBlock];
-        double sz, cz;
-#pragma unroll
-        for (int kk = 0; kk < KC; kk++) {
-            const double4 n = ksr[kk];
-            if (kk == 0 || __double_as_longlong(n.z) != __double_as_longlong(ksr[kk - 1].z))
-                sincos_table64(n.z * a.z, tab, &sz, &cz);
-            double s, c;
-            sincos_table64(fma(n.y, a.y, n.x * a.x), tab, &s, &c);
-            const double qc = a.w * c, qs = a.w * s;
-            acc[4 * kk + 0] = fma(qc, cz, acc[4 * kk + 0]);
-            acc[4 * kk + 1] = fma(qs, sz, acc[4 * kk + 1]);
-            acc[4 * kk + 2] = fma(qs, cz, acc[4 * kk + 2]);
-            acc[4 * kk + 3] = fma(qc, sz, acc[4 * kk + 3]);
-            // keeps the sums of this k ahead of the next one's branch (the
-            // compiler gathers them at the end otherwise, with 182 registers)
-            asm volatile("" : "+v"(acc[4 * kk]), "+v"(acc[4 * kk + 1]), "+v"(acc[4 * kk + 2]), "+v"(acc[4 * kk + 3]));
-        }
-    }
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    wave_transpose_reduce<4 * KC>(acc, lane);
-    if (lane < 4 * KC) sh[wid][lane] = acc[0];
-    __syncthreads();
-    if (threadIdx.x < 4 * KC) {
-        // rho (re, im) and rhohat (re, im) of one k; for nz < 0 the two change places
-        const int kk = threadIdx.x >> 2, v = threadIdx.x & 3;
-        const double id = ksr[kk].w;    // +-(1 + index in the k-set), the sign of nz; 0: padding
-        if (id != 0.0) {
-            const int l = (int)fabs(id) - 1;
-            double t = 0.0, u = 0.0;
-#pragma unroll
-            for (int w = 0; w < kBlock / 64; w++) {
-                t += sh[w][4 * kk + 2 * (v & 1)];
-                u += sh[w][4 * kk + 2 * (v & 1) + 1];
-            }
-            // rho: cc - ss, sc + cs; rhohat: cc + ss, sc - cs
-            const bool hat = (v >= 2) != (id < 0.0);
-            part[((int64_t)tc.tile * P_pad + l) * 4 + v] = hat == ((v & 1) != 0) ? t - u : t + u;
-        }
-    }
+    sf64_block<KC, false>(p64, ks, tbase, n_sys, per_thread, P_pad, part, tc, threadIdx.x, lds.sh, lds.tab);
 }
 
 // ---------------------------------------------------------------------------
@@ -514,146 +343,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 //    One wave per (system, k); lanes split the tiles and the image orders.
 // ---------------------------------------------------------------------------
 
-struct AssembleArgs {
-    const double *part;         // structure-factor partials [tile][P_pad][4], FP64 in both precisions
-    int P, P_pad;
-    const int *tbase;
-    const int32_t *kset;
-    const SysDesc *sys;
-    const ImgTable *img;
-    double *krec;
-    float4 *kf32;
-    double *kf64;              // FP64: the force pass's records
-    int n_sys, with_scalars;   // with_scalars: n_sys more blocks compute the IBC scalars
-    ScalArgs sc;
-    long long *step;           // MD step counter to advance, or null
-};
-
-__device__ __forceinline__ double dmono(int e_self, double g_self, int e_other, double g_other) {
-    // d/dg_self of g_self^e_self g_other^e_other
-    if (e_self == 0) return 0.0;
-    double r = (double)e_self;
-    for (int i = 0; i < e_self - 1; i++) r *= g_self;
-    for (int i = 0; i < e_other; i++) r *= g_other;
-    return r;
-}
-
-// a double held by lane `src`, read by every lane
-__device__ __forceinline__ double lane_value(double v, int src) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
-                            __builtin_amdgcn_readlane(__double2loint(v), src));
-}
-
-// One wave per (system, k).  DG: also the gamma derivatives of Y_odd and
-// Y_even (for dE/dgamma; zero otherwise).
 template <bool DG>
 __global__ __launch_bounds__(64) void k_assemble(AssembleArgs a) {
-    if ((int)blockIdx.x >= a.n_sys * a.P) {
-        const int r = blockIdx.x - a.n_sys * a.P;
-        ibc_scalars(a.sc, r, threadIdx.x);
-        if (a.step && r == 0 && threadIdx.x == 0) *a.step += 1;
-        return;
-    }
-    const int r = blockIdx.x / a.P, l = blockIdx.x - r * a.P;
-    const SysDesc &d = a.sys[r];
-    const ImgTable &it = a.img[r];
-    const int lane = threadIdx.x;
-    // v[0..3]: this lane's share of rho and rhohat (lanes split the tiles);
-    // v[4..7]: Yo, Ye; v[8..15]: dYo/dg_top, dYe/dg_top, dYo/dg_bot,
-    // dYe/dg_bot (lanes split the image orders o = lane+1, lane+65, ...)
-    constexpr int NV = DG ? 16 : 8;
-    double v[NV];
-#pragma unroll
-    for (int c = 0; c < NV; c++) v[c] = 0.0;
-    for (int t = a.tbase[r] + lane; t < a.tbase[r + 1]; t += 64) {
-        const int64_t o = ((int64_t)t * a.P_pad + l) * 4;
-        for (int c = 0; c < 4; c++) v[c] += a.part[o + c];
-    }
-    const int64_t kg = (int64_t)r * a.P + l;
-    const int nx = a.kset[3 * kg], ny = a.kset[3 * kg + 1], nz = a.kset[3 * kg + 2];
-    const double rev_per_H = (double)nz * d.H / d.Lz;   // kz H / (2 pi)
-    for (int o = lane + 1; o <= d.M; o += 64) {
-        const double gpl = it.gp[o - 1], gml = it.gm[o - 1];
-        double mp, mm;   // multiples of kz H in the exponents of the + and - terms
-        int slot;
-        if (o & 1) { mp = (double)(o + 1); mm = -(double)(o - 1); slot = 4; }
-        else       { mp = (double)o;       mm = -(double)o;       slot = 6; }
-        double sp, cp, sm, cm;
-        sincos_rev64(mp * rev_per_H, &sp, &cp);
-        sincos_rev64(mm * rev_per_H, &sm, &cm);
-        v[slot] += gpl * cp + gml * cm;
-        v[slot + 1] += gpl * sp + gml * sm;
-        if constexpr (DG) {
-            const double dpt = dmono(it.ea_p[o - 1], d.g_top, it.eb_p[o - 1], d.g_bot);
-            const double dmt = dmono(it.ea_m[o - 1], d.g_top, it.eb_m[o - 1], d.g_bot);
-            const double dpb = dmono(it.eb_p[o - 1], d.g_bot, it.ea_p[o - 1], d.g_top);
-            const double dmb = dmono(it.eb_m[o - 1], d.g_bot, it.ea_m[o - 1], d.g_top);
-            v[4 + slot] += dpt * cp + dmt * cm;
-            v[5 + slot] += dpt * sp + dmt * sm;
-            v[8 + slot] += dpb * cp + dmb * cm;
-            v[9 + slot] += dpb * sp + dmb * sm;
-        }
-    }
-    // the NV wave sums at once (fixed-order butterfly): lane c then holds
-    // the sum of value c, which every lane reads
-    wave_transpose_reduce<NV>(v, lane);
-    double S[NV];
-#pragma unroll
-    for (int c = 0; c < NV; c++) S[c] = lane_value(v[0], c);
-    const double rr = S[0], ri = S[1], hr = S[2], hi = S[3];
-    const double *y = S + 4;   // Yo, Ye (re, im), then the derivatives
-    const double kx = 2.0 * kPi * nx / d.Lx, ky = 2.0 * kPi * ny / d.Ly, kz = 2.0 * kPi * nz / d.Lz;
-    const double k2 = kx * kx + ky * ky + kz * kz;
-    const double c = d.cfac / k2;
-    // rho^M = (1 + Ye) rho + Yo rhohat
-    const double er = 1.0 + y[2], ei = y[3];
-    const double mr = er * rr - ei * ri + y[0] * hr - y[1] * hi;
-    const double mi = er * ri + ei * rr + y[0] * hi + y[1] * hr;
-    // A = rho^M + (1 + conj Ye) rho ; B = conj(Yo) rho
-    const double Ar = mr + er * rr + ei * ri;
-    const double Ai = mi + er * ri - ei * rr;
-    const double Br = y[0] * rr + y[1] * ri;
-    const double Bi = y[0] * ri - y[1] * rr;
-    // polar form for the force passes, Im(e^{-i ph} cA) = |cA| sin(arg cA - ph):
-    // lane 1 for A, lane 2 for B, in parallel
-    constexpr double inv2pi = 0.15915494309189535;
-    double mag = 0.0, arg = 0.0;
-    if (lane == 1 || lane == 2) {
-        const double xr = lane == 1 ? Ar : Br, xi = lane == 1 ? Ai : Bi;
-        mag = c * hypot(xr, xi);
-        arg = atan2(xi, xr) * inv2pi;
-    }
-    const double magA = lane_value(mag, 1), argA = lane_value(arg, 1);
-    const double magB = lane_value(mag, 2), argB = lane_value(arg, 2);
-    if (lane != 0) return;
-    const double e = c * (rr * mr + ri * mi);
-    // d e / d gamma = c Re(rho conj(dYe rho + dYo rhohat))
-    double de[2] = {0.0, 0.0};
-    if constexpr (DG) {
-        for (int w = 0; w < 2; w++) {
-            const double *dy = y + 4 + 4 * w;
-            const double tr = dy[2] * rr - dy[3] * ri + dy[0] * hr - dy[1] * hi;
-            const double ti = dy[2] * ri + dy[3] * rr + dy[0] * hi + dy[1] * hr;
-            de[w] = c * (rr * tr + ri * ti);
-        }
-    }
-    double *rec = a.krec + kg * kKRec;
-    rec[0] = kx; rec[1] = ky; rec[2] = kz;
-    rec[3] = c * Ar; rec[4] = c * Ai; rec[5] = c * Br; rec[6] = c * Bi;
-    rec[7] = e; rec[8] = de[0]; rec[9] = de[1];
-    rec[10] = nx; rec[11] = ny; rec[12] = nz;
-    rec[13] = rr; rec[14] = ri; rec[15] = kx * kx + ky * ky;
-    rec[16] = magA; rec[17] = argA; rec[18] = magB; rec[19] = argB;
-    if (a.kf64) {
-        double *f = a.kf64 + kg * kKF64;
-        f[0] = nx; f[1] = ny; f[2] = nz;
-        f[4] = magA; f[5] = argA; f[6] = magB; f[7] = argB;
-        f[8] = c * Ar; f[9] = c * Ai; f[10] = c * Br; f[11] = c * Bi;
-        return;
-    }
-    a.kf32[3 * kg] = make_float4((float)kx, (float)ky, (float)kz, (float)(kx * kx + ky * ky));
-    a.kf32[3 * kg + 1] = make_float4((float)(c * Ar), (float)(c * Ai), (float)(c * Br), (float)(c * Bi));
-    a.kf32[3 * kg + 2] = make_float4((float)magA, (float)argA, (float)magB, (float)argB);
+    assemble_wave<DG>(a, blockIdx.x, threadIdx.x);
 }
 
 int choose_tile(int64_t N, int n_kchunks) {
@@ -668,32 +360,45 @@ int choose_tile(int64_t N, int n_kchunks) {
     return per;
 }
 
-hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool want_dg, long long *step) {
-    const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
-    prof_begin(h, 1, s);
-    if (h->n_tiles > 0) {
-        const int tiles8 = (h->n_tiles + 7) / 8 * 8;
-        if (fp32) {
-            const dim3 g((unsigned)tiles8 * (h->P_pad / kKChunk32));
-            hipLaunchKernelGGL(k_sf32<kKChunk32>, g, dim3(kBlock), 0, s, h->w.p32, h->w.kn32, h->w.lay.tbase,
-                               h->n_sys, h->per, h->P_pad, h->n_tiles, (double *)h->w.sfpart);
-        } else {
-            const dim3 g((unsigned)tiles8 * (h->P_pad / kKChunk64));
-            hipLaunchKernelGGL(k_sf64<kKChunk64>, g, dim3(kBlock), 0, s, h->w.p64, h->w.kn64, h->w.lay.tbase,
-                               h->n_sys, h->per, h->P_pad, h->n_tiles, (double *)h->w.sfpart);
-        }
-    }
-    prof_end(h, 1, s);
+SfArgs sf_args(rbe2d_ctx *h) {
+    SfArgs a;
+    a.p32 = h->w.p32; a.p64 = h->w.p64; a.kn32 = h->w.kn32; a.kn64 = h->w.kn64; a.tbase = h->w.lay.tbase;
+    a.n_sys = h->n_sys; a.per = h->per; a.P_pad = h->P_pad; a.n_tiles = h->n_tiles;
+    a.part = (double *)h->w.sfpart;
+    return a;
+}
+
+AssembleArgs assemble_args(rbe2d_ctx *h, bool with_scalars, long long *step) {
     AssembleArgs a;
     a.part = (const double *)h->w.sfpart; a.P = h->P; a.P_pad = h->P_pad;
     a.tbase = h->w.lay.tbase; a.kset = h->w.kset; a.sys = h->w.sys; a.img = h->w.img;
-    a.krec = h->w.krec; a.kf32 = h->w.kf32; a.kf64 = fp32 ? nullptr : h->w.kf64;
+    a.krec = h->w.krec; a.kf32 = h->w.kf32;
+    a.kf64 = h->precision == RBE2D_PREC_FP32_PHASE ? nullptr : h->w.kf64;
     a.n_sys = h->n_sys; a.with_scalars = with_scalars; a.sc = scal_args(h);
     a.step = step;
+    return a;
+}
+
+hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars, bool want_dg, long long *step) {
+    prof_begin(h, 1, s);
+    if (h->n_tiles > 0) {
+        const SfArgs a = sf_args(h);
+        const int tiles8 = (h->n_tiles + 7) / 8 * 8;
+        if (h->precision == RBE2D_PREC_FP32_PHASE)
+            hipLaunchKernelGGL(k_sf32<kKChunk32>, dim3((unsigned)tiles8 * (h->P_pad / kKChunk32)), dim3(kBlock), 0, s,
+                               a.p32, a.kn32, a.tbase, a.n_sys, a.per, a.P_pad, a.n_tiles, a.part);
+        else
+            hipLaunchKernelGGL(k_sf64<kKChunk64>, dim3((unsigned)tiles8 * (h->P_pad / kKChunk64)), dim3(kBlock), 0, s,
+                               a.p64, a.kn64, a.tbase, a.n_sys, a.per, a.P_pad, a.n_tiles, a.part);
+    }
+    prof_end(h, 1, s);
+    return launch_assemble(h, assemble_args(h, with_scalars, step), want_dg, s);
+}
+
+hipError_t launch_assemble(rbe2d_ctx *h, const AssembleArgs &a, bool want_dg, hipStream_t s) {
     prof_begin(h, 2, s);
-    const dim3 ga(h->n_sys * h->P + (with_scalars ? h->n_sys : 0));
-    if (want_dg) hipLaunchKernelGGL(k_assemble<true>, ga, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL(k_assemble<false>, ga, dim3(64), 0, s, a);
+    if (want_dg) hipLaunchKernelGGL(k_assemble<true>, dim3(a.items()), dim3(64), 0, s, a);
+    else hipLaunchKernelGGL(k_assemble<false>, dim3(a.items()), dim3(64), 0, s, a);
     prof_end(h, 2, s);
     return hipGetLastError();
 }
@@ -717,7 +422,7 @@ struct ForceArgs {
     const double *pos;       // for the IBC potential (z_i)
     const double *q;
     const double *scal;
-    const double4 *freal;    // added when add_real
+    RealParts real;          // added when add_real
     double *F;               // final output (caller order, N x 3)
     double *dEdq;            // final dE/dq when want_pot
     double *var;             // force-variance estimate per particle (variance mode)
@@ -733,22 +438,24 @@ struct ForceArgs {
     int32_t *err_out;
 };
 
-__device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64_t g, double fx,
-                                                double fy, double fz, double pot) {
+// f: the sums over k (times q_i and with the real-space part: force_terms)
+__device__ __forceinline__ double4 force_terms(const ForceArgs &a, double qi, const double4 &f,
+                                               const double4 &real) {
+    if (a.want_var || !a.do_kspace) return a.want_var ? f : real;
+    return make_double4(fma(-qi, f.x, real.x), fma(-qi, f.y, real.y), fma(-qi, f.z, real.z), real.w + f.w);
+}
+
+__device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64_t g, double qi, const double4 &f) {
     const SysDesc &d = a.sys[r];
     const double *sc = a.scal + kScal * r;
-    const double qi = a.q[g];
     if (a.want_var) {
-        // pot carries sum_l |t_l|^2 / q_i^2: (P sum |t|^2 - |F|^2) / (P - 1)
+        // f.w carries sum_l |t_l|^2 / q_i^2: (P sum |t|^2 - |F|^2) / (P - 1)
         const double P = (double)a.P;
-        a.var[g] = a.P > 1 ? qi * qi * (P * pot - (fx * fx + fy * fy + fz * fz)) / (P - 1.0) : 0.0;
+        a.var[g] = a.P > 1 ? qi * qi * (P * f.w - (f.x * f.x + f.y * f.y + f.z * f.z)) / (P - 1.0) : 0.0;
         return;
     }
-    double Fx = 0, Fy = 0, Fz = 0, ph = 0;
-    if (a.do_kspace) {
-        Fx = -qi * fx; Fy = -qi * fy; Fz = -qi * fz;
-        ph = pot - 2.0 * d.alpha * d.pref / sqrt(kPi) * qi;   // + dE_self/dq_i
-    }
+    double Fx = f.x, Fy = f.y, Fz = f.z, ph = f.w;
+    if (a.do_kspace) ph -= 2.0 * d.alpha * d.pref / sqrt(kPi) * qi;   // + dE_self/dq_i
     if (a.do_ibc) {
         if (d.surf) {
             // IBC with the surface terms: linear (and quadratic) in z
@@ -760,10 +467,6 @@ __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64
             ph += -sc[4] * a.pos[3 * g + 2] + sc[5];
         }
     }
-    if (a.add_real) {
-        const double4 rr = a.freal[g];
-        Fx += rr.x; Fy += rr.y; Fz += rr.z; ph += rr.w;
-    }
     if (a.want_pot) {
         // backward: dL/dr = -gE F, dL/dq = gE phi
         const double gs = a.gE ? *a.gE : 1.0;
@@ -773,24 +476,12 @@ __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64
         if (a.dEdq) a.dEdq[g] = gs * ph;
         return;
     }
-    const double f[3] = {Fx, Fy, Fz};
+    const double o[3] = {Fx, Fy, Fz};
     for (int c = 0; c < 3; c++) {
-        const double v = a.accumulate ? a.F[3 * g + c] + f[c] : f[c];
+        const double v = a.accumulate ? a.F[3 * g + c] + o[c] : o[c];
         a.F[3 * g + c] = v;
         if (a.vel) a.vel[3 * g + c] = fma(a.half_dt, v, a.vel[3 * g + c]);
     }
-}
-
-// The per-k records of a force pass are the same for a whole wave: read as
-// constant memory they come by scalar loads also where the compiler cannot
-// tell that the launch's other stores (the split pass's LDS, the energies)
-// leave them alone; as vector loads they took 40 more registers.
-typedef float vec4f __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(4))) vec4f ConstFloat4;
-typedef __attribute__((address_space(4))) double ConstDouble;
-__device__ __forceinline__ float4 record(const float4 *p) {
-    const vec4f v = *(const ConstFloat4 *)p;
-    return make_float4(v.x, v.y, v.z, v.w);
 }
 
 // Blocks of the force pass.  SPLIT (too few particles to fill the chip): the
@@ -814,21 +505,32 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
         const int Nr = a.lay.off[r + 1] - a.lay.off[r];
         if (first >= Nr) return;
         const int64_t ii = (int64_t)a.lay.pbase[r] + first + lane;   // (the records are padded)
-        double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
+        const bool on = first + lane < Nr;
+        const int64_t g = (int64_t)a.lay.off[r] + first + (on ? lane : 0);
+        const int nw = blockDim.x / kWave;
+        const double qi = a.q[g];
+        // the parts of the real-space forces too are dealt to the waves
+        double4 real = make_double4(0.0, 0.0, 0.0, 0.0), f = real;
+        if (a.add_real)
+            for (int p = wid; p < a.real.n; p += nw) {
+                const double4 v = a.real.f[p * a.real.stride + g];
+                real.x += v.x; real.y += v.y; real.z += v.z; real.w += v.w;
+            }
         if (a.do_kspace)
-            for (int k = wid; k < a.split; k += blockDim.x / kWave)
+            for (int k = wid; k < a.split; k += nw)
                 sum(r, ii, k * a.k_per_split, min(a.P, (k + 1) * a.k_per_split), f);
         // (stores only from here on: the loads above stay scalar)
         if (a.err_out && blockIdx.x == 0 && threadIdx.x == 0) *a.err_out = *a.err;
         double4 *part = reinterpret_cast<double4 *>(fsh);
+        f = force_terms(a, qi, f, real);
         part[threadIdx.x] = f;
         __syncthreads();
-        if (wid != 0 || first + lane >= Nr) return;
-        for (int w = 1; w < (int)blockDim.x / kWave; w++) {
+        if (wid != 0 || !on) return;
+        for (int w = 1; w < nw; w++) {
             const double4 v = part[w * kWave + lane];
             f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
         }
-        finish_particle(a, r, (int64_t)a.lay.off[r] + first + lane, f.x, f.y, f.z, f.w);
+        finish_particle(a, r, g, qi, f);
     } else {
         const int b = blockIdx.x;
         const int r = find_sys(a.lay.bbase, a.n_sys, b);
@@ -836,7 +538,9 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
         if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
         double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
         if (a.do_kspace) sum(r, (int64_t)a.lay.pbase[r] + iloc, 0, a.P, f);
-        finish_particle(a, r, (int64_t)a.lay.off[r] + iloc, f.x, f.y, f.z, f.w);
+        const int64_t g = (int64_t)a.lay.off[r] + iloc;
+        const double qi = a.q[g];
+        finish_particle(a, r, g, qi, force_terms(a, qi, f, a.add_real ? a.real.sum<1>(g) : make_double4(0, 0, 0, 0)));
     }
 }
 
@@ -970,7 +674,7 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
     a.p32 = h->w.p32; a.p64 = h->w.p64; a.kn32 = h->w.kn32;
     a.kf32 = h->w.kf32; a.kf64 = h->w.kf64; a.lay = h->w.lay; a.sys = h->w.sys;
     a.n_sys = h->n_sys; a.P = h->P; a.P_pad = h->P_pad;
-    a.pos = pos; a.q = q; a.scal = h->w.scal; a.freal = h->w.freal;
+    a.pos = pos; a.q = q; a.scal = h->w.scal; a.real = real_parts(h);
     a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = x.var; a.vel = x.vel; a.half_dt = x.half_dt;
     a.accumulate = accumulate; a.add_real = add_real; a.want_pot = want_pot; a.want_var = x.var != nullptr;
     a.do_kspace = (flags & RBE2D_KSPACE) != 0; a.do_ibc = (flags & RBE2D_IBC) != 0;

@@ -29,7 +29,7 @@ constexpr int kWave = 64;
 constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
 constexpr int kMaxFamilySplit = 3;   // ... and its image families into further groups, for at most
 constexpr int64_t kFamilySplitMax = 49152;   // this many targets
-constexpr int kTileSplits = 4;       // FP64 real space: 1, 2, 4 or 8 waves share the pair work of 64 targets
+constexpr int kTileSplits = 4;       // FP64 real space: 1, 2, 4 or 12 waves share the pair work of 64 targets
 constexpr double kPi = 3.14159265358979323846;
 
 // One family of image sources for the real-space sum, seen from the target:
@@ -146,12 +146,10 @@ struct Workspace {
     int *sidx = nullptr;        // caller index of sorted particle
     int *scell = nullptr;       // local cell of sorted particle (FP32 kernel)
     double4 *freal = nullptr;   // per caller particle: F_real (x, y, z), phi_real
-    double2 *dgreal = nullptr;  // per caller particle: d phi_real / d gamma_{top,bot}
     double *rpart = nullptr;    // per real-space wave: sum q phi, sum q dphi/dg_top, .../dg_bot
     // partial real-space outputs when the pair work of each target is split
     // over several blocks (small N, FP32): [split][split_cap] / [split][waves]
     double4 *freal_s = nullptr;
-    double2 *dgreal_s = nullptr;
     double *rpart_s = nullptr;
     double *spart = nullptr;    // per real-space wave: short-range pair and wall energies
     int *err = nullptr;         // device error word
@@ -194,6 +192,7 @@ struct rbe2d_ctx {
     int64_t split_cap = 0;           // targets per split of the partial real-space outputs
     int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most
     bool one_stream = false;         // run the k-space chain on the caller's stream too (no side stream)
+    int real_parts = 1;              // parts of the last pair sums (1: freal, rpart; else freal_s, rpart_s)
     bool cells_counted = false;      // the preparation counted the particles per cell (next build skips it)
     bool records_moved = false;      // ... in an MD pass, whose particle records the build reads
     bool kset_valid = false;
@@ -243,6 +242,30 @@ struct rbe2d_ctx {
 
 namespace rbe2d {
 
+// Per-particle outputs of the pair kernel, in parts `stride` apart; whoever
+// needs them adds the parts, in their order
+struct RealParts {
+    const double4 *f;
+    int n;
+    int64_t stride;
+    template <int B = kMaxRealSplit>   // loads in flight
+    __device__ __forceinline__ double4 sum(int64_t g) const {
+        double4 t = f[g];
+        for (int p0 = 1; p0 < n; p0 += B) {
+            double4 v[B];
+#pragma unroll
+            for (int k = 0; k < B; k++) v[k] = f[min(p0 + k, n - 1) * stride + g];
+#pragma unroll
+            for (int k = 0; k < B; k++)
+                if (p0 + k < n) { t.x += v[k].x; t.y += v[k].y; t.z += v[k].z; t.w += v[k].w; }
+        }
+        return t;
+    }
+};
+inline RealParts real_parts(const rbe2d_ctx *h) {
+    return h->real_parts > 1 ? RealParts{h->w.freal_s, h->real_parts, h->n_total} : RealParts{h->w.freal, 1, 0};
+}
+
 // kernel launchers (return hipSuccess or the launch error); all systems at once
 // k-vector tables, particle records and IBC block sums; with scalars, also
 // the IBC scalars (else the assembly launch computes them); with count, also
@@ -268,10 +291,15 @@ struct ForceExtra {
 hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, double *F, double *dEdq,
                          uint32_t flags, bool accumulate, bool want_pot, bool add_real, const double *gE,
                          hipStream_t s, const ForceExtra &x = ForceExtra());
-hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s);
-hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);
-hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);
-hipError_t launch_tile_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s);   // FP64
+// Cell list and pair sums.  With `ride` the structure factors and the per-k
+// assembly (with the IBC scalars) are blocks of these launches: for calls on
+// one stream, instead of launch_kcoef_sf.
+struct RideAlong {
+    long long *step = nullptr;   // as in launch_kcoef_sf
+};
+hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
+                       const RideAlong *ride = nullptr);
+hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);   // the cell list alone
 // F += F_real (and v += half_dt F); also the energies when energy is set
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s,
                            double *energy = nullptr, uint32_t energy_flags = 0);

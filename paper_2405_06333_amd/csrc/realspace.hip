@@ -15,6 +15,7 @@
 #include "devmath.h"
 #include "energy.h"
 #include "erfcx_fit.h"
+#include "kspace_dev.h"
 #include "rbe2d_internal.h"
 
 // Compile-time parameters of the FP32 pair kernel (measured best on the
@@ -214,13 +215,44 @@ __device__ __forceinline__ void place_particle(const CellArgs &a, const SysDesc 
     }
 }
 
+// SF: the structure factors of the call (FP32 or FP64) are further blocks of
+// the cell-list launch.  On one stream they wait for each other otherwise, with
+// most of the chip idle: 500 ions, 5 + 5 us.
+enum SfKind { kNoSf, kSf32, kSf64 };
+template <SfKind SF>
+struct SfRide {
+    static constexpr int kLds = SF == kNoSf ? 1 : SF == kSf32 ? sizeof(SfLds32<kKChunk32>) : sizeof(SfLds64<kKChunk64>);
+    // part `b` of the structure factors by kBlock threads (past the last: the last once more)
+    static __device__ __forceinline__ void run(const SfArgs &a, int b, int tid, void *lds) {
+        const int nkc = a.P_pad / (SF == kSf32 ? kKChunk32 : kKChunk64);
+        b = min(b, a.n_tiles * nkc - 1);
+        const TileChunk tc{b / nkc, b % nkc};
+        if constexpr (SF == kSf32)
+            sf32_block<kKChunk32, true>(a.p32, a.kn32, a.tbase, a.n_sys, a.per, a.P_pad, a.part, tc, tid,
+                                        ((SfLds32<kKChunk32> *)lds)->sh);
+        if constexpr (SF == kSf64) {
+            SfLds64<kKChunk64> *l = (SfLds64<kKChunk64> *)lds;
+            sf64_block<kKChunk64, true>(a.p64, a.kn64, a.tbase, a.n_sys, a.per, a.P_pad, a.part, tc, tid, l->sh, l->tab);
+        }
+    }
+    static int parts(const SfArgs &a) { return a.n_tiles * (a.P_pad / (SF == kSf32 ? kKChunk32 : kKChunk64)); }
+};
+
 // Sorted positions are padded per system to whole waves.  One thread per
 // padded sorted position, so a wave belongs to one system (its constants
 // are scalar loads); the thread takes slot j of the unordered cell lists
 // (tmp), gathers the particle it holds and writes its record within the
 // same cell, so the stores of a wave stay within a few neighbouring cells.
-__global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a) {
-    const int t = blockIdx.x * kBlock + threadIdx.x;
+template <SfKind SF>
+__global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a, SfArgs sf, int n_sf) {
+    if constexpr (SF != kNoSf) {
+        __shared__ __align__(16) unsigned char lds[SfRide<SF>::kLds];
+        if ((int)blockIdx.x < n_sf) {
+            SfRide<SF>::run(sf, blockIdx.x, threadIdx.x, lds);
+            return;
+        }
+    }
+    const int t = (blockIdx.x - n_sf) * kBlock + threadIdx.x;
     if (t >= a.n_waves * kWave) return;
     const int r = __builtin_amdgcn_readfirstlane(find_sys(a.lay.sbase, a.n_sys, t & ~(kWave - 1)));
     const SysDesc d = a.sys[r];   // a copy: wave-uniform values in scalar registers
@@ -240,10 +272,19 @@ __global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a) {
 constexpr int kSmallThreads = 1024;
 constexpr size_t kSmallLds = 60 << 10;
 constexpr int kSmallN = 4096;
-__global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a) {
-    extern __shared__ int lds[];
+template <SfKind SF>
+__global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a, SfArgs sf) {
+    extern __shared__ __align__(16) int lds[];
     __shared__ int sh[kSmallThreads / kWave];
     const int r = blockIdx.x;
+    if constexpr (SF != kNoSf) {
+        if (r >= a.n_sys) {
+            const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock);
+            SfRide<SF>::run(sf, (r - a.n_sys) * (kSmallThreads / kBlock) + sub, threadIdx.x % kBlock,
+                            (char *)lds + sub * SfRide<SF>::kLds);
+            return;
+        }
+    }
     const SysDesc &d = a.sys[r];
     const int off = a.lay.off[r], N = a.lay.off[r + 1] - off;
     const int c0 = d.cbase, nc = d.ncx * d.ncy * d.ncz;
@@ -290,14 +331,13 @@ struct RealArgs {
     Layout lay;
     int n_sys, n_waves;         // n_waves: padded real-space waves of all systems
     int nblocks;                // logical blocks (the grid is rounded up to 8 * RBE2D_REAL_CHUNKS chunks)
+    int nbx;                    // ASM: blocks per grid row that sum pairs
     double4 *freal;
-    double2 *dgreal;
     double *rpart;              // per wave
     int nsplit;                 // > 1: block row y handles x-columns y, y + nsplit, ... of every target
     int64_t split_stride;       // targets per split in the partial outputs
     int rsplit_stride;          // waves per split in the partial wave sums
     double4 *freal_s;
-    double2 *dgreal_s;
     double *rpart_s;
 };
 
@@ -463,9 +503,12 @@ struct LaneRings : TargetSums<DG> {
 // pairs each: 63 us instead of 99.  Whole force calls of 24,000 ions with
 // 2 against 1: 93 against 111 and 125 against 160 us; of 64,000: 142 against
 // 139 and 192 against 187.
-template <bool WANT_DG, bool ISO, int SPLIT>
+//
+// ASM: the per-k assembly of the call rides along (blocks from nbx on of each
+// grid row), which on one stream waits for its end otherwise.
+template <bool WANT_DG, bool ISO, int SPLIT, bool ASM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(SPLIT == 2 ? 2 : RBE2D_REAL_WAVES32, 8)))
-void k_real(RealArgs a) {
+void k_real(RealArgs a, AssembleArgs as) {
     constexpr bool FEW = SPLIT == 2;
     constexpr int U = RBE2D_REAL_U32;      // source loads in flight per lane, twice
     constexpr int kRingQ = RBE2D_RING_Q;   // ring entries per lane
@@ -478,7 +521,16 @@ void k_real(RealArgs a) {
     // neighbouring cells share that XCD's L2, and the targets near the walls
     // (cell order is z-slowest; they search extra image families) are shared
     // by all XCDs instead of loading the first and last ones.
-    const int cs = (int)(gridDim.x >> 3) / RBE2D_REAL_CHUNKS;   // blocks per chunk
+    const int nbx = ASM ? a.nbx : (int)gridDim.x;
+    if constexpr (ASM) {
+        if ((int)blockIdx.x >= nbx) {
+            const int b = (((int)blockIdx.x - nbx) * gridDim.z + blockIdx.z) * gridDim.y + blockIdx.y;
+            assemble_wave<WANT_DG>(as, b * (kBlock / kWave) + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave),
+                                   threadIdx.x % kWave);
+            return;
+        }
+    }
+    const int cs = (nbx >> 3) / RBE2D_REAL_CHUNKS;   // blocks per chunk
     const int j = (int)(blockIdx.x >> 3);
     const int lb = ((j / cs) * 8 + (int)(blockIdx.x & 7)) * cs + j % cs;
     if (lb >= a.nblocks) return;
@@ -751,14 +803,11 @@ void k_real(RealArgs a) {
         const int i = a.sidx[t];
         const double qi = me.w * d.pref;
         const double4 fo = make_double4(qi * fx, qi * fy, qi * fz, d.pref * phi);
-        const double2 go = make_double2(d.pref * dpt, d.pref * dpb);
         if (SPLIT) {
             const int64_t o = (int64_t)split * a.split_stride + i;
             a.freal_s[o] = fo;
-            if (WANT_DG) a.dgreal_s[o] = go;
         } else {
             a.freal[i] = fo;
-            if (WANT_DG) a.dgreal[i] = go;
         }
         qphi = qi * phi;
         if (WANT_DG) {
@@ -778,57 +827,8 @@ void k_real(RealArgs a) {
     }
 }
 
-// sum of the split partial outputs, in split order; the loads of five parts
-// at a time are in flight together
-__global__ __launch_bounds__(kBlock) void k_real_combine(RealArgs a, int nparts, int n_total, int want_dg) {
-    const int g = blockIdx.x * kBlock + threadIdx.x;
-    constexpr int B = kMaxRealSplit;
-    if (g < n_total) {
-        double4 f = make_double4(0.0, 0.0, 0.0, 0.0);
-        double2 dg = make_double2(0.0, 0.0);
-        for (int s0 = 0; s0 < nparts; s0 += B) {
-            double4 v[B];
-            double2 u[B];
-#pragma unroll
-            for (int k = 0; k < B; k++) {
-                const int64_t o = (int64_t)min(s0 + k, nparts - 1) * a.split_stride + g;
-                v[k] = a.freal_s[o];
-                if (want_dg) u[k] = a.dgreal_s[o];
-            }
-#pragma unroll
-            for (int k = 0; k < B; k++)
-                if (s0 + k < nparts) {
-                    f.x += v[k].x; f.y += v[k].y; f.z += v[k].z; f.w += v[k].w;
-                    if (want_dg) { dg.x += u[k].x; dg.y += u[k].y; }
-                }
-        }
-        a.freal[g] = f;
-        if (want_dg) a.dgreal[g] = dg;
-    }
-    if (g < a.n_waves) {
-        double w[3] = {0.0, 0.0, 0.0};
-        for (int s0 = 0; s0 < nparts; s0 += B) {
-            double v[B][3];
-#pragma unroll
-            for (int k = 0; k < B; k++)
-                for (int c = 0; c < 3; c++)
-                    v[k][c] = a.rpart_s[3 * ((int64_t)min(s0 + k, nparts - 1) * a.rsplit_stride + g) + c];
-#pragma unroll
-            for (int k = 0; k < B; k++)
-                if (s0 + k < nparts)
-                    for (int c = 0; c < 3; c++) w[c] += v[k][c];
-        }
-        for (int c = 0; c < 3; c++) a.rpart[3 * g + c] = w[c];
-    }
-}
-
-hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s) {
-    hipError_t e = launch_cells(h, pos, q, s);
-    return e == hipSuccess ? launch_pairs(h, want_dg, s) : e;
-}
-
-hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s) {
-    if (h->n_total == 0) return hipSuccess;
+template <SfKind SF>
+static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s) {
     CellArgs c;
     c.pos = pos; c.q = q; c.sys = h->w.sys; c.lay = h->w.lay; c.n_sys = h->n_sys;
     c.n_total = (int)h->n_total; c.ncells = h->total_cells;
@@ -845,9 +845,13 @@ hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStr
     // MD pass that moved the particles may have counted them already
     if (!h->cells_counted) hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, s, c);
     h->cells_counted = false;
+    const SfArgs sf = sf_args(h);
+    const int n_sf = SF == kNoSf ? 0 : SfRide<SF>::parts(sf);
     const size_t lds = (h->max_cells + 1 + (size_t)h->max_n) * sizeof(int);
     if (h->max_n <= kSmallN && lds <= kSmallLds) {
-        hipLaunchKernelGGL(k_cells_small, dim3(h->n_sys), dim3(kSmallThreads), lds, s, c);
+        constexpr int per = kSmallThreads / kBlock;
+        hipLaunchKernelGGL(k_cells_small<SF>, dim3(h->n_sys + (n_sf + per - 1) / per), dim3(kSmallThreads),
+                           std::max<size_t>(lds, per * SfRide<SF>::kLds), s, c, sf);
         prof_end(h, 3, s);
         return hipGetLastError();
     }
@@ -856,19 +860,28 @@ hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStr
     hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf,
                        h->w.start);
     hipLaunchKernelGGL(k_cell_scatter, dim3(nb), dim3(kBlock), 0, s, c);
-    hipLaunchKernelGGL(k_cell_rank, dim3((h->n_swaves * kWave + kBlock - 1) / kBlock), dim3(kBlock), 0, s, c);
+    hipLaunchKernelGGL(k_cell_rank<SF>, dim3(n_sf + (h->n_swaves * kWave + kBlock - 1) / kBlock), dim3(kBlock), 0, s, c,
+                       sf, n_sf);
     prof_end(h, 3, s);
     return hipGetLastError();
 }
 
-hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
-    if (h->n_total == 0) return hipSuccess;
-    if (h->precision != RBE2D_PREC_FP32_PHASE) return launch_tile_pairs(h, want_dg, s);
+hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s) {
+    return h->n_total > 0 ? build_cells<kNoSf>(h, pos, q, s) : hipSuccess;
+}
+
+// The pair sums; returns whether the assembly rode along
+static bool launch_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipStream_t s) {
+    if (h->precision != RBE2D_PREC_FP32_PHASE) {
+        h->real_parts = 1;
+        launch_tile_pairs(h, want_dg, as, s);
+        return as != nullptr;
+    }
     RealArgs r;
     r.src = h->w.sorted; r.src16 = h->w.src16; r.sidx = h->w.sidx; r.scell = h->w.scell; r.start = h->w.start;
     r.sys = h->w.sys; r.fam = h->w.fam; r.lay = h->w.lay; r.n_sys = h->n_sys; r.n_waves = h->n_swaves;
-    r.freal = h->w.freal; r.dgreal = h->w.dgreal; r.rpart = h->w.rpart;
-    r.freal_s = h->w.freal_s; r.dgreal_s = h->w.dgreal_s; r.rpart_s = h->w.rpart_s;
+    r.freal = h->w.freal; r.rpart = h->w.rpart;
+    r.freal_s = h->w.freal_s; r.rpart_s = h->w.rpart_s;
     r.split_stride = h->n_total;
     r.rsplit_stride = (int)(h->cap_sorted / kWave);
     // too few targets to fill the chip: split each target's x-columns over
@@ -883,35 +896,50 @@ hipError_t launch_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
     const int nbs = (h->n_swaves * kWave + kBlock - 1) / kBlock;
     r.nblocks = nbs;
     const int nch = 8 * RBE2D_REAL_CHUNKS;
-    const int nbc = (nbs + nch - 1) / nch * nch;
+    r.nbx = (nbs + nch - 1) / nch * nch;
     // few targets: the image families in two more layers of blocks
     int nfam = 0;
     for (const SysHost &sh : h->sys) nfam = std::max(nfam, sh.d.nfam);
     const int split = r.nsplit == 1 ? 0 : h->n_total > kFamilySplitMax ? 1 : 2;
     const int layers = split == 2 ? std::min(kMaxFamilySplit, 1 + nfam) : 1;
-    const dim3 grid(nbc, r.nsplit, layers);
+    h->real_parts = r.nsplit * layers;
+    const bool ride = as && split == 2;
+    const AssembleArgs asm_args = ride ? *as : AssembleArgs();
+    const int rows = r.nsplit * layers, per_row = rows * (kBlock / kWave);
+    const dim3 grid(r.nbx + (ride ? (as->items() + per_row - 1) / per_row : 0), r.nsplit, layers);
     prof_begin(h, 4, s);
-#define RBE2D_REAL(DG, ISO_, S) \
-    if (want_dg == DG && h->iso == ISO_ && split == S) \
-        hipLaunchKernelGGL((k_real<DG, ISO_, S>), grid, dim3(kBlock), 0, s, r);
-#define RBE2D_REAL_FORMS(S) \
-    RBE2D_REAL(false, false, S) RBE2D_REAL(true, false, S) RBE2D_REAL(false, true, S) RBE2D_REAL(true, true, S)
-    RBE2D_REAL_FORMS(0) RBE2D_REAL_FORMS(1) RBE2D_REAL_FORMS(2)
+#define RBE2D_REAL(DG, ISO_, S, A) \
+    if (want_dg == DG && h->iso == ISO_ && split == S && ride == A) \
+        hipLaunchKernelGGL((k_real<DG, ISO_, S, A>), grid, dim3(kBlock), 0, s, r, asm_args);
+#define RBE2D_REAL_FORMS(S, A) \
+    RBE2D_REAL(false, false, S, A) RBE2D_REAL(true, false, S, A) RBE2D_REAL(false, true, S, A) RBE2D_REAL(true, true, S, A)
+    RBE2D_REAL_FORMS(0, false) RBE2D_REAL_FORMS(1, false) RBE2D_REAL_FORMS(2, false) RBE2D_REAL_FORMS(2, true)
 #undef RBE2D_REAL_FORMS
 #undef RBE2D_REAL
-    if (r.nsplit > 1) {
-        const int64_t n = std::max<int64_t>(h->n_total, h->n_swaves);
-        hipLaunchKernelGGL(k_real_combine, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, r,
-                           r.nsplit * layers, (int)h->n_total, (int)want_dg);
-    }
     prof_end(h, 4, s);
-    return hipGetLastError();
+    return ride;
+}
+
+hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
+                       const RideAlong *ride) {
+    if (h->n_total == 0) return hipSuccess;
+    const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
+    hipError_t e = !ride ? build_cells<kNoSf>(h, pos, q, s)
+                         : fp32 ? build_cells<kSf32>(h, pos, q, s) : build_cells<kSf64>(h, pos, q, s);
+    if (e != hipSuccess) return e;
+    if (ride) {
+        const AssembleArgs as = assemble_args(h, true, ride->step);
+        if (!launch_pairs(h, want_dg, &as, s)) e = launch_assemble(h, as, want_dg, s);
+    } else {
+        launch_pairs(h, want_dg, nullptr, s);
+    }
+    return e == hipSuccess ? hipGetLastError() : e;
 }
 
 // F += F_real (the pair kernel's per-particle output), and in MD steps the
 // closing half kick v += dt/2 F with the completed force
 // (blocks from n_blocks on: the systems' energies)
-__global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, const double4 *freal, double *F, double *vel,
+__global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, RealParts real, double *F, double *vel,
                                                      double half_dt, int n_blocks, EnergyArgs en) {
     __shared__ double sh[kBlock / kWave];
     if ((int)blockIdx.x >= n_blocks) {
@@ -920,7 +948,7 @@ __global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, const double4 *f
     }
     const int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (g >= n) return;
-    const double4 fr = freal[g];
+    const double4 fr = real.sum(g);
     const double add[3] = {fr.x, fr.y, fr.z};
     for (int c = 0; c < 3; c++) {
         const double f = F[3 * g + c] + add[c];
@@ -934,7 +962,7 @@ hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt,
     if (h->n_total == 0) return hipSuccess;
     prof_begin(h, 10, s);
     const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_add_real, dim3(nb + (energy ? h->n_sys : 0)), dim3(kBlock), 0, s, h->n_total, h->w.freal, F,
+    hipLaunchKernelGGL(k_add_real, dim3(nb + (energy ? h->n_sys : 0)), dim3(kBlock), 0, s, h->n_total, real_parts(h), F,
                        vel, half_dt, nb, energy_args(h, energy, energy_flags, nullptr, nullptr));
     prof_end(h, 10, s);
     return hipGetLastError();

@@ -6,6 +6,7 @@
 #include "devmath.h"
 #include "erfcx_fit.h"
 #include "exp2_fit.h"
+#include "kspace_dev.h"
 #include "rbe2d_internal.h"
 
 namespace rbe2d {
@@ -59,8 +60,8 @@ struct TileArgs {
     int n_sys, n_waves;         // n_waves: tiles of all systems
     int wpt;                    // waves per tile
     int nblocks;                // logical blocks (the grid is rounded up to 8 * kTileChunks chunks)
+    int nbx;                    // ASM: blocks that sum pairs
     double4 *freal;
-    double2 *dgreal;
     double *rpart;              // per tile
     // short-range forces
     MdExtra mx;
@@ -72,7 +73,8 @@ struct TileArgs {
 constexpr int kTileChunks = 8;      // contiguous tile ranges per XCD
 constexpr int kMaxRuns = 80;        // runs per batch of the candidate list
 constexpr int kRunGroup = 16;       // columns looked up together; up to 3 runs each
-constexpr int kMaxTileWaves = 8;    // waves per tile (and block)
+constexpr int kMaxTileWaves = 12;   // waves per tile (and block)
+constexpr int kTileWaves[kTileSplits] = {1, 2, 4, kMaxTileWaves};
 
 // LDS written by other lanes of the same wave: the wave's LDS operations are
 // executed in order, this keeps the compiler from reordering them
@@ -290,12 +292,22 @@ struct TileLds {
 };
 
 // DG: also the gamma derivatives of the potential.
-template <TileKind KIND, bool DG>
+// ASM: the per-k assembly of the call rides along (blocks from nbx on), which on
+// one stream waits for the pair sums otherwise.
+template <TileKind KIND, bool DG, bool ASM>
 __global__ __launch_bounds__(kWave * kMaxTileWaves) __attribute__((amdgpu_waves_per_eu(KIND == kErfc ? 3 : 4, 8)))
-void k_tile(TileArgs a) {
+void k_tile(TileArgs a, AssembleArgs as) {
     using Lds = TileLds<DG>;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ double coef64[KIND == kErfc ? RBE2D_ERFCX64_DEG : 1];
+    const int nbx = ASM ? a.nbx : (int)gridDim.x;
+    if constexpr (ASM) {
+        if ((int)blockIdx.x >= nbx) {
+            assemble_wave<DG>(as, ((int)blockIdx.x - nbx) * (blockDim.x / kWave) +
+                                      __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), threadIdx.x % kWave);
+            return;
+        }
+    }
     if (KIND == kErfc) {
         if (threadIdx.x < RBE2D_ERFCX64_DEG) coef64[threadIdx.x] = rbe2d_erfcx64_a[threadIdx.x];
         __syncthreads();
@@ -305,7 +317,7 @@ void k_tile(TileArgs a) {
     // ranges of tiles (range k of XCD x is range 8k + x), so neighbouring
     // cells share that XCD's L2, and the tiles near the walls (cell order is
     // z-slowest; they have image sources too) are shared by all XCDs.
-    const int cs = (int)(gridDim.x >> 3) / kTileChunks;   // blocks per range
+    const int cs = (nbx >> 3) / kTileChunks;   // blocks per range
     const int jblk = (int)(blockIdx.x >> 3);
     const int lb = ((jblk / cs) * 8 + (int)(blockIdx.x & 7)) * cs + jblk % cs;
     if (lb >= a.nblocks) return;
@@ -560,7 +572,6 @@ void k_tile(TileArgs a) {
             const int i = a.sidx[t];
             const double qi = me.w * d.pref;
             a.freal[i] = make_double4(qi * fx, qi * fy, qi * fz, d.pref * phi);
-            if (DG) a.dgreal[i] = make_double2(d.pref * dpt, d.pref * dpb);
             qphi = qi * phi;
             if (DG) { qdt = qi * dpt; qdb = qi * dpb; }
         }
@@ -579,44 +590,52 @@ static TileArgs tile_args(rbe2d_ctx *h) {
     TileArgs r{};
     r.src = h->w.sorted; r.sidx = h->w.sidx; r.start = h->w.start;
     r.sys = h->w.sys; r.fam = h->w.fam; r.lay = h->w.lay; r.n_sys = h->n_sys; r.n_waves = h->n_swaves;
-    r.freal = h->w.freal; r.dgreal = h->w.dgreal; r.rpart = h->w.rpart; r.spart = h->w.spart;
-    // too few tiles to fill the chip's 4096 wave slots: several waves share
-    // one, up to 8 (a block)
-    int wpt = 1;
-    while (wpt < kMaxTileWaves && (int64_t)h->n_swaves * wpt < 2048) wpt *= 2;
+    r.freal = h->w.freal; r.rpart = h->w.rpart; r.spart = h->w.spart;
+    // too few tiles to fill the chip: several waves share one, 12 or 4 where all
+    // blocks are then in flight at once (3 waves per SIMD of 256 CUs).  Force
+    // calls: 8000 ions, 12 waves 67 us, 8 waves 69; 20000 ions, 4 waves 102, 8
+    // waves 112, 6 waves 117 (a block of 6 loads two of the four SIMDs twice);
+    // 64000 ions, 2 waves 160, 4 waves 166; 120000 ions, 2 waves 237, 1 wave 272.
+    int n = h->n_swaves <= 256 ? 3 : h->n_swaves <= 768 ? 2 : h->n_swaves <= 2048 ? 1 : 0;
     if (h->precision != RBE2D_PREC_FP32_PHASE) {   // (FP32 handles tune the split of their own pair kernel)
-        if (h->force_rsplit) wpt = 1 << (h->force_rsplit - 1);
-        else if (h->tuned_now && h->tune.rsplit) wpt = 1 << (h->tune.rsplit - 1);
+        if (h->force_rsplit) n = h->force_rsplit - 1;
+        else if (h->tuned_now && h->tune.rsplit) n = h->tune.rsplit - 1;
     }
-    r.wpt = std::min(wpt, kMaxTileWaves);
+    r.wpt = kTileWaves[std::min(n, kTileSplits - 1)];
     return r;
 }
 
 template <TileKind KIND, bool DG>
-static void launch_tile(TileArgs r, hipStream_t s) {
+static void launch_tile(TileArgs r, const AssembleArgs *as, hipStream_t s) {
     const int waves = std::max(4, r.wpt);            // per block
     const int per_block = waves / r.wpt;
     r.nblocks = (r.n_waves + per_block - 1) / per_block;
     const int nch = 8 * kTileChunks;
-    const int nb = (r.nblocks + nch - 1) / nch * nch;
+    r.nbx = (r.nblocks + nch - 1) / nch * nch;
     const int bytes = waves * TileLds<DG>::kWaveBytes;
-    hipLaunchKernelGGL((k_tile<KIND, DG>), dim3(nb), dim3(waves * kWave), bytes, s, r);
+    if constexpr (KIND == kErfc) {
+        if (as) {
+            const int na = (as->items() + waves - 1) / waves;
+            hipLaunchKernelGGL((k_tile<KIND, DG, true>), dim3(r.nbx + na), dim3(waves * kWave), bytes, s, r, *as);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_tile<KIND, DG, false>), dim3(r.nbx), dim3(waves * kWave), bytes, s, r, AssembleArgs());
 }
 
-hipError_t launch_tile_pairs(rbe2d_ctx *h, bool want_dg, hipStream_t s) {
+void launch_tile_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipStream_t s) {
     const TileArgs r = tile_args(h);
     prof_begin(h, 4, s);
-    if (want_dg) launch_tile<kErfc, true>(r, s);
-    else launch_tile<kErfc, false>(r, s);
+    if (want_dg) launch_tile<kErfc, true>(r, as, s);
+    else launch_tile<kErfc, false>(r, as, s);
     prof_end(h, 4, s);
-    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // Short-range forces of the MD (purely repulsive shifted-truncated LJ between
 // ions and against the walls): the tiles of the pair sum with the LJ cutoff
 // and no images, in FP64.  Forces are added to F[stride * i + 0..2] (the
-// caller's N x 3 forces, or the pair kernel's per-particle output); per-tile
+// caller's N x 3 forces, or a part of the pair kernel's per-particle output); per-tile
 // energy sums go to spart.
 // ---------------------------------------------------------------------------
 
@@ -643,9 +662,9 @@ hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *ener
         TileArgs a = tile_args(h);
         a.mx = mx;
         // into_real: add to the pair kernel's per-particle output (x, y, z, phi)
-        a.F = into_real ? (double *)h->w.freal : F;
+        a.F = into_real ? (double *)real_parts(h).f : F;
         a.stride = into_real ? 4 : 3;
-        launch_tile<kWca, false>(a, s);
+        launch_tile<kWca, false>(a, nullptr, s);
     }
     if (energy) {
         if (h->n_total > 0 && mx.short_on()) {
