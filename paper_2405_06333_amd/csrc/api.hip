@@ -402,6 +402,7 @@ void free_all(rbe2d_ctx *h) {
     if (h->lay_ev) (void)hipEventDestroy(h->lay_ev);
     if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
     if (h->join_ev) (void)hipEventDestroy(h->join_ev);
+    if (h->cells_ev) (void)hipEventDestroy(h->cells_ev);
     if (h->side) (void)hipStreamDestroy(h->side);
 }
 
@@ -443,7 +444,7 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     // the FP32 records get one wave of padding: the pair kernel reads the first
     // record of an empty run, which may start at the end of the array
     if (fp32) { A(&w.src16, h->cap_sorted + kWave); A(&w.scell, h->cap_sorted); }
-    A(&w.freal, nc);
+    A(&w.freal, nc); A(&w.fshort, h->one_stream ? 0 : nc);   // (the call without a handle has no MD)
     A(&w.rpart, 3 * (h->cap_sorted / kWave));
     // FP32 pair kernel: the split is only used when there are too few targets
     // to fill the chip
@@ -539,6 +540,7 @@ rbe2d_status create_handle(int n, const rbe2d_params *ps, bool batch, rbe2d_hand
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->fork_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&h->join_ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&h->cells_ev, hipEventDisableTiming);
     if (e != hipSuccess) {
         const bool oom = e == hipErrorOutOfMemory;
         free_all(h);
@@ -712,7 +714,9 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
                             bool accumulate, const ForceJob &job, hipStream_t s) {
     const bool kside = (parts & (RBE2D_KSPACE | RBE2D_IBC)) != 0, real = (parts & RBE2D_REAL) != 0;
     const bool sc_asm = (parts & RBE2D_KSPACE) != 0;
-    const bool two = kside && real && h->n_total > 0 && !on_one_stream(h, false);
+    // (MD steps, captured or not: two streams; captured, 2000 ions take 63 us
+    // per Langevin step in FP64 against 74, 75 against 77 in FP32)
+    const bool two = kside && real && h->n_total > 0 && (job.prepared ? !h->one_stream : !on_one_stream(h, false));
     if (kside && !job.prepared) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
     hipStream_t ks = two ? h->side : s;
     if (two) {
@@ -724,18 +728,24 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     const bool ride = rides_along(h, sc_asm && real && !two);
     RideAlong ra;
     ra.step = job.step;
-    if (real) {
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr), "real-space launch");
-        if (job.mx) RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, s, true), "short-range launch");
-    }
+    // (an MD step: two streams)  the short-range kernel needs the cell list
+    // only: on the side stream after the k-space chain, beside the pair kernel
+    const bool shortr = two && job.mx;
+    if (real)
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, shortr ? h->cells_ev : nullptr),
+                  "real-space launch");
     if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");
     ForceExtra x;
     if (!two) {
-        x.vel = job.vel; x.half_dt = 0.5 * job.dt; x.energy = job.energy; x.err_out = job.err_out;
+        x.energy = job.energy; x.err_out = job.err_out;
     }
     RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, two ? parts & ~(uint32_t)RBE2D_REAL : parts, accumulate, false,
                                real && !two, nullptr, ks, x), "force launch");
     if (two) {
+        if (shortr) {
+            RBE2D_TRY(h, hipStreamWaitEvent(ks, h->cells_ev, 0), "stream wait");
+            RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, ks), "short-range launch");
+        }
         rbe2d_status st = stream_wait(h, s, ks, h->join_ev);
         if (st) return st;
         RBE2D_TRY(h, launch_add_real(h, F, job.vel, 0.5 * job.dt, s, job.energy, parts), "real-space add");
@@ -810,26 +820,29 @@ rbe2d_status md_step(rbe2d_ctx *h, double *pos, double *vel, const double *q, do
 // the current positions (whose k-set is drawn, with its k-vector table, and
 // whose k-space particle records and IBC block sums the preceding MD pass
 // wrote).  The k-space chain (structure factors, assembly with the IBC
-// scalars, force scatter) runs on the side stream, real space on s.  After
+// scalars, force scatter) runs on the side stream, real space on s (also for
+// small systems: 500 ions 55 us per step FP32, 63 on one stream as in
+// compute_forces; 16000 ions 92 and 104).  After
 // the forces, either the closing half kick (last step of the run) or one
 // pass with the closing and next opening half kicks, the next drift, the next
 // records and the next k-set (device step counter: advanced by the assembly).
 rbe2d_status vv_unit(rbe2d_ctx *h, double *pos, double *vel, const double *q, double *F, double dt, double zlo,
                      double zhi_from_top, uint64_t seed, int64_t step, bool dev_step, bool last, hipStream_t s) {
+    long long *counter = dev_step ? h->w.step : nullptr;
     hipStream_t ks = h->side;
     rbe2d_status st = stream_wait(h, ks, s, h->fork_ev);
     if (st) return st;
     // real space first: its latency-bound cell list then starts ahead of the
     // structure factors (also in a captured graph, whose nodes follow this order)
     RBE2D_TRY(h, launch_real(h, pos, q, false, s), "real-space launch");
-    RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, dev_step ? h->w.step : nullptr), "structure-factor launch");
+    RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, counter), "structure-factor launch");
     RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, RBE2D_KSPACE | RBE2D_IBC, false, false, false, nullptr, ks),
               "force launch");
     st = stream_wait(h, s, ks, h->join_ev);
     if (st) return st;
     if (!last)
         RBE2D_TRY(h, launch_prep_md(h, 2, pos, vel, F, q, dt, zlo, zhi_from_top, nullptr, seed,
-                                    (uint64_t)(step + 1) * (uint64_t)h->n_sys, dev_step ? h->w.step : nullptr, s),
+                                    (uint64_t)(step + 1) * (uint64_t)h->n_sys, counter, s),
                   "md leapfrog");
     else
         RBE2D_TRY(h, launch_add_real(h, F, vel, 0.5 * dt, s), "real-space add");

@@ -516,6 +516,10 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
                 const double4 v = a.real.f[p * a.real.stride + g];
                 real.x += v.x; real.y += v.y; real.z += v.z; real.w += v.w;
             }
+        if (a.add_real && a.real.more && wid == 0) {
+            const double4 v = a.real.more[g];
+            real.x += v.x; real.y += v.y; real.z += v.z;
+        }
         if (a.do_kspace)
             for (int k = wid; k < a.split; k += nw)
                 sum(r, ii, k * a.k_per_split, min(a.P, (k + 1) * a.k_per_split), f);

@@ -151,6 +151,7 @@ struct Workspace {
     // over several blocks (small N, FP32): [split][split_cap] / [split][waves]
     double4 *freal_s = nullptr;
     double *rpart_s = nullptr;
+    double4 *fshort = nullptr;  // per caller particle: short-range force of an MD step
     double *spart = nullptr;    // per real-space wave: short-range pair and wall energies
     int *err = nullptr;         // device error word
     long long *step = nullptr;  // device MD step counter (graph replays)
@@ -192,6 +193,7 @@ struct rbe2d_ctx {
     int64_t split_cap = 0;           // targets per split of the partial real-space outputs
     int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most
     bool one_stream = false;         // run the k-space chain on the caller's stream too (no side stream)
+    bool short_part = false;         // fshort belongs to the forces of this cell list
     int real_parts = 1;              // parts of the last pair sums (1: freal, rpart; else freal_s, rpart_s)
     bool cells_counted = false;      // the preparation counted the particles per cell (next build skips it)
     bool records_moved = false;      // ... in an MD pass, whose particle records the build reads
@@ -213,7 +215,7 @@ struct rbe2d_ctx {
     // the k-space chain runs on a second stream beside the real-space chain
     // (default priority), forked from and joined back to the caller's stream
     hipStream_t side = nullptr;
-    hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+    hipEvent_t fork_ev = nullptr, join_ev = nullptr, cells_ev = nullptr;
     bool kev_pending = false;
     // launch parameters: tuned for one particle layout by rbe2d_autotune, else
     // heuristic; force_* override both while the tuner times candidates
@@ -242,10 +244,10 @@ struct rbe2d_ctx {
 
 namespace rbe2d {
 
-// Per-particle outputs of the pair kernel, in parts `stride` apart; whoever
-// needs them adds the parts, in their order
+// Per-particle outputs of the pair kernel, in parts `stride` apart, and of the
+// short-range kernel (or null); whoever needs them adds the parts, in their order
 struct RealParts {
-    const double4 *f;
+    const double4 *f, *more;
     int n;
     int64_t stride;
     template <int B = kMaxRealSplit>   // loads in flight
@@ -259,11 +261,14 @@ struct RealParts {
             for (int k = 0; k < B; k++)
                 if (p0 + k < n) { t.x += v[k].x; t.y += v[k].y; t.z += v[k].z; t.w += v[k].w; }
         }
+        if (more) { const double4 v = more[g]; t.x += v.x; t.y += v.y; t.z += v.z; }
         return t;
     }
 };
 inline RealParts real_parts(const rbe2d_ctx *h) {
-    return h->real_parts > 1 ? RealParts{h->w.freal_s, h->real_parts, h->n_total} : RealParts{h->w.freal, 1, 0};
+    const double4 *more = h->short_part ? h->w.fshort : nullptr;
+    return h->real_parts > 1 ? RealParts{h->w.freal_s, more, h->real_parts, h->n_total}
+                             : RealParts{h->w.freal, more, 1, 0};
 }
 
 // kernel launchers (return hipSuccess or the launch error); all systems at once
@@ -297,17 +302,17 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
 struct RideAlong {
     long long *step = nullptr;   // as in launch_kcoef_sf
 };
+// after_cells: recorded between the two when set
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
-                       const RideAlong *ride = nullptr);
+                       const RideAlong *ride = nullptr, hipEvent_t after_cells = nullptr);
 hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);   // the cell list alone
 // F += F_real (and v += half_dt F); also the energies when energy is set
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s,
                            double *energy = nullptr, uint32_t energy_flags = 0);
 void launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s);
-// short-range forces added to F, or with into_real to the pair kernel's
-// per-particle output (then folded into F with the real-space forces)
-hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s,
-                        bool into_real = false);
+// short-range forces added to F, or without F kept beside the pair kernel's
+// output (then part of the real-space forces of this cell list)
+hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s);
 hipError_t launch_energy(rbe2d_ctx *h, double *energy, uint32_t flags, const double *gE, double *dEdgamma,
                          hipStream_t s);
 hipError_t launch_sample(rbe2d_ctx *h, uint64_t seed, uint64_t stream_id, const long long *dev_step,

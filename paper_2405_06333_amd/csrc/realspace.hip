@@ -840,6 +840,7 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     c.p32 = records && fp32 ? h->w.p32 : nullptr;
     c.p64 = records && !fp32 ? h->w.p64 : nullptr;
     const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
+    h->short_part = false;
     prof_begin(h, 3, s);
     // the counts start at zero (the previous build's scan cleared them); the
     // MD pass that moved the particles may have counted them already
@@ -921,11 +922,12 @@ static bool launch_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hip
 }
 
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
-                       const RideAlong *ride) {
+                       const RideAlong *ride, hipEvent_t after_cells) {
     if (h->n_total == 0) return hipSuccess;
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
     hipError_t e = !ride ? build_cells<kNoSf>(h, pos, q, s)
                          : fp32 ? build_cells<kSf32>(h, pos, q, s) : build_cells<kSf64>(h, pos, q, s);
+    if (e == hipSuccess && after_cells) e = hipEventRecord(after_cells, s);
     if (e != hipSuccess) return e;
     if (ride) {
         const AssembleArgs as = assemble_args(h, true, ride->step);

@@ -65,8 +65,7 @@ struct TileArgs {
     double *rpart;              // per tile
     // short-range forces
     MdExtra mx;
-    double *F;
-    int stride;
+    double *F;                  // added to when set, else written to freal
     double *spart;              // per tile
 };
 
@@ -295,7 +294,7 @@ struct TileLds {
 // ASM: the per-k assembly of the call rides along (blocks from nbx on), which on
 // one stream waits for the pair sums otherwise.
 template <TileKind KIND, bool DG, bool ASM>
-__global__ __launch_bounds__(kWave * kMaxTileWaves) __attribute__((amdgpu_waves_per_eu(KIND == kErfc ? 3 : 4, 8)))
+__global__ __launch_bounds__(kWave * kMaxTileWaves) __attribute__((amdgpu_waves_per_eu(3, 8)))
 void k_tile(TileArgs a, AssembleArgs as) {
     using Lds = TileLds<DG>;
     extern __shared__ __align__(16) unsigned char lds[];
@@ -333,7 +332,8 @@ void k_tile(TileArgs a, AssembleArgs as) {
     if (active) me = a.src[t];
     double fx = 0, fy = 0, fz = 0, phi = 0, dpt = 0, dpb = 0;
     unsigned char *wl = lds + wid * Lds::kWaveBytes;
-    if (__ballot(active) != 0 && (KIND != kWca || a.mx.eps != 0.0)) {
+    // all pairs of the targets `on` (the sources are the same for any of them)
+    auto pass = [&](bool on) {
         double4 *ring = reinterpret_cast<double4 *>(wl);
         double2 *ringdg = reinterpret_cast<double2 *>(wl + Lds::kDg);
         half8 *tgt = reinterpret_cast<half8 *>(wl + Lds::kTargets);   // entry kWave: zeros
@@ -343,9 +343,9 @@ void k_tile(TileArgs a, AssembleArgs as) {
         const float Lx = (float)d.Lx, Ly = (float)d.Ly;
         const float marg = 1e-5f * rc + 1e-6f * (fmaxf(Lx, Ly) + 4.0f * (float)d.H + rc);
         const float zb = fminf(fmaxf((float)me.z, 0.0f), (float)d.H);
-        const float x0 = wave_fmin((float)me.x, active), x1 = wave_fmax((float)me.x, active);
-        const float y0 = wave_fmin((float)me.y, active), y1 = wave_fmax((float)me.y, active);
-        const float z0 = wave_fmin(zb, active), z1 = wave_fmax(zb, active);
+        const float x0 = wave_fmin((float)me.x, on), x1 = wave_fmax((float)me.x, on);
+        const float y0 = wave_fmin((float)me.y, on), y1 = wave_fmax((float)me.y, on);
+        const float z0 = wave_fmin(zb, on), z1 = wave_fmax(zb, on);
         const float xc = 0.5f * (x0 + x1), yc = 0.5f * (y0 + y1), zc = 0.5f * (z0 + z1);
         RunFinder<DG> rf{d, fams, a.start + d.cbase, runs, dgw, x0, x1, y0, y1, z0, z1, rc + marg, marg,
                            xc, yc, zc, KIND == kWca ? 0 : d.nfam, a.lay.sbase[r] - a.lay.off[r], lane, 0, 0};
@@ -368,7 +368,7 @@ void k_tile(TileArgs a, AssembleArgs as) {
             const float T = (float)hx * (float)hx + (float)hy * (float)hy + (float)hz * (float)hz - thr;
             const _Float16 th = (_Float16)T, tl = (_Float16)(T - (float)th), one = (_Float16)1.0f, two = (_Float16)-2.0f;
             half8 tv = {two * hx, two * hy, two * hz, one, one, th, tl, (_Float16)0.0f};
-            if (!active) tv = half8{0, 0, 0, one, one, (_Float16)30000.0f, 0, 0};
+            if (!on) tv = half8{0, 0, 0, one, one, (_Float16)30000.0f, 0, 0};
             tgt[lane] = tv;
             if (lane == 0) {
                 tgt[kWave] = half8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -474,11 +474,19 @@ void k_tile(TileArgs a, AssembleArgs as) {
             // (the tile's own targets are taken by the first chunk)
             if (!diag && rn.code == kSelfCode && (uint32_t)(src_j - t0) < (uint32_t)kWave) src_ok = false;
             const bool mirror = rn.zm < 0.0f;
-            const float px = (float)rec.x + rn.shx, py = (float)rec.y + rn.shy, pz = fmaf((float)rec.z, rn.zm, rn.za);
+            float px = (float)rec.x + rn.shx, py = (float)rec.y + rn.shy, pz = fmaf((float)rec.z, rn.zm, rn.za);
             const double xs = (double)copy_x(rn.code) * d.Lx, ys = (double)copy_y(rn.code) * d.Ly;
             ring[e] = make_double4(rec.x + xs, rec.y + ys, (mirror ? -rec.z : rec.z) + rn.c, rn.w * rec.w);
             if (DG) ringdg[e] = make_double2(dgw[ri].x * rec.w, dgw[ri].y * rec.w);
-            const _Float16 hx = (_Float16)(px * sg), hy = (_Float16)(py * sg), hz = (_Float16)(pz * sg);
+            px *= sg; py *= sg; pz *= sg;
+            if constexpr (KIND == kWca) {
+                // the tile's own members of another pass may lie anywhere: kept
+                // finite, and as far out of reach
+                px = __builtin_amdgcn_fmed3f(px, -100.0f, 100.0f);
+                py = __builtin_amdgcn_fmed3f(py, -100.0f, 100.0f);
+                pz = __builtin_amdgcn_fmed3f(pz, -100.0f, 100.0f);
+            }
+            const _Float16 hx = (_Float16)px, hy = (_Float16)py, hz = (_Float16)pz;
             const float S = (float)hx * (float)hx + (float)hy * (float)hy + (float)hz * (float)hz;
             const _Float16 sh = (_Float16)(src_ok ? S : 30000.0f), one = (_Float16)1.0f;
             const _Float16 sl = (_Float16)(src_ok ? S - (float)sh : 0.0f);
@@ -533,6 +541,21 @@ void k_tile(TileArgs a, AssembleArgs as) {
             if (last) break;
             nbase ^= kWave;
         }
+    };
+    if constexpr (KIND == kErfc) {
+        if (__ballot(active) != 0) pass(active);
+    } else if (a.mx.eps != 0.0) {
+        // without the serpentine numbering a tile that runs over the end of a
+        // layer spans all of it: one pass per layer then (21,000 ions in a thin
+        // slab: 18 us instead of 102)
+        const int layer = d.snake ? 0 : min(d.ncz - 1, max(0, (int)(me.z / d.hz)));
+        for (uint64_t left = __ballot(active); left != 0;) {
+            const int l0 = __builtin_amdgcn_readlane(layer, (int)__builtin_ctzll(left));
+            const bool on = active && layer == l0;
+            left &= ~__ballot(on);
+            pass(on);
+            wave_lds_fence();
+        }
     }
     if (a.wpt > 1) {
         // sums of the tile's waves, in wave order
@@ -560,8 +583,12 @@ void k_tile(TileArgs a, AssembleArgs as) {
                 if (hb > 0.0 && hb < a.mx.hcut) { ew += lj_rep(a.mx.sigw2 / (hb * hb), a.mx.epsw, &rfo); fz += rfo / hb; }
                 if (ht > 0.0 && ht < a.mx.hcut) { ew += lj_rep(a.mx.sigw2 / (ht * ht), a.mx.epsw, &rfo); fz -= rfo / ht; }
             }
-            double *o = a.F + (int64_t)a.stride * a.sidx[t];
-            o[0] += fx; o[1] += fy; o[2] += fz;
+            if (a.F) {
+                double *o = a.F + (int64_t)3 * a.sidx[t];
+                o[0] += fx; o[1] += fy; o[2] += fz;
+            } else {
+                a.freal[a.sidx[t]] = make_double4(fx, fy, fz, 0.0);
+            }
         }
         ep = wave_sum(ep);
         ew = wave_sum(ew);
@@ -634,9 +661,9 @@ void launch_tile_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipSt
 // ---------------------------------------------------------------------------
 // Short-range forces of the MD (purely repulsive shifted-truncated LJ between
 // ions and against the walls): the tiles of the pair sum with the LJ cutoff
-// and no images, in FP64.  Forces are added to F[stride * i + 0..2] (the
-// caller's N x 3 forces, or a part of the pair kernel's per-particle output); per-tile
-// energy sums go to spart.
+// and no images, in FP64.  Forces are added to the caller's N x 3 forces, or in
+// an MD step kept as one more part of the real-space forces: the step runs
+// this launch beside the pair kernel's.  Per-tile energy sums go to spart.
 // ---------------------------------------------------------------------------
 
 // per-system sums of the wave energies, fixed order
@@ -656,14 +683,14 @@ __global__ __launch_bounds__(kBlock) void k_short_energy(const double *spart, La
     }
 }
 
-hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s, bool into_real) {
+hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s) {
     prof_begin(h, 9, s);
     if (h->n_total > 0 && mx.short_on()) {
         TileArgs a = tile_args(h);
         a.mx = mx;
-        // into_real: add to the pair kernel's per-particle output (x, y, z, phi)
-        a.F = into_real ? (double *)real_parts(h).f : F;
-        a.stride = into_real ? 4 : 3;
+        a.F = F;
+        a.freal = h->w.fshort;
+        h->short_part = !F;
         launch_tile<kWca, false>(a, nullptr, s);
     }
     if (energy) {
