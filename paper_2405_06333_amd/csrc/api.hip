@@ -450,9 +450,12 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     // to fill the chip
     h->split_cap = fp32 ? std::min<int64_t>(nc, 1 << 18) : 0;
     const int64_t fam_cap = fp32 ? std::min<int64_t>(nc, kFamilySplitMax) : 0;
-    const int64_t parts = std::max(kMaxRealSplit * h->split_cap, kMaxRealSplit * kMaxFamilySplit * fam_cap);
+    int64_t parts = std::max(kMaxRealSplit * h->split_cap, kMaxRealSplit * kMaxFamilySplit * fam_cap);
+    int64_t wparts = kMaxRealSplit * kMaxFamilySplit * (h->cap_sorted / kWave);
+    // FP64: as many parts as there are blocks, of 64 targets each at most
+    if (!fp32) parts = (wparts = kTileBlocks) * kWave;
     A(&w.freal_s, parts);
-    A(&w.rpart_s, fp32 ? kMaxRealSplit * kMaxFamilySplit * 3 * (h->cap_sorted / kWave) : 0);
+    A(&w.rpart_s, 3 * wparts);
     A(&w.spart, 2 * (h->cap_sorted / kWave));
     A(&w.err, 4);
     A(&w.step, 1);

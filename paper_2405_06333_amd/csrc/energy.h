@@ -77,7 +77,7 @@ __device__ __forceinline__ void energy_block(const EnergyArgs &a, int r, double 
 inline EnergyArgs energy_args(rbe2d_ctx *h, double *energy, uint32_t flags, const double *gE, double *dEdgamma) {
     EnergyArgs a;
     a.krec = h->w.krec; a.rpart = h->real_parts > 1 ? h->w.rpart_s : h->w.rpart; a.scal = h->w.scal; a.sys = h->w.sys; a.lay = h->w.lay;
-    a.P = h->P; a.parts = h->real_parts; a.stride = (int)(h->cap_sorted / kWave);
+    a.P = h->P; a.parts = h->real_parts; a.stride = h->real_stride;
     a.do_real = (flags & RBE2D_REAL) != 0;
     a.do_k = (flags & RBE2D_KSPACE) != 0;
     a.do_ibc = (flags & RBE2D_IBC) != 0;

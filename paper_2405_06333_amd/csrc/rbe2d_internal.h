@@ -29,7 +29,15 @@ constexpr int kWave = 64;
 constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
 constexpr int kMaxFamilySplit = 3;   // ... and its image families into further groups, for at most
 constexpr int64_t kFamilySplitMax = 49152;   // this many targets
-constexpr int kTileSplits = 4;       // FP64 real space: 1, 2, 4 or 12 waves share the pair work of 64 targets
+// FP64 real space: 1, 2, 4 or (index 4 of the tuner) tile_parts blocks of 4
+// waves share the pair work of a tile of 64 targets; the chip holds
+// kTileBlocks such blocks
+constexpr int kTileSplits = 4, kTileBlocks = 768;
+constexpr int kMaxTileParts = 16;
+constexpr int tile_parts(int n_tiles) {
+    const int fit = kTileBlocks / (n_tiles > 0 ? n_tiles : 1);
+    return fit < 1 ? 1 : fit < kMaxTileParts ? fit : kMaxTileParts;
+}
 constexpr double kPi = 3.14159265358979323846;
 
 // One family of image sources for the real-space sum, seen from the target:
@@ -194,6 +202,7 @@ struct rbe2d_ctx {
     int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most
     bool one_stream = false;         // run the k-space chain on the caller's stream too (no side stream)
     bool short_part = false;         // fshort belongs to the forces of this cell list
+    int real_stride = 0;             // waves per part in rpart_s
     int real_parts = 1;              // parts of the last pair sums (1: freal, rpart; else freal_s, rpart_s)
     bool cells_counted = false;      // the preparation counted the particles per cell (next build skips it)
     bool records_moved = false;      // ... in an MD pass, whose particle records the build reads

@@ -874,7 +874,6 @@ hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStr
 // The pair sums; returns whether the assembly rode along
 static bool launch_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipStream_t s) {
     if (h->precision != RBE2D_PREC_FP32_PHASE) {
-        h->real_parts = 1;
         launch_tile_pairs(h, want_dg, as, s);
         return as != nullptr;
     }
@@ -904,6 +903,7 @@ static bool launch_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hip
     const int split = r.nsplit == 1 ? 0 : h->n_total > kFamilySplitMax ? 1 : 2;
     const int layers = split == 2 ? std::min(kMaxFamilySplit, 1 + nfam) : 1;
     h->real_parts = r.nsplit * layers;
+    h->real_stride = r.rsplit_stride;
     const bool ride = as && split == 2;
     const AssembleArgs asm_args = ride ? *as : AssembleArgs();
     const int rows = r.nsplit * layers, per_row = rows * (kBlock / kWave);

@@ -13,7 +13,7 @@ namespace rbe2d {
 
 // ---------------------------------------------------------------------------
 // Pair sums.  A tile is 64 consecutive targets of one system in cell order
-// (one lane each); 1 to 8 waves share its candidates.
+// (one lane each); 1 to 64 waves share its candidates.
 //
 //  1. The columns of cells that come within the cutoff of the tile's bounding
 //     box -- in the periodic copies and, for the erfc sum, in every image
@@ -57,8 +57,11 @@ struct TileArgs {
     const SysDesc *sys;
     const Family *fam;          // kMaxFamilies per system
     Layout lay;
-    int n_sys, n_waves;         // n_waves: tiles of all systems
-    int wpt;                    // waves per tile
+    int n_sys, n_total, n_waves;   // n_waves: tiles of all systems
+    int wpt;                    // waves per tile in a block
+    int parts;                  // blocks (grid rows) per tile; their sums go to freal_s and rpart_s if > 1
+    double4 *freal_s;
+    double *rpart_s;
     int nblocks;                // logical blocks (the grid is rounded up to 8 * kTileChunks chunks)
     int nbx;                    // ASM: blocks that sum pairs
     double4 *freal;
@@ -73,7 +76,6 @@ constexpr int kTileChunks = 8;      // contiguous tile ranges per XCD
 constexpr int kMaxRuns = 80;        // runs per batch of the candidate list
 constexpr int kRunGroup = 16;       // columns looked up together; up to 3 runs each
 constexpr int kMaxTileWaves = 12;   // waves per tile (and block)
-constexpr int kTileWaves[kTileSplits] = {1, 2, 4, kMaxTileWaves};
 
 // LDS written by other lanes of the same wave: the wave's LDS operations are
 // executed in order, this keeps the compiler from reordering them
@@ -302,7 +304,8 @@ void k_tile(TileArgs a, AssembleArgs as) {
     const int nbx = ASM ? a.nbx : (int)gridDim.x;
     if constexpr (ASM) {
         if ((int)blockIdx.x >= nbx) {
-            assemble_wave<DG>(as, ((int)blockIdx.x - nbx) * (blockDim.x / kWave) +
+            const int b = ((int)blockIdx.x - nbx) * gridDim.y + blockIdx.y;
+            assemble_wave<DG>(as, b * (blockDim.x / kWave) +
                                       __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), threadIdx.x % kWave);
             return;
         }
@@ -321,7 +324,8 @@ void k_tile(TileArgs a, AssembleArgs as) {
     const int lb = ((jblk / cs) * 8 + (int)(blockIdx.x & 7)) * cs + jblk % cs;
     if (lb >= a.nblocks) return;
     const int per_block = (int)(blockDim.x / kWave) / a.wpt;
-    const int tile = lb * per_block + wid / a.wpt, sub = wid % a.wpt;
+    const int tile = lb * per_block + wid / a.wpt, bsub = wid % a.wpt;
+    const int sub = (int)blockIdx.y * a.wpt + bsub, nsub = (int)gridDim.y * a.wpt;   // of the tile's waves
     const bool tile_on = tile < a.n_waves;                 // wave-uniform; barriers below see every wave
     const int t = min(tile, a.n_waves - 1) * kWave + lane;
     const int r = __builtin_amdgcn_readfirstlane(find_sys(a.lay.sbase, a.n_sys, t & ~(kWave - 1)));
@@ -429,9 +433,10 @@ void k_tile(TileArgs a, AssembleArgs as) {
         double4 rec;
         // Fetches this lane's source of the next chunk; false after the last.
         // The first chunk of the tile (wave 0) is its own targets; then lane l
-        // takes positions l nch + c of the list, c = sub, sub + wpt, ...
+        // takes positions l nch + c of the list of nch chunks; the chunks of all
+        // lists are dealt to the tile's waves in turn
         bool own = sub == 0, diag = false;
-        int c = 0, nch = 0;
+        int c = own ? -1 : sub - 1 - nsub, nch = 0;
         auto fetch = [&]() -> bool {
             diag = own;
             if (own) {
@@ -439,12 +444,12 @@ void k_tile(TileArgs a, AssembleArgs as) {
                 src_ok = active;
                 src_j = active ? t : t0;
             } else {
-                c += a.wpt;
+                c += nsub;
                 if (c >= nch) {
                     do {
+                        c -= nch;
                         if (!rf.fill()) return false;
                         nch = (rf.total + kWave - 1) / kWave;
-                        c = sub;
                     } while (c >= nch);
                     int lo = 0, hi = rf.nr - 1;   // first run that ends after the lane's first position
                     while (lo < hi) {
@@ -558,15 +563,15 @@ void k_tile(TileArgs a, AssembleArgs as) {
         }
     }
     if (a.wpt > 1) {
-        // sums of the tile's waves, in wave order
+        // sums of the block's waves, in wave order
         __syncthreads();
         double *mine = reinterpret_cast<double *>(wl);
-        if (sub != 0) {
+        if (bsub != 0) {
             mine[lane] = fx; mine[kWave + lane] = fy; mine[2 * kWave + lane] = fz; mine[3 * kWave + lane] = phi;
             if (DG) { mine[4 * kWave + lane] = dpt; mine[5 * kWave + lane] = dpb; }
         }
         __syncthreads();
-        if (sub != 0) return;
+        if (bsub != 0) return;
         for (int s = 1; s < a.wpt; s++) {
             const double *o = reinterpret_cast<const double *>(wl + s * Lds::kWaveBytes);
             fx += o[lane]; fy += o[kWave + lane]; fz += o[2 * kWave + lane]; phi += o[3 * kWave + lane];
@@ -598,7 +603,8 @@ void k_tile(TileArgs a, AssembleArgs as) {
         if (active) {
             const int i = a.sidx[t];
             const double qi = me.w * d.pref;
-            a.freal[i] = make_double4(qi * fx, qi * fy, qi * fz, d.pref * phi);
+            double4 *o = a.parts > 1 ? a.freal_s + (int64_t)blockIdx.y * a.n_total : a.freal;
+            o[i] = make_double4(qi * fx, qi * fy, qi * fz, d.pref * phi);
             qphi = qi * phi;
             if (DG) { qdt = qi * dpt; qdb = qi * dpb; }
         }
@@ -606,29 +612,39 @@ void k_tile(TileArgs a, AssembleArgs as) {
         qphi = wave_sum(qphi);
         if (DG) { qdt = wave_sum(qdt); qdb = wave_sum(qdb); }
         if (lane == 0) {
-            a.rpart[3 * tile] = qphi;
-            a.rpart[3 * tile + 1] = qdt;
-            a.rpart[3 * tile + 2] = qdb;
+            double *o = a.parts > 1 ? a.rpart_s + 3 * ((int64_t)blockIdx.y * a.n_waves + tile) : a.rpart + 3 * tile;
+            o[0] = qphi;
+            o[1] = qdt;
+            o[2] = qdb;
         }
     }
 }
 
+template <TileKind KIND>
 static TileArgs tile_args(rbe2d_ctx *h) {
     TileArgs r{};
     r.src = h->w.sorted; r.sidx = h->w.sidx; r.start = h->w.start;
-    r.sys = h->w.sys; r.fam = h->w.fam; r.lay = h->w.lay; r.n_sys = h->n_sys; r.n_waves = h->n_swaves;
-    r.freal = h->w.freal; r.rpart = h->w.rpart; r.spart = h->w.spart;
-    // too few tiles to fill the chip: several waves share one, 12 or 4 where all
-    // blocks are then in flight at once (3 waves per SIMD of 256 CUs).  Force
-    // calls: 8000 ions, 12 waves 67 us, 8 waves 69; 20000 ions, 4 waves 102, 8
-    // waves 112, 6 waves 117 (a block of 6 loads two of the four SIMDs twice);
-    // 64000 ions, 2 waves 160, 4 waves 166; 120000 ions, 2 waves 237, 1 wave 272.
-    int n = h->n_swaves <= 256 ? 3 : h->n_swaves <= 768 ? 2 : h->n_swaves <= 2048 ? 1 : 0;
-    if (h->precision != RBE2D_PREC_FP32_PHASE) {   // (FP32 handles tune the split of their own pair kernel)
+    r.sys = h->w.sys; r.fam = h->w.fam; r.lay = h->w.lay; r.n_sys = h->n_sys; r.n_total = (int)h->n_total; r.n_waves = h->n_swaves;
+    r.freal = h->w.freal; r.rpart = h->w.rpart; r.freal_s = h->w.freal_s; r.rpart_s = h->w.rpart_s; r.spart = h->w.spart;
+    // Too few tiles to fill the chip: 4 or 2 waves share one, and up to 384 tiles
+    // as many blocks of 4 waves as the chip holds at once (3 waves per SIMD of
+    // 256 CUs): a lone wave of a SIMD is bound by its chain of instructions.
+    // Force calls with one block of 12 (to 256 tiles) or 4 waves | with parts:
+    // 4000 ions 66 | 56 and 75 | 58 us, 10000 81 | 75, 20000 101 | 83 and 129 |
+    // 100.  Two or three parts of 385 to 768 tiles change less than 4 % either
+    // way.  64000 ions: 2 waves 160, 4 waves 166; 120000: 2 waves 237, 1 wave 272.
+    int n = h->n_swaves <= 768 ? 2 : h->n_swaves <= 2048 ? 1 : 0;
+    r.parts = 1;
+    if (KIND == kWca) {
+        // little work per tile: up to 12 waves of one block
+        if (h->n_swaves <= 256) { r.wpt = kMaxTileWaves; return r; }
+    } else {
+        if (n == 2) n = 3;
         if (h->force_rsplit) n = h->force_rsplit - 1;
         else if (h->tuned_now && h->tune.rsplit) n = h->tune.rsplit - 1;
+        if (n >= 3) r.parts = tile_parts(h->n_swaves);
     }
-    r.wpt = kTileWaves[std::min(n, kTileSplits - 1)];
+    r.wpt = 1 << std::min(n, 2);
     return r;
 }
 
@@ -642,16 +658,18 @@ static void launch_tile(TileArgs r, const AssembleArgs *as, hipStream_t s) {
     const int bytes = waves * TileLds<DG>::kWaveBytes;
     if constexpr (KIND == kErfc) {
         if (as) {
-            const int na = (as->items() + waves - 1) / waves;
-            hipLaunchKernelGGL((k_tile<KIND, DG, true>), dim3(r.nbx + na), dim3(waves * kWave), bytes, s, r, *as);
+            const int row = waves * r.parts;
+            hipLaunchKernelGGL((k_tile<KIND, DG, true>), dim3(r.nbx + (as->items() + row - 1) / row, r.parts), dim3(waves * kWave), bytes, s, r, *as);
             return;
         }
     }
-    hipLaunchKernelGGL((k_tile<KIND, DG, false>), dim3(r.nbx), dim3(waves * kWave), bytes, s, r, AssembleArgs());
+    hipLaunchKernelGGL((k_tile<KIND, DG, false>), dim3(r.nbx, r.parts), dim3(waves * kWave), bytes, s, r, AssembleArgs());
 }
 
 void launch_tile_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipStream_t s) {
-    const TileArgs r = tile_args(h);
+    const TileArgs r = tile_args<kErfc>(h);
+    h->real_parts = r.parts;
+    h->real_stride = h->n_swaves;
     prof_begin(h, 4, s);
     if (want_dg) launch_tile<kErfc, true>(r, as, s);
     else launch_tile<kErfc, false>(r, as, s);
@@ -686,7 +704,7 @@ __global__ __launch_bounds__(kBlock) void k_short_energy(const double *spart, La
 hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s) {
     prof_begin(h, 9, s);
     if (h->n_total > 0 && mx.short_on()) {
-        TileArgs a = tile_args(h);
+        TileArgs a = tile_args<kWca>(h);
         a.mx = mx;
         a.F = F;
         a.freal = h->w.fshort;

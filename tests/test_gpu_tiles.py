@@ -76,9 +76,10 @@ def test_real_space_and_derivatives(torch, R, orc, w):
     slab.check()
 
 
-@pytest.mark.parametrize("N", [9000, 40000, 70000, 140000])
+@pytest.mark.parametrize("N", [700, 9000, 24576, 24577, 40000, 70000, 140000])
 def test_waves_per_tile(torch, R, orc, N):
-    """8, 4, 2 and 1 waves share a tile as the system grows."""
+    """16, 5, 2 and 1 blocks of 4 waves, 2 waves and 1 wave share a tile as the
+    system grows."""
     L = float(np.sqrt(N / 1.5))
     w = wl(20, N, L, L, 6.0, 3.0, M=2)
     pos, q = inputs.sample(w)
