@@ -1002,22 +1002,42 @@ std::mutex g_static_mu;
 
 // Tables of one system, passed by value as kernel arguments (each launch's
 // arguments stay below 4 KB)
-struct PutDesc {
-    SysDesc d;
-    int lay[10];
-};
 constexpr int kFamPerPut = 32;
 struct PutFam {
     Family f[kFamPerPut];
     int first, count;
 };
+constexpr int kImgPerPut = 32;
+struct PutImg {
+    double gp[kImgPerPut], gm[kImgPerPut];
+    int ea_p[kImgPerPut], eb_p[kImgPerPut], ea_m[kImgPerPut], eb_m[kImgPerPut];
+};
+struct PutDesc {
+    SysDesc d;
+    int lay[10];
+    PutImg img;      // the first image orders
+    PutFam fam;      // the first families
+};
+static_assert(sizeof(PutDesc) + 128 <= 4096, "kernel arguments");
 
+__device__ __forceinline__ void put_families(const PutFam &a, Family *fam) {
+    if ((int)threadIdx.x < a.count) fam[a.first + threadIdx.x] = a.f[threadIdx.x];
+}
 // (the cell counts start at zero in every build: the array may hold another
 // call's values)
 __global__ __launch_bounds__(kBlock) void k_put_desc(PutDesc a, SysDesc *sys, int *off, int *pbase, int *bbase,
-                                                     int *tbase, int *sbase, int *err, int *count, int n_count) {
+                                                     int *tbase, int *sbase, int *err, int *count, int n_count,
+                                                     ImgTable *img, Family *fam) {
     for (int c = blockIdx.x * kBlock + threadIdx.x; c < n_count; c += gridDim.x * kBlock) count[c] = 0;
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    if (blockIdx.x != 0) return;
+    put_families(a.fam, fam);
+    const int o = (int)threadIdx.x - kWave;
+    if (o >= 0 && o < kImgPerPut) {
+        img->gp[o] = a.img.gp[o]; img->gm[o] = a.img.gm[o];
+        img->ea_p[o] = a.img.ea_p[o]; img->eb_p[o] = a.img.eb_p[o];
+        img->ea_m[o] = a.img.ea_m[o]; img->eb_m[o] = a.img.eb_m[o];
+    }
+    if (threadIdx.x != 0) return;
     *sys = a.d;
     int *dst[5] = {off, pbase, bbase, tbase, sbase};
     for (int k = 0; k < 5; k++) {
@@ -1029,9 +1049,7 @@ __global__ __launch_bounds__(kBlock) void k_put_desc(PutDesc a, SysDesc *sys, in
 __global__ void k_put_img(ImgTable a, ImgTable *img) {
     if (threadIdx.x == 0) *img = a;
 }
-__global__ void k_put_fam(PutFam a, Family *fam) {
-    if ((int)threadIdx.x < a.count) fam[a.first + threadIdx.x] = a.f[threadIdx.x];
-}
+__global__ void k_put_fam(PutFam a, Family *fam) { put_families(a, fam); }
 
 rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t N, const double *pos,
                             const double *q, double *F, double *energy, uint32_t flags, int32_t *err_word,
@@ -1109,17 +1127,25 @@ rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t 
     // last call's contents; every call rewrites what it reads)
     const SysHost &sh = h->sys[0];
     pd.d = sh.d;
-    const int ncb = std::min((h->total_cells + kBlock - 1) / kBlock, 256);
-    hipLaunchKernelGGL(k_put_desc, dim3(ncb), dim3(kBlock), 0, s, pd, h->w.sys, h->w.lay.off, h->w.lay.pbase,
-                       h->w.lay.bbase, h->w.lay.tbase, h->w.lay.sbase, h->w.err, h->w.count, h->total_cells);
-    hipLaunchKernelGGL(k_put_img, dim3(1), dim3(64), 0, s, sh.img, h->w.img);
-    for (int f0 = 0; f0 < (int)sh.fam.size(); f0 += kFamPerPut) {
+    auto families = [&](int f0) {
         PutFam pf;
         pf.first = f0;
-        pf.count = std::min<int>(kFamPerPut, (int)sh.fam.size() - f0);
+        pf.count = std::max(0, std::min<int>(kFamPerPut, (int)sh.fam.size() - f0));
         for (int i = 0; i < pf.count; i++) pf.f[i] = sh.fam[f0 + i];
-        hipLaunchKernelGGL(k_put_fam, dim3(1), dim3(64), 0, s, pf, h->w.fam);
+        return pf;
+    };
+    pd.fam = families(0);
+    for (int o = 0; o < kImgPerPut; o++) {
+        pd.img.gp[o] = sh.img.gp[o]; pd.img.gm[o] = sh.img.gm[o];
+        pd.img.ea_p[o] = sh.img.ea_p[o]; pd.img.eb_p[o] = sh.img.eb_p[o];
+        pd.img.ea_m[o] = sh.img.ea_m[o]; pd.img.eb_m[o] = sh.img.eb_m[o];
     }
+    const int ncb = std::min((h->total_cells + kBlock - 1) / kBlock, 256);
+    hipLaunchKernelGGL(k_put_desc, dim3(ncb), dim3(kBlock), 0, s, pd, h->w.sys, h->w.lay.off, h->w.lay.pbase,
+                       h->w.lay.bbase, h->w.lay.tbase, h->w.lay.sbase, h->w.err, h->w.count, h->total_cells, h->w.img, h->w.fam);
+    if (sh.d.M > kImgPerPut) hipLaunchKernelGGL(k_put_img, dim3(1), dim3(64), 0, s, sh.img, h->w.img);
+    for (int f0 = kFamPerPut; f0 < (int)sh.fam.size(); f0 += kFamPerPut)
+        hipLaunchKernelGGL(k_put_fam, dim3(1), dim3(64), 0, s, families(f0), h->w.fam);
     h->cells_counted = false;
     RBE2D_TRY(nullptr, hipGetLastError(), "table upload");
     ForceJob job;

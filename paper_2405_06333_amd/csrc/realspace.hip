@@ -85,13 +85,14 @@ __global__ __launch_bounds__(kBlock) void k_cell_count(CellArgs a) {
     a.slot[g] = atomicAdd(&a.count[c], 1);
 }
 
-// exclusive scan of count[0..ncells) into start[0..ncells] in two launches:
-// per-block totals of 4096 cells, then each block adds the totals before it
-// (at most a few hundred) to the scan of its own cells.  The second launch
-// also clears the counts for the next build.  Integer sums: the order does
-// not matter.
+// exclusive scan of count[0..ncells) into start[0..ncells]: each block of 4096
+// cells adds the cells before it to the scan of its own.  Up to kScanDirect
+// blocks it reads their counts itself; beyond, a launch of its own leaves the
+// blocks' totals (at most a few hundred).  The scatter clears the counts for
+// the next build.  Integer sums: the order does not matter.
 constexpr int kScanPer = 16;                      // cells per thread
 constexpr int kScanCells = kBlock * kScanPer;     // cells per scan block
+constexpr int kScanDirect = 8;                    // (2 or 32: the same within 1 %)
 
 __device__ __forceinline__ void load_counts(const int *count, int n, int c0, int (&v)[kScanPer]) {
     if (c0 + kScanPer <= n && (c0 & 3) == 0) {
@@ -124,11 +125,22 @@ __global__ __launch_bounds__(kBlock) void k_scan_totals(const int *count, int n,
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_apply(int *count, int n, const int *btot, int *start) {
-    __shared__ int sh_wave[kBlock / 64];
+// btot null: the cells before this block from their counts
+__global__ __launch_bounds__(kBlock) void k_scan_apply(const int *count, int n, const int *btot, int *start) {
+    __shared__ int sh_wave[kBlock / 64], sh_before[kBlock / 64];
     __shared__ int sh_base;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (wid == 0) {
+    if (!btot) {
+        int b = 0;
+        for (int k = 0; k < (int)blockIdx.x; k++) {
+            int u[kScanPer];
+            load_counts(count, n, k * kScanCells + threadIdx.x * kScanPer, u);
+#pragma unroll
+            for (int c = 0; c < kScanPer; c++) b += u[c];
+        }
+        b = wave_sum(b);
+        if (lane == 0) sh_before[wid] = b;
+    } else if (wid == 0) {
         // cells before this block: the totals of the blocks before it
         int b = 0;
         for (int k = lane; k < (int)blockIdx.x; k += 64) b += btot[k];
@@ -150,7 +162,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(int *count, int n, const 
     }
     if (lane == 63) sh_wave[wid] = incl;
     __syncthreads();
-    int before = sh_base;
+    int before = 0;
+    if (btot) before = sh_base;
+    else
+        for (int w = 0; w < kBlock / 64; w++) before += sh_before[w];
     for (int w = 0; w < wid; w++) before += sh_wave[w];
     int run = before + incl - t;
 #pragma unroll
@@ -158,7 +173,6 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(int *count, int n, const 
         const int c = c0 + k;
         if (c < n) {
             start[c] = run;
-            count[c] = 0;       // the next build counts from zero
         }
         run += v[k];
         if (c == n - 1) start[n] = run;
@@ -170,6 +184,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_scatter(CellArgs a) {
     if (g >= a.n_total) return;
     const int c = a.cell[g];
     a.tmp[a.start[c] + a.slot[g]] = make_int2(g, c);
+    a.count[c] = 0;       // the next build counts from zero
 }
 
 // Particle gc.x of cell gc.y, whose members are at positions [b, e) of the
@@ -857,9 +872,11 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
         return hipGetLastError();
     }
     const int nsb = (h->total_cells + kScanCells - 1) / kScanCells;
-    hipLaunchKernelGGL(k_scan_totals, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf,
-                       h->w.start);
+    const bool totals = nsb > kScanDirect;
+    if (totals)
+        hipLaunchKernelGGL(k_scan_totals, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells, h->w.scanbuf);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nsb), dim3(kBlock), 0, s, h->w.count, h->total_cells,
+                       totals ? h->w.scanbuf : nullptr, h->w.start);
     hipLaunchKernelGGL(k_cell_scatter, dim3(nb), dim3(kBlock), 0, s, c);
     hipLaunchKernelGGL(k_cell_rank<SF>, dim3(n_sf + (h->n_swaves * kWave + kBlock - 1) / kBlock), dim3(kBlock), 0, s, c,
                        sf, n_sf);

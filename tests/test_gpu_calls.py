@@ -55,3 +55,20 @@ def test_force_calls(torch, R, orc, precision, N, P):
     slab.forces(pd, qd, out=H, flags=R.KSPACE | R.IBC | R.ACCUMULATE)
     assert torch.allclose(G + H - 0.5, F, rtol=0, atol=1e-13 * float(F.abs().max()) + 1e-13)
     slab.check()
+
+
+@pytest.mark.parametrize("M", [16, 17, 32, 33, 40])
+def test_tables_of_the_call_without_a_handle(torch, R, M):
+    """One launch carries 32 image orders and 32 image families; the rest
+    follow in launches of their own.  Same inputs, same sums: only the order of
+    FP64 sums may differ from the handle's."""
+    w = inputs.Workload(f"tab{M}", 90, 12.0, 12.0, 0.1, 0.99, 0.98, 1.0, 4.0, 40, M, seed=M, margin=0.005)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, "fp64")
+    kset = slab.draw_kset(w.seed)
+    slab.set_kset(kset)
+    pd, qd = to_dev(torch, pos), to_dev(torch, q)
+    F, E = slab.forces(pd, qd, want_energy=True)
+    Fs, Es = R.forces_noalloc(slab.params, to_dev(torch, kset, torch.int32), pd, qd, want_energy=True)
+    assert rel_rms(Fs.cpu().numpy(), F.cpu().numpy()) <= 1e-12
+    assert rel_rms(Es.cpu().numpy(), E.cpu().numpy()) <= 1e-12
