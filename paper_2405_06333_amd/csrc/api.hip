@@ -740,12 +740,16 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     const bool ride = rides_along(h, sc_asm && real && !two);
     RideAlong ra;
     ra.step = job.step;
-    // (an MD step: two streams)  the short-range kernel needs the cell list
-    // only: on the side stream after the k-space chain, beside the pair kernel
+    // (an MD step: two streams)  The short-range kernel needs the cell list
+    // only: after the k-space chain on the side stream, beside the pair kernel,
+    // or, where that chain is the longer one, after the pair kernel.
     const bool shortr = two && job.mx;
+    const bool short_side = h->precision != RBE2D_PREC_FP32_PHASE || h->n_total <= kShortTiles32;
     if (real)
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, shortr ? h->cells_ev : nullptr),
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, shortr && short_side ? h->cells_ev : nullptr),
                   "real-space launch");
+    if (shortr && !short_side)
+        RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, s), "short-range launch");
     if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");
     ForceExtra x;
     if (!two) {
@@ -754,7 +758,7 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     RBE2D_TRY(h, launch_kforce(h, pos, q, F, nullptr, two ? parts & ~(uint32_t)RBE2D_REAL : parts, accumulate, false,
                                real && !two, nullptr, ks, x), "force launch");
     if (two) {
-        if (shortr) {
+        if (shortr && short_side) {
             RBE2D_TRY(h, hipStreamWaitEvent(ks, h->cells_ev, 0), "stream wait");
             RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, ks), "short-range launch");
         }

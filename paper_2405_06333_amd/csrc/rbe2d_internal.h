@@ -29,6 +29,9 @@ constexpr int kWave = 64;
 constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
 constexpr int kMaxFamilySplit = 3;   // ... and its image families into further groups, for at most
 constexpr int64_t kFamilySplitMax = 49152;   // this many targets
+// FP32 handles: the short-range kernel works on tiles, beside the pair kernel in
+// an MD step, up to this many ions
+constexpr int64_t kShortTiles32 = 24576;
 // FP64 real space: 1, 2, 4 or (index 4 of the tuner) tile_parts blocks of 4
 // waves share the pair work of a tile of 64 targets; the chip holds
 // kTileBlocks such blocks

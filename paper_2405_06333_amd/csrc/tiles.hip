@@ -140,6 +140,17 @@ __device__ __forceinline__ double lj_rep(double s2_over_r2, double eps, double *
     return 4.0 * eps * (s6 * s6 - s6 + 0.25);
 }
 
+// Energy of an ion at height z at the two walls, its force added to fz
+__device__ __forceinline__ double wall_terms(const MdExtra &mx, const SysDesc &d, double z, double *fz) {
+    double ew = 0.0, rf;
+    if (mx.epsw != 0.0) {
+        const double hb = z, ht = d.H - z;
+        if (hb > 0.0 && hb < mx.hcut) { ew += lj_rep(mx.sigw2 / (hb * hb), mx.epsw, &rf); *fz += rf / hb; }
+        if (ht > 0.0 && ht < mx.hcut) { ew += lj_rep(mx.sigw2 / (ht * ht), mx.epsw, &rf); *fz -= rf / ht; }
+    }
+    return ew;
+}
+
 // of nonnegative floats, whose bits order like integers
 __device__ __forceinline__ float wave_fmin(float v, bool on) {
     return __int_as_float(wave_reduce<false>(on ? __float_as_int(v) : 0x7f800000));
@@ -582,12 +593,7 @@ void k_tile(TileArgs a, AssembleArgs as) {
     if constexpr (KIND == kWca) {
         double ep = phi, ew = 0.0;
         if (active) {
-            if (a.mx.epsw != 0.0) {
-                const double hb = me.z, ht = d.H - me.z;
-                double rfo;
-                if (hb > 0.0 && hb < a.mx.hcut) { ew += lj_rep(a.mx.sigw2 / (hb * hb), a.mx.epsw, &rfo); fz += rfo / hb; }
-                if (ht > 0.0 && ht < a.mx.hcut) { ew += lj_rep(a.mx.sigw2 / (ht * ht), a.mx.epsw, &rfo); fz -= rfo / ht; }
-            }
+            ew = wall_terms(a.mx, d, me.z, &fz);
             if (a.F) {
                 double *o = a.F + (int64_t)3 * a.sidx[t];
                 o[0] += fx; o[1] += fy; o[2] += fz;
@@ -684,6 +690,98 @@ void launch_tile_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hipSt
 // this launch beside the pair kernel's.  Per-tile energy sums go to spart.
 // ---------------------------------------------------------------------------
 
+// The same by one thread per target, over the runs of cells within the cutoff.
+// On the FP32 pair kernel's fine cells (r_c / 6 along y) it scans 50 ions per
+// target where a tile, 60 units long on the 1e6-ion slab, takes 600 candidates;
+// with few targets its chain of gathers is what a launch lasts.  Langevin steps
+// with it | with tiles: 1e6 ions 1.28 | 1.48 ms, 60000 168 | 192 us, 30000 130 |
+// 134, 20000 117 | 113.
+struct ScanArgs {
+    const double4 *src;
+    const int *sidx, *scell, *start;
+    const SysDesc *sys;
+    Layout lay;
+    int n_sys, n_waves;
+    MdExtra mx;
+    double *F;                  // added to when set, else written to freal
+    double4 *freal;
+    double *spart;
+};
+__global__ __launch_bounds__(kBlock) void k_short(ScanArgs a) {
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    const int r = __builtin_amdgcn_readfirstlane(find_sys(a.lay.sbase, a.n_sys, t & ~(kWave - 1)));
+    const SysDesc d = a.sys[r];
+    const int shift = a.lay.sbase[r] - a.lay.off[r];
+    const bool active = t - a.lay.sbase[r] < a.lay.off[r + 1] - a.lay.off[r];
+    double fx = 0, fy = 0, fz = 0, ep = 0, ew = 0;
+    if (active) {
+        const double4 me = a.src[t];
+        const int cid = a.scell[t];
+        const int cy = cid % d.ncy, cx = (cid / d.ncy) % d.ncx;
+        if (a.mx.eps != 0.0) {
+            // cell ranges within the cutoff, with a 1e-9 margin (cells were
+            // assigned by division); a small box searches each column or row once
+            const double rc = sqrt(a.mx.rc2) * (1.0 + 1e-9);
+            const int rx = (int)ceil(rc / d.hx), ry = (int)ceil(rc / d.hy);
+            const bool allx = d.ncx <= 2 * rx, ally = d.ncy <= 2 * ry;
+            const double xrel = me.x - cx * d.hx, yrel = me.y - cy * d.hy;
+            const int x0 = allx ? 0 : cx + (int)floor((xrel - rc) * d.inv_hx);
+            const int x1 = allx ? d.ncx - 1 : cx + (int)floor((xrel + rc) * d.inv_hx);
+            const int y0 = ally ? 0 : cy + (int)floor((yrel - rc) * d.inv_hy);
+            const int y1 = ally ? d.ncy - 1 : cy + (int)floor((yrel + rc) * d.inv_hy);
+            const int z0 = max(0, (int)floor((me.z - rc) * d.inv_hz));
+            const int z1 = min(d.ncz - 1, (int)floor((me.z + rc) * d.inv_hz));
+            const int *start = a.start + d.cbase;
+            for (int lz = z0; lz <= z1; lz++)
+                for (int ix = x0; ix <= x1; ix++) {
+                    const int row = (lz * d.ncx + (ix % d.ncx + d.ncx) % d.ncx) * d.ncy;
+                    // along y: one run of cells, or two where it wraps
+                    for (int part = 0; part < 2; part++) {
+                        int ya = y0, yb = y1;
+                        if (!ally) {
+                            if (part == 0) { ya = max(y0, 0); yb = min(y1, d.ncy - 1); }
+                            else if (y0 < 0) { ya = y0 + d.ncy; yb = d.ncy - 1; }
+                            else if (y1 >= d.ncy) { ya = 0; yb = y1 - d.ncy; }
+                            else break;
+                        } else if (part == 1) {
+                            break;
+                        }
+                        if (ya > yb) continue;
+                        const int b = start[row + ya] + shift, e = start[row + yb + 1] + shift;
+                        for (int j = b; j < e; j++) {
+                            if (j == t) continue;
+                            const double4 sj = a.src[j];
+                            double dx = me.x - sj.x, dy = me.y - sj.y;
+                            dx -= d.Lx * rint(dx * d.inv_Lx);
+                            dy -= d.Ly * rint(dy * d.inv_Ly);
+                            const double dz = me.z - sj.z;
+                            const double r2 = dx * dx + dy * dy + dz * dz;
+                            if (r2 < a.mx.rc2) {
+                                double rf;
+                                ep += 0.5 * lj_rep(a.mx.sig2 / r2, a.mx.eps, &rf);
+                                fx += rf / r2 * dx; fy += rf / r2 * dy; fz += rf / r2 * dz;
+                            }
+                        }
+                    }
+                }
+        }
+        ew = wall_terms(a.mx, d, me.z, &fz);
+        const int i = a.sidx[t];
+        if (a.F) {
+            double *o = a.F + (int64_t)3 * i;
+            o[0] += fx; o[1] += fy; o[2] += fz;
+        } else {
+            a.freal[i] = make_double4(fx, fy, fz, 0.0);
+        }
+    }
+    ep = wave_sum(ep);
+    ew = wave_sum(ew);
+    if ((threadIdx.x & (kWave - 1)) == 0 && t / kWave < a.n_waves) {
+        a.spart[2 * (t / kWave)] = ep;
+        a.spart[2 * (t / kWave) + 1] = ew;
+    }
+}
+
 // per-system sums of the wave energies, fixed order
 __global__ __launch_bounds__(kBlock) void k_short_energy(const double *spart, Layout lay, double *energy) {
     __shared__ double sh[kBlock / 64];
@@ -704,12 +802,18 @@ __global__ __launch_bounds__(kBlock) void k_short_energy(const double *spart, La
 hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s) {
     prof_begin(h, 9, s);
     if (h->n_total > 0 && mx.short_on()) {
-        TileArgs a = tile_args<kWca>(h);
-        a.mx = mx;
-        a.F = F;
-        a.freal = h->w.fshort;
         h->short_part = !F;
-        launch_tile<kWca, false>(a, nullptr, s);
+        if (h->precision == RBE2D_PREC_FP32_PHASE && h->n_total > kShortTiles32) {
+            ScanArgs a;
+            a.src = h->w.sorted; a.sidx = h->w.sidx; a.scell = h->w.scell; a.start = h->w.start;
+            a.sys = h->w.sys; a.lay = h->w.lay; a.n_sys = h->n_sys; a.n_waves = h->n_swaves;
+            a.mx = mx; a.F = F; a.freal = h->w.fshort; a.spart = h->w.spart;
+            hipLaunchKernelGGL(k_short, dim3((h->n_swaves * kWave + kBlock - 1) / kBlock), dim3(kBlock), 0, s, a);
+        } else {
+            TileArgs a = tile_args<kWca>(h);
+            a.mx = mx; a.F = F; a.freal = h->w.fshort;
+            launch_tile<kWca, false>(a, nullptr, s);
+        }
     }
     if (energy) {
         if (h->n_total > 0 && mx.short_on()) {

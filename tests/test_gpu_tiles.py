@@ -107,3 +107,23 @@ def test_short_range(torch, R, orc, w, precision):
     ref, ep, ew = orc.short_range(pos, w.Lx, w.Ly, w.H, 1.0, 0.9, 0.6, 0.7)
     assert rel_rms(F.cpu().numpy(), ref) <= 1e-12
     assert np.allclose(E.cpu().numpy()[0], [ep, ew], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("N", [24576, 24577, 60000])
+def test_short_range_by_tiles_or_targets(torch, R, N):
+    """FP32 handles: tiles up to 24576 ions, one thread per ion beyond; the same
+    FP64 terms as an FP64 handle's tiles.  They shift an image before or after
+    the difference is taken, 3e-14 apart in a box of 270; that is 14 times as
+    much relative to the force at r = 0.01: 4e-11, bound 1e-10."""
+    L = float(np.sqrt(N / 1.5))
+    w = wl(21, N, L, 1.1 * L, 6.0, 3.0, M=2)
+    pos, q = inputs.sample(w)
+    P, Q = to_dev(torch, pos), to_dev(torch, q)
+    mp = R.md_params(sigma=0.6, eps=1.0, sigma_wall=0.5, eps_wall=1.0)
+    out = []
+    for precision in ("fp32", "fp64"):
+        F = torch.full((N, 3), 0.25, dtype=torch.float64, device="cuda")
+        _, E = gpu_slab(R, w, precision).short_forces(P, Q, mp, F=F, want_energy=True)
+        out.append((F.cpu().numpy() - 0.25, E.cpu().numpy()))
+    assert rel_rms(out[0][0], out[1][0]) <= 1e-10
+    assert rel_rms(out[0][1], out[1][1]) <= 1e-10
