@@ -1115,7 +1115,10 @@ rbe2d_status forces_noalloc(const rbe2d_params *p, const int32_t *kset, int64_t 
         h->split_blocks = kStaticSplitBlocks;
         h->one_stream = true;
         h->side = nullptr;
-        // carve the workspaces from the array
+        // carve the workspaces from the array (no pointer of other parameters'
+        // survives: FP64 has no FP32 source records, and their writer goes by
+        // the pointer)
+        h->w = Workspace();
         Carver carve;
         carve.base = S.base;
         plan_workspace(h, 1, false, carve);

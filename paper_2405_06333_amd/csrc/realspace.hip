@@ -848,9 +848,10 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     c.pos = pos; c.q = q; c.sys = h->w.sys; c.lay = h->w.lay; c.n_sys = h->n_sys;
     c.n_total = (int)h->n_total; c.ncells = h->total_cells;
     c.cell = h->w.cell; c.slot = h->w.slot; c.count = h->w.count; c.start = h->w.start;
-    c.tmp = h->w.tmp; c.n_waves = h->n_swaves; c.sidx = h->w.sidx; c.scell = h->w.scell; c.sorted = h->w.sorted; c.src16 = h->w.src16;
+    c.tmp = h->w.tmp; c.n_waves = h->n_swaves; c.sidx = h->w.sidx; c.scell = h->w.scell; c.sorted = h->w.sorted;
     // counted by the MD pass: its k-space records of these positions precede this build on s
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
+    c.src16 = fp32 ? h->w.src16 : nullptr;
     const bool records = h->cells_counted && h->records_moved;
     c.p32 = records && fp32 ? h->w.p32 : nullptr;
     c.p64 = records && !fp32 ? h->w.p64 : nullptr;

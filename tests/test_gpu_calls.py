@@ -72,3 +72,20 @@ def test_tables_of_the_call_without_a_handle(torch, R, M):
     Fs, Es = R.forces_noalloc(slab.params, to_dev(torch, kset, torch.int32), pd, qd, want_energy=True)
     assert rel_rms(Fs.cpu().numpy(), F.cpu().numpy()) <= 1e-12
     assert rel_rms(Es.cpu().numpy(), E.cpu().numpy()) <= 1e-12
+
+
+def test_call_without_a_handle_changes_precision(torch, R):
+    """FP32, FP64 with other sizes, and FP32 again: each call's workspaces are
+    its own (an FP64 call once wrote the FP32 source records where the last
+    FP32 call had kept them, across its own tables)."""
+    for precision, N, P, M in (("fp32", 3000, 128, 8), ("fp64", 2141, 227, 5), ("fp32", 700, 40, 0), ("fp64", 65, 300, 2)):
+        w = wl(N, P, M)
+        pos, q = inputs.sample(w)
+        slab = gpu_slab(R, w, precision)
+        kset = slab.draw_kset(w.seed)
+        slab.set_kset(kset)
+        pd, qd = to_dev(torch, pos), to_dev(torch, q)
+        F = slab.forces(pd, qd).cpu().numpy()
+        for _ in range(2):
+            Fs = R.forces_noalloc(slab.params, to_dev(torch, kset, torch.int32), pd, qd)
+            assert rel_rms(Fs.cpu().numpy(), F) <= 1e-12
