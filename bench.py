@@ -39,15 +39,16 @@ SLOTS_FORCE = 16   # k.r (3), khat.r (1), angle offsets of the polar amplitudes 
                    # |cA| sin (1), X +- |cB| sin (2), 3 force FMAs
 SLOTS_REAL = 22    # per pair within r_c: d2 (5), cutoff (1), rsqrt (2), exp (2+1), erfc fit
                    # (rcp 2 + 7 FMA), force factor (2); pairs outside r_c not counted
-# the FP64 path (FP64 FMA issues at the FP32 rate on gfx950): software sincos
-# on revolutions (quarter-turn reduction 4, 6 + 7 polynomial FMAs and products,
-# t^2, 4 for the quadrant rotation: 21 per sincos)
-SLOTS_SF64 = 51      # k.r and khat.r (5), two sincos (42), 4 accumulating FMAs
-SLOTS_FORCE64 = 46   # phases (3), two half-turn-reduced sines (2 x 16) with their angle offsets
-                     # and amplitudes (2 x 3), X +- Y (2), 3 force FMAs
-SLOTS_REAL64 = 66    # per pair within r_c: d2 and cutoff (6), 1/sqrt refined twice (9), d and
-                     # 1/r^2 (2), exp (25), 1/(1 + p x) refined twice (6), erfcx fit (12),
-                     # products (6)
+# the FP64 path (FP64 FMA issues at the FP32 rate on gfx950): a table sine and
+# cosine on revolutions takes 16, a half-turn-reduced sine 13 (reduction 3,
+# t^2 1, 9 terms)
+SLOTS_SF64 = 32      # xy phase (2), its sine and cosine (16), charge (2), 4 accumulating FMAs, and
+                     # half of a z phase and its sine and cosine (8.5): half of the |nz| repeat
+SLOTS_FORCE64 = 39   # phases and angle offsets (6), two sines (26), amplitudes (2), X +- Y (2),
+                     # 3 force FMAs
+SLOTS_REAL64 = 63    # per pair within r_c: displacement, d2 and cutoff (7), 1/sqrt refined (7), d and
+                     # 1/r^2 (2), exp (19), 1/(1 + p x) refined (7), erfcx fit (12), products and
+                     # sums (9)
 SLOTS = {"fp32": {"sf_pass": SLOTS_SF, "force_scatter": SLOTS_FORCE, "real_pairs": SLOTS_REAL},
          "fp64": {"sf_pass": SLOTS_SF64, "force_scatter": SLOTS_FORCE64, "real_pairs": SLOTS_REAL64}}
 

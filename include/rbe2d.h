@@ -318,8 +318,9 @@ rbe2d_status rbe2d_force_variance(rbe2d_handle h, const int64_t *offsets, const 
  * (host, n_sys + 1 int64, as in rbe2d_batch_forces; {0, N} for a single
  * system) on the caller's pos and q (device) and the current k-set:
  * particles per thread of the structure-factor tiles (1..16), the k-range
- * split of the force pass (1..64) and, for small systems, the x-column split
- * of the pair work (1..5).  The fastest are kept in the handle and used by
+ * split of the force pass (1..64) and the split of the pair work (FP32, small
+ * systems: x-column groups, 1..5; FP64: 1..4 for 1, 2 or 4 waves per 64
+ * targets or as many blocks of 4 as the chip holds).  The fastest are kept in the handle and used by
  * every later call with the same per-system counts (other layouts use the
  * built-in heuristics); a cached MD graph is dropped.  Writes the three
  * choices to chosen (host int[3]) when not NULL.  Synchronises `stream`;
