@@ -244,7 +244,9 @@ static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
     a.pos = pos; a.q = q; a.sys = h->w.sys; a.lay = h->w.lay; a.n_sys = h->n_sys;
     a.p32 = h->w.p32; a.p64 = h->w.p64; a.bpart = h->w.bpart; a.err = h->w.err;
     a.cell = h->w.cell; a.slot = h->w.slot;
-    a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock : h->n_sys;
+    // (the call without a handle may go without a k-set, and then without k-space)
+    if (h->w.kset)
+        a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock : h->n_sys;
     a.tab.sample = sample_args(h, 0, 0, nullptr);
     a.tab.P_pad = h->P_pad; a.tab.kn32 = h->w.kn32; a.tab.kn64 = h->w.kn64;
     return a;
@@ -264,6 +266,7 @@ template <int MD>
 static void launch_prep_kernel(rbe2d_ctx *h, const PrepArgs &a, hipStream_t s) {
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
     const dim3 g(a.n_tblocks + h->n_blocks);
+    if (g.x == 0) return;
     if (fp32) hipLaunchKernelGGL((k_prep<true, MD>), g, dim3(kBlock), 0, s, a);
     else hipLaunchKernelGGL((k_prep<false, MD>), g, dim3(kBlock), 0, s, a);
 }

@@ -89,3 +89,23 @@ def test_call_without_a_handle_changes_precision(torch, R):
         for _ in range(2):
             Fs = R.forces_noalloc(slab.params, to_dev(torch, kset, torch.int32), pd, qd)
             assert rel_rms(Fs.cpu().numpy(), F) <= 1e-12
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [0, 300])
+def test_call_without_a_handle_or_a_kset(torch, R, precision, N):
+    """Without the k-space part the k-set may be NULL."""
+    import ctypes
+    w = wl(max(N, 1), 40)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    kset = slab.draw_kset(w.seed)
+    pd, qd = to_dev(torch, pos), to_dev(torch, q)
+    flags = R.REAL | R.IBC
+    want = R.forces_noalloc(slab.params, to_dev(torch, kset, torch.int32), pd, qd, flags=flags)
+    F, E = torch.zeros_like(pd), torch.zeros(5, dtype=torch.float64, device="cuda")
+    st = R.lib().rbe2d_forces_noalloc(ctypes.byref(slab.params), None, N, pd.data_ptr(), qd.data_ptr(), F.data_ptr(),
+                                      E.data_ptr(), flags, None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert st == R.RBE2D_OK
+    assert torch.equal(F, want if N else torch.zeros_like(pd))
