@@ -668,6 +668,18 @@ bool on_one_stream(const rbe2d_ctx *h, bool energy) {
 // real-space launches (not while the launches are timed class by class)
 bool rides_along(const rbe2d_ctx *h, bool one_stream) { return one_stream && h->n_total > 0 && h->prof.n == 0; }
 
+// A pair kernel whose waves are all on the chip at once lasts as long as the
+// latest of them: the structure factors then start after the cell list, beside
+// the pair kernel, and not on the chip before it.  us per call with the fork
+// before | after the cell list: energy and gradient of 150000 ions FP32 631 |
+// 557, FP64 693 | 533; forces of 150000 ions FP64 450 | 377, FP32 484 | 447 and
+// 281 | 258, of 250000 FP32 662 | 511 and 383 | 403; but of 100000 FP32, where
+// the pair work is split over more waves, 284 | 270 and 197 | 214.
+bool pairs_first(const rbe2d_ctx *h, bool energy) {
+    return h->n_swaves <= 4096 &&
+           (energy || h->precision != RBE2D_PREC_FP32_PHASE || h->n_swaves > 2048);
+}
+
 // `to` waits for what `from` has been given so far
 rbe2d_status stream_wait(rbe2d_ctx *h, hipStream_t to, hipStream_t from, hipEvent_t ev) {
     RBE2D_TRY(h, hipEventRecord(ev, from), "stream event");
@@ -691,14 +703,18 @@ rbe2d_status run_common(rbe2d_ctx *h, const double *pos, const double *q, uint32
     const bool sc_asm = (flags & RBE2D_KSPACE) != 0;
     if (kside) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
     const bool two = sc_asm && real && h->n_total > 0 && !on_one_stream(h, true);
-    if (two) {
+    const bool late = two && pairs_first(h, true);
+    if (two && !late) {
         rbe2d_status st = stream_wait(h, h->side, s, h->fork_ev);
         if (st) return st;
     }
     // real space is enqueued first: its cell list starts ahead of the structure factors
     const bool ride = rides_along(h, sc_asm && real && !two);
     const RideAlong ra;
-    if (real) RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s, ride ? &ra : nullptr), "real-space launch");
+    if (real)
+        RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s, ride ? &ra : nullptr, late ? h->fork_ev : nullptr),
+                  "real-space launch");
+    if (late) RBE2D_TRY(h, hipStreamWaitEvent(h->side, h->fork_ev, 0), "stream wait");
     if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, two ? h->side : s, true, want_dg), "structure-factor launch");
     return two ? stream_wait(h, s, h->side, h->join_ev) : RBE2D_OK;
 }
@@ -731,7 +747,8 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     const bool two = kside && real && h->n_total > 0 && (job.prepared ? !h->one_stream : !on_one_stream(h, false));
     if (kside && !job.prepared) RBE2D_TRY(h, launch_prep(h, pos, q, s, !sc_asm, real), "prep launch");
     hipStream_t ks = two ? h->side : s;
-    if (two) {
+    const bool late = two && !job.prepared && pairs_first(h, false);
+    if (two && !late) {
         rbe2d_status st = stream_wait(h, ks, s, h->fork_ev);
         if (st) return st;
     }
@@ -746,8 +763,9 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     const bool shortr = two && job.mx;
     const bool short_side = h->precision != RBE2D_PREC_FP32_PHASE || h->n_total <= kShortTiles32;
     if (real)
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, shortr && short_side ? h->cells_ev : nullptr),
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, late ? h->fork_ev : shortr && short_side ? h->cells_ev : nullptr),
                   "real-space launch");
+    if (late) RBE2D_TRY(h, hipStreamWaitEvent(ks, h->fork_ev, 0), "stream wait");
     if (shortr && !short_side)
         RBE2D_TRY(h, launch_short(h, *job.mx, nullptr, nullptr, s), "short-range launch");
     if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, ks, true, false, job.step), "structure-factor launch");

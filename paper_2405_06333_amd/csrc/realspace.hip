@@ -858,8 +858,8 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
     h->short_part = false;
     prof_begin(h, 3, s);
-    // the counts start at zero (the previous build's scan cleared them); the
-    // MD pass that moved the particles may have counted them already
+    // the counts start at zero (the previous build cleared them); the particle
+    // pass may have counted already
     if (!h->cells_counted) hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, s, c);
     h->cells_counted = false;
     const SfArgs sf = sf_args(h);

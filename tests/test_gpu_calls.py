@@ -109,3 +109,23 @@ def test_call_without_a_handle_or_a_kset(torch, R, precision, N):
     torch.cuda.synchronize()
     assert st == R.RBE2D_OK
     assert torch.equal(F, want if N else torch.zeros_like(pd))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [24577, 98305, 140000])
+def test_two_streams_from_a_first_call_on(torch, R, precision, N):
+    """Two streams, forked before or after the cell list: the first call on new
+    inputs equals the calls after it, bit by bit, and its parts add up."""
+    w = wl(N, 33, M=2)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    slab.set_kset(slab.draw_kset(w.seed))
+    pd, qd = to_dev(torch, pos), to_dev(torch, q)
+    F = slab.forces(pd, qd)
+    e = slab.energy(pd, qd)
+    for _ in range(3):
+        assert torch.equal(slab.forces(pd, qd), F)
+        assert torch.equal(slab.energy(pd, qd), e)
+    G = slab.forces(pd, qd, flags=R.REAL) + slab.forces(pd, qd, flags=R.KSPACE | R.IBC)
+    assert rel_rms(G.cpu().numpy(), F.cpu().numpy()) <= 1e-13
+    slab.check()
