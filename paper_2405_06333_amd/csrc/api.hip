@@ -611,6 +611,23 @@ rbe2d_status compute_layout(rbe2d_ctx *h, const int64_t *counts, int *lay) {
     return RBE2D_OK;
 }
 
+// Every call counts the particles per cell from zero, and its cell list clears
+// the counts.  Counts of a call that failed in between are cleared at its end
+// (CountGuard: replays of a captured call count from zero as well), or, where
+// that launch fails too, when the next call begins.
+hipError_t clear_counts(rbe2d_ctx *h, hipStream_t s) {
+    if (!h->cells_counted) return hipSuccess;
+    (void)hipGetLastError();   // (the failure that left them, reported by its call)
+    const hipError_t e = launch_fill(h->w.count, (int64_t)h->total_cells * 4, s);
+    if (e == hipSuccess) h->cells_counted = false;
+    return e;
+}
+struct CountGuard {
+    rbe2d_ctx *h;
+    hipStream_t s;
+    ~CountGuard() { (void)clear_counts(h, s); }
+};
+
 // Particle layout of all systems for the given counts; uploaded (through
 // pinned staging, ordered on the stream) only when it changes.
 rbe2d_status set_layout(rbe2d_ctx *h, const int64_t *counts, hipStream_t s) {
@@ -619,6 +636,7 @@ rbe2d_status set_layout(rbe2d_ctx *h, const int64_t *counts, hipStream_t s) {
     std::vector<int> lay(5 * (n + 1), 0);
     rbe2d_status st = compute_layout(h, counts, lay.data());
     if (st) return st;
+    RBE2D_TRY(h, clear_counts(h, s), "count clear");
     if (h->lay_valid && lay == h->lay_host) return RBE2D_OK;
     if (h->lay_ev_pending) RBE2D_TRY(h, hipEventSynchronize(h->lay_ev), "layout wait");
     std::memcpy(h->lay_stage, lay.data(), lay.size() * sizeof(int));
@@ -794,6 +812,7 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
 
 rbe2d_status run_forces(rbe2d_ctx *h, const double *pos, const double *q, double *F, double *energy,
                         uint32_t flags, hipStream_t s) {
+    const CountGuard guard{h, s};
     if (flags & ~(uint32_t)(RBE2D_ALL | RBE2D_ACCUMULATE)) return fail(h, RBE2D_E_INVAL, "unknown flags");
     rbe2d_status st = check_arrays(h, pos, q);
     if (st) return st;
@@ -947,6 +966,7 @@ rbe2d_status md_run(rbe2d_ctx *h, double *pos, double *vel, const double *q, dou
                     double zhi_from_top, uint64_t seed, int64_t step0, int32_t n_steps, bool use_graph,
                     const MdExtra *mx, hipStream_t s) {
     if (n_steps <= 0) return RBE2D_OK;
+    const CountGuard guard{h, s};
     h->kset_valid = true;
     if (!mx && h->n_total > 0)
         return vv_run(h, pos, vel, q, F, dt, zlo, zhi_from_top, seed, step0, n_steps, use_graph, s);
@@ -1333,6 +1353,7 @@ rbe2d_status rbe2d_energy(rbe2d_handle h, int64_t N, const double *pos, const do
     rbe2d_status st = single_layout(h, N, s);
     if (st) return st;
     if (!energy) return fail(h, RBE2D_E_INVAL, "energy is NULL");
+    const CountGuard guard{h, s};
     st = check_arrays(h, pos, q);
     if (st) return st;
     // the gamma-derivative sums of the pair kernel cost little and let a
@@ -1358,6 +1379,7 @@ rbe2d_status rbe2d_energy_backward(rbe2d_handle h, int64_t N, const double *pos,
     rbe2d_status st = single_layout(h, N, s);
     if (st) return st;
     if (!gE) return fail(h, RBE2D_E_INVAL, "gE is NULL");
+    const CountGuard guard{h, s};
     st = check_arrays(h, pos, q);
     if (st) return st;
     if (!reuse) {
@@ -1467,6 +1489,7 @@ rbe2d_status rbe2d_short_forces(rbe2d_handle h, const int64_t *offsets, const do
     st = layout_from_offsets(h, offsets, s);
     if (st) return st;
     if (h->n_total > 0 && (!pos || !q || !F)) return fail(h, RBE2D_E_INVAL, "NULL array");
+    const CountGuard guard{h, s};
     if (mx.short_on()) RBE2D_TRY(h, launch_cells(h, pos, q, s), "cell list");
     RBE2D_TRY(h, launch_short(h, mx, F, energy, s), "short-range launch");
     return RBE2D_OK;
@@ -1504,6 +1527,7 @@ rbe2d_status rbe2d_autotune(rbe2d_handle h, const int64_t *offsets, const double
     if (!h->kset_valid) return fail(h, RBE2D_E_STATE, "no k-set: call rbe2d_set_kset or rbe2d_sample_kset");
     if (total > 0 && (!pos || !q)) return fail(h, RBE2D_E_INVAL, "pos or q is NULL");
     RBE2D_TRY(h, hipStreamSynchronize(s), "autotune sync");
+    const CountGuard guard{h, s};
     free_graph(h);                 // a captured step holds the old launch parameters
     h->tune = rbe2d_ctx::Tuning();
     const int prof_n = h->prof.n;

@@ -861,7 +861,12 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     // the counts start at zero (the previous build cleared them); the particle
     // pass may have counted already
     if (!h->cells_counted) hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kBlock), 0, s, c);
-    h->cells_counted = false;
+    h->cells_counted = true;   // (until all launches of the build are given)
+    auto built = [&] {
+        const hipError_t e = hipGetLastError();
+        h->cells_counted = e != hipSuccess;
+        return e;
+    };
     const SfArgs sf = sf_args(h);
     const int n_sf = SF == kNoSf ? 0 : SfRide<SF>::parts(sf);
     const size_t lds = (h->max_cells + 1 + (size_t)h->max_n) * sizeof(int);
@@ -870,7 +875,7 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
         hipLaunchKernelGGL(k_cells_small<SF>, dim3(h->n_sys + (n_sf + per - 1) / per), dim3(kSmallThreads),
                            std::max<size_t>(lds, per * SfRide<SF>::kLds), s, c, sf);
         prof_end(h, 3, s);
-        return hipGetLastError();
+        return built();
     }
     const int nsb = (h->total_cells + kScanCells - 1) / kScanCells;
     const bool totals = nsb > kScanDirect;
@@ -882,7 +887,7 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     hipLaunchKernelGGL(k_cell_rank<SF>, dim3(n_sf + (h->n_swaves * kWave + kBlock - 1) / kBlock), dim3(kBlock), 0, s, c,
                        sf, n_sf);
     prof_end(h, 3, s);
-    return hipGetLastError();
+    return built();
 }
 
 hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s) {

@@ -1,0 +1,130 @@
+"""The library's host side on a runtime without a GPU (host_runtime.cpp): what a
+failed call leaves on the device does not reach the next one.
+
+Each scenario runs in a process of its own, with the stand-in runtime loaded
+ahead of the library."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+from paper_2405_06333_amd import rbe2d as R   # noqa: E402  (loads the library on first use)
+
+FP64, FP32 = R.PREC_FP64, R.PREC_FP32_PHASE
+BUF = 1 << 16   # stands for every device array: kernels do not run
+
+
+class Host:
+    """A handle and its calls on the stand-in runtime."""
+
+    def __init__(self, precision, N, P=8, n_sys=1):
+        self.fake, self.L, self.N = ctypes.CDLL(sys.argv[2]), R.lib(), N
+        self.fake.fake_log.restype = ctypes.c_char_p
+        p = R.Params(Lx=40.0, Ly=40.0, H=6.0, Lz_ext=0.0, eps_lz=0.0, gamma_top=0.7, gamma_bot=-0.5, alpha=1.0,
+                     r_c=3.0, P=P, M=2, precision=precision, reserved=0, n_max=N, coulomb_prefactor=1.0)
+        self.params = p
+        self.h = ctypes.c_void_p()
+        self.off = (ctypes.c_int64 * (n_sys + 1))(*[i * N for i in range(n_sys + 1)])
+        if n_sys == 1:
+            assert self.L.rbe2d_create(ctypes.byref(p), ctypes.byref(self.h)) == 0
+        else:
+            assert self.L.rbe2d_batch_create(n_sys, (R.Params * n_sys)(*[p] * n_sys), ctypes.byref(self.h)) == 0
+        assert self.L.rbe2d_sample_kset(self.h, 1, 0, None) == 0
+        self.md = R.md_params(gamma=1.0, kT=1.0, sigma=0.5, eps=1.0, sigma_wall=0.5, eps_wall=1.0, wall_margin=0.1)
+        self.calm = R.md_params(gamma=1.0, kT=1.0, wall_margin=0.1)
+
+    def call(self, name, fail=None, skip=0):
+        """Status and launches [(kernel, blocks, threads, error)] of one call."""
+        self.fake.fake_clear()
+        if fail:
+            self.fake.fake_fail(fail.encode(), skip)
+        L, h, N, off = self.L, self.h, self.N, self.off
+        st = {
+            "forces": lambda: L.rbe2d_forces(h, N, BUF, BUF, BUF, None, R.ALL, None),
+            "forces_energy": lambda: L.rbe2d_forces(h, N, BUF, BUF, BUF, BUF, R.ALL, None),
+            "real": lambda: L.rbe2d_forces(h, N, BUF, BUF, BUF, BUF, R.REAL, None),
+            "energy": lambda: L.rbe2d_energy(h, N, BUF, BUF, BUF, None),
+            "backward": lambda: L.rbe2d_energy_backward(h, N, BUF, BUF, BUF, BUF, BUF, BUF, None),
+            "batch": lambda: L.rbe2d_batch_forces(h, off, BUF, BUF, BUF, BUF, R.ALL, None),
+            "variance": lambda: L.rbe2d_force_variance(h, off, BUF, BUF, BUF, None),
+            "short": lambda: L.rbe2d_short_forces(h, off, BUF, BUF, BUF, BUF, ctypes.byref(self.md), None),
+            "short_off": lambda: L.rbe2d_short_forces(h, off, BUF, BUF, BUF, BUF, ctypes.byref(self.calm), None),
+            "md": lambda: L.rbe2d_md_run(h, N, BUF, BUF, BUF, BUF, 1e-3, 0.1, 5.9, 1, 0, 2, 0, None),
+            "md_graph": lambda: L.rbe2d_md_run(h, N, BUF, BUF, BUF, BUF, 1e-3, 0.1, 5.9, 1, 0, 2, 1, None),
+            "md_ex": lambda: L.rbe2d_md_run_ex(h, off, BUF, BUF, BUF, BUF, 1e-3, ctypes.byref(self.md), 1, 0, 2, 0, None),
+            "md_ex_graph": lambda: L.rbe2d_md_run_ex(h, off, BUF, BUF, BUF, BUF, 1e-3, ctypes.byref(self.md), 1, 0, 2, 1,
+                                                     None),
+            "noalloc": lambda: L.rbe2d_forces_noalloc(ctypes.byref(self.params), BUF, N, BUF, BUF, BUF, BUF, R.ALL, BUF,
+                                                      None),
+        }[name]()
+        log = [l.split() for l in self.fake.fake_log().decode().splitlines()]
+        return st, [(n, int(g), int(b), int(e)) for n, g, b, e in log]
+
+
+def counts(log, clears=("k_cells_small", "k_cell_scatter", "k_fill"), pending=False):
+    """Follows the cell counts on the device: whether the log leaves some that no
+    pass cleared, and whether a pass counted on top of others'."""
+    twice = False
+    for name, _, _, err in log:
+        if err == 0 and ("k_prep" in name or "k_cell_count" in name):
+            pending, twice = True, twice or pending
+        elif err == 0 and any(c in name for c in clears):
+            pending = False
+    return pending, twice
+
+
+SYSTEMS = [(FP64, 500), (FP64, 5000), (FP64, 100000), (FP64, 300000), (FP32, 500), (FP32, 30000), (FP32, 140000)]
+COUNTING = ["forces_energy", "real", "energy", "backward", "md", "md_ex"]
+
+
+def counts_after_failed_calls():
+    """A call that fails between its count and its cell list leaves no counts
+    that the next one would add to, or take for its own."""
+    left = 0
+    for precision, N in SYSTEMS:
+        s = Host(precision, N)
+        for first in COUNTING + ["md_graph"]:
+            launches = len(s.call(first)[1])
+            faults = [("k_", i) for i in range(launches)]
+            faults += [(f, i) for f in ("hipEventRecord", "hipStreamWaitEvent") for i in range(3)]
+            faults += [(f, 0) for f in ("hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate",
+                                        "hipGraphLaunch")]
+            for what, i in faults:
+                for then in ("forces", "real", "short", "md_ex"):
+                    assert s.call("md_ex_graph")[0] == 0      # (the next graph is captured anew)
+                    st, failed = s.call(first, what, i)
+                    if st == 0:
+                        continue
+                    case = (precision, N, first, what, i, then)
+                    left += counts(failed, clears=("k_cells_small", "k_cell_scatter"))[0]
+                    pending, twice = counts(failed)
+                    assert not pending and not twice, case    # (a captured call may be replayed now)
+                    st, log = s.call(then)
+                    assert st == 0 and not counts(log)[1], case
+                    assert any("k_prep" in l[0] or "k_cell_count" in l[0] for l in log), case
+                    assert not any("k_fill" in l[0] for l in log), case
+    assert left > 0
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("runtime") / "libhost_runtime.so")
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-o", so, os.path.join(ROOT, "tests", "host_runtime.cpp")],
+                   check=True)
+    return so
+
+
+@pytest.mark.parametrize("scenario", ["counts_after_failed_calls"])
+def test_host_side(runtime, scenario):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
+                       text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)
+    globals()[sys.argv[1]]()
