@@ -364,8 +364,10 @@ void k_tile(TileArgs a, AssembleArgs as) {
         const float xc = 0.5f * (x0 + x1), yc = 0.5f * (y0 + y1), zc = 0.5f * (z0 + z1);
         RunFinder<DG> rf{d, fams, a.start + d.cbase, runs, dgw, x0, x1, y0, y1, z0, z1, rc + marg, marg,
                            xc, yc, zc, KIND == kWca ? 0 : d.nfam, a.lay.sbase[r] - a.lay.off[r], lane, 0, 0};
-        rf.cxlo = (int)floorf((rf.x0 - rf.rcm) * (float)d.inv_hx);
-        rf.ncol = (int)floorf((rf.x1 + rf.rcm) * (float)d.inv_hx) - rf.cxlo + 1;
+        // (columns of the box and its copies only: in a box 5e5 times as long as
+        // it is wide the margin alone reaches past them)
+        rf.cxlo = max((int)floorf((rf.x0 - rf.rcm) * (float)d.inv_hx), -d.ncx);
+        rf.ncol = min((int)floorf((rf.x1 + rf.rcm) * (float)d.inv_hx), 2 * d.ncx - 1) - rf.cxlo + 1;
         // Prefilter frame: coordinates about the box centre, scaled by a power
         // of two so that every candidate lies within 64 (|s|^2 < 12288 in half
         // precision).  Half-precision rounding moves each coordinate by at

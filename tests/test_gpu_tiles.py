@@ -127,3 +127,27 @@ def test_short_range_by_tiles_or_targets(torch, R, N):
         out.append((F.cpu().numpy() - 0.25, E.cpu().numpy()))
     assert rel_rms(out[0][0], out[1][0]) <= 1e-10
     assert rel_rms(out[0][1], out[1][1]) <= 1e-10
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("Ly, H", [(6e5, 4.0), (1.0, 2.0e5)], ids=["long", "tall"])
+def test_boxes_far_longer_than_wide(torch, R, orc, precision, Ly, H):
+    """The margin of the cell search grows with the box; in these it alone
+    reaches past the copies in x.  Ions in one corner, so that they interact."""
+    w = wl(40, 200, 1.0, Ly, H, 0.5, alpha=0.1, M=0)    # (FP32 handles refuse a wider k-range)
+    rng = np.random.default_rng(w.seed)
+    pos = rng.uniform([0.0, 0.0, 0.2], [1.0, min(Ly, 12.0), 3.8 if H < 10 else 14.2], (w.N, 3))
+    q = np.where(np.arange(w.N) % 2 == 0, 1.0, -1.0)
+    kset = np.tile(np.array([[1, 0, 0]], dtype=np.int32), (w.P, 1))
+    slab = gpu_slab(R, w, precision)
+    slab.set_kset(kset)
+    P, Q = to_dev(torch, pos), to_dev(torch, q)
+    if precision == "fp64":     # (FP32 handles: the short-range tiles alone)
+        F = slab.forces(P, Q, flags=R.REAL)
+        ref = orc.evaluate(oracle_slab(orc, w, slab.Lz_ext), pos, q, kset, parts=("real",))
+        assert rel_rms(F.cpu().numpy(), ref.F) <= 1e-9
+    F, E = slab.short_forces(P, Q, R.md_params(sigma=0.4, eps=0.9, sigma_wall=0.2, eps_wall=0.7, wall_margin=0.01),
+                             want_energy=True)
+    ref, ep, ew = orc.short_range(pos, w.Lx, w.Ly, w.H, 0.4, 0.9, 0.2, 0.7)
+    assert rel_rms(F.cpu().numpy(), ref) <= 1e-10     # (y / Ly and back: 1e-16 of the position)
+    assert np.allclose(E.cpu().numpy()[0], [ep, ew], rtol=1e-10, atol=0)
