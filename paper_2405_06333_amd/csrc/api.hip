@@ -801,11 +801,11 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
         rbe2d_status st = stream_wait(h, s, ks, h->join_ev);
         if (st) return st;
         RBE2D_TRY(h, launch_add_real(h, F, job.vel, 0.5 * job.dt, s, job.energy, parts), "real-space add");
-        if (job.err_out) launch_copy_err(h, job.err_out, s);
+        if (job.err_out) RBE2D_TRY(h, launch_copy_err(h, job.err_out, s), "error word");
     }
     if (h->n_total == 0) {   // (no force pass)
         if (job.energy) RBE2D_TRY(h, launch_energy(h, job.energy, parts, nullptr, nullptr, s), "energy launch");
-        if (job.err_out) launch_copy_err(h, job.err_out, s);
+        if (job.err_out) RBE2D_TRY(h, launch_copy_err(h, job.err_out, s), "error word");
     }
     return RBE2D_OK;
 }

@@ -711,12 +711,13 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
     RBE2D_FORCE(0, true) RBE2D_FORCE(1, true) RBE2D_FORCE(2, true)
 #undef RBE2D_FORCE
     prof_end(h, 5, s);
+    hipError_t e = hipGetLastError();
     if (!split) {
         // a launch of its own: the energies of an unsplit pass are a small part of the call
-        if (energies) (void)launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
-        if (x.err_out) launch_copy_err(h, x.err_out, s);
+        if (e == hipSuccess && energies) e = launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
+        if (e == hipSuccess && x.err_out) e = launch_copy_err(h, x.err_out, s);
     }
-    return hipGetLastError();
+    return e;
 }
 
 }  // namespace rbe2d

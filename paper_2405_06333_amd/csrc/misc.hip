@@ -57,8 +57,9 @@ hipError_t launch_set_step(rbe2d_ctx *h, long long value, hipStream_t s) {
 __global__ void k_copy_err(const int *src, int32_t *dst) {
     if (threadIdx.x == 0) *dst = *src;
 }
-void launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s) {
+hipError_t launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s) {
     hipLaunchKernelGGL(k_copy_err, dim3(1), dim3(64), 0, s, h->w.err, dst);
+    return hipGetLastError();
 }
 
 }  // namespace rbe2d

@@ -321,7 +321,7 @@ hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStr
 // F += F_real (and v += half_dt F); also the energies when energy is set
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s,
                            double *energy = nullptr, uint32_t energy_flags = 0);
-void launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s);
+hipError_t launch_copy_err(rbe2d_ctx *h, int32_t *dst, hipStream_t s);
 // short-range forces added to F, or without F kept beside the pair kernel's
 // output (then part of the real-space forces of this cell list)
 hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *energy, hipStream_t s);

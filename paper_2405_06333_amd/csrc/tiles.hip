@@ -817,15 +817,17 @@ hipError_t launch_short(rbe2d_ctx *h, const MdExtra &mx, double *F, double *ener
             launch_tile<kWca, false>(a, nullptr, s);
         }
     }
-    if (energy) {
+    hipError_t e = hipGetLastError();
+    if (energy && e == hipSuccess) {
         if (h->n_total > 0 && mx.short_on()) {
             hipLaunchKernelGGL(k_short_energy, dim3(h->n_sys), dim3(kBlock), 0, s, h->w.spart, h->w.lay, energy);
+            e = hipGetLastError();
         } else {
-            (void)launch_fill(energy, (int64_t)h->n_sys * 2 * sizeof(double), s);
+            e = launch_fill(energy, (int64_t)h->n_sys * 2 * sizeof(double), s);
         }
     }
     prof_end(h, 9, s);
-    return hipGetLastError();
+    return e;
 }
 
 }  // namespace rbe2d

@@ -1,5 +1,6 @@
-"""The library's host side on a runtime without a GPU (host_runtime.cpp): what a
-failed call leaves on the device does not reach the next one.
+"""The library's host side on a runtime without a GPU (host_runtime.cpp): every
+failing launch or stream call is reported, and what a failed call leaves on the
+device does not reach the next one.
 
 Each scenario runs in a process of its own, with the stand-in runtime loaded
 ahead of the library."""
@@ -81,6 +82,20 @@ SYSTEMS = [(FP64, 500), (FP64, 5000), (FP64, 100000), (FP64, 300000), (FP32, 500
 COUNTING = ["forces_energy", "real", "energy", "backward", "md", "md_ex"]
 
 
+def lost_errors():
+    """Every launch of every call, failed in turn, makes the call fail."""
+    for precision, N in SYSTEMS:
+        s = Host(precision, N)
+        for name in ["forces", *COUNTING, "variance", "short", "short_off"] + (["noalloc"] if N <= 32768 else []):
+            st, log = s.call(name)
+            assert st == 0 and log, (precision, N, name)
+            for i in range(len(log)):
+                # (a fresh handle state: nothing of the failed call before this one is reused)
+                assert s.call("forces")[0] == 0
+                st, failed = s.call(name, "k_", i)
+                assert st == R.RBE2D_E_HIP, (precision, N, name, i, failed[i])
+
+
 def counts_after_failed_calls():
     """A call that fails between its count and its cell list leaves no counts
     that the next one would add to, or take for its own."""
@@ -118,7 +133,7 @@ def runtime(tmp_path_factory):
     return so
 
 
-@pytest.mark.parametrize("scenario", ["counts_after_failed_calls"])
+@pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
