@@ -345,6 +345,9 @@ void k_tile(TileArgs a, AssembleArgs as) {
     const bool active = tile_on && t - a.lay.sbase[r] < a.lay.off[r + 1] - a.lay.off[r];
     double4 me = make_double4(0.0, 0.0, 0.0, 0.0);
     if (active) me = a.src[t];
+    // an ion whose position is not finite (x and y, once wrapped, are then NaN)
+    // has no pairs, and no part in the tile's box
+    const bool placed = active && me.x == me.x && me.y == me.y;
     double fx = 0, fy = 0, fz = 0, phi = 0, dpt = 0, dpb = 0;
     unsigned char *wl = lds + wid * Lds::kWaveBytes;
     // all pairs of the targets `on` (the sources are the same for any of them)
@@ -497,13 +500,12 @@ void k_tile(TileArgs a, AssembleArgs as) {
             ring[e] = make_double4(rec.x + xs, rec.y + ys, (mirror ? -rec.z : rec.z) + rn.c, rn.w * rec.w);
             if (DG) ringdg[e] = make_double2(dgw[ri].x * rec.w, dgw[ri].y * rec.w);
             px *= sg; py *= sg; pz *= sg;
-            if constexpr (KIND == kWca) {
-                // the tile's own members of another pass may lie anywhere: kept
-                // finite, and as far out of reach
-                px = __builtin_amdgcn_fmed3f(px, -100.0f, 100.0f);
-                py = __builtin_amdgcn_fmed3f(py, -100.0f, 100.0f);
-                pz = __builtin_amdgcn_fmed3f(pz, -100.0f, 100.0f);
-            }
+            // kept finite (two sources share a row of the MFMAs), and as far out of
+            // reach: sources without a place, and the tile's own members of another
+            // pass, which may lie anywhere
+            px = __builtin_amdgcn_fmed3f(px, -100.0f, 100.0f);
+            py = __builtin_amdgcn_fmed3f(py, -100.0f, 100.0f);
+            pz = __builtin_amdgcn_fmed3f(pz, -100.0f, 100.0f);
             const _Float16 hx = (_Float16)px, hy = (_Float16)py, hz = (_Float16)pz;
             const float S = (float)hx * (float)hx + (float)hy * (float)hy + (float)hz * (float)hz;
             const _Float16 sh = (_Float16)(src_ok ? S : 30000.0f), one = (_Float16)1.0f;
@@ -561,15 +563,15 @@ void k_tile(TileArgs a, AssembleArgs as) {
         }
     };
     if constexpr (KIND == kErfc) {
-        if (__ballot(active) != 0) pass(active);
+        if (__ballot(placed) != 0) pass(placed);
     } else if (a.mx.eps != 0.0) {
         // without the serpentine numbering a tile that runs over the end of a
         // layer spans all of it: one pass per layer then (21,000 ions in a thin
         // slab: 18 us instead of 102)
         const int layer = d.snake ? 0 : min(d.ncz - 1, max(0, (int)(me.z / d.hz)));
-        for (uint64_t left = __ballot(active); left != 0;) {
+        for (uint64_t left = __ballot(placed); left != 0;) {
             const int l0 = __builtin_amdgcn_readlane(layer, (int)__builtin_ctzll(left));
-            const bool on = active && layer == l0;
+            const bool on = placed && layer == l0;
             left &= ~__ballot(on);
             pass(on);
             wave_lds_fence();

@@ -151,3 +151,31 @@ def test_boxes_far_longer_than_wide(torch, R, orc, precision, Ly, H):
     ref, ep, ew = orc.short_range(pos, w.Lx, w.Ly, w.H, 0.4, 0.9, 0.2, 0.7)
     assert rel_rms(F.cpu().numpy(), ref) <= 1e-10     # (y / Ly and back: 1e-16 of the position)
     assert np.allclose(E.cpu().numpy()[0], [ep, ew], rtol=1e-10, atol=0)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [60, 700, 9000])
+def test_ions_without_a_place_leave_the_others_alone(torch, R, precision, N):
+    """An ion whose position is not finite has no neighbours; every other ion
+    has what it has without it (summation order aside).  REAL alone and the
+    short-range forces: with k-space the charges of all ions meet."""
+    L = max(9.0, float(np.sqrt(N / 1.5)))
+    w = wl(41, N, L, L, 6.0, 3.0, M=2)
+    pos, q = inputs.sample(w)
+    rng = np.random.default_rng(w.seed)
+    lost = np.sort(rng.choice(N, max(1, N // 50), replace=False))
+    kept = np.setdiff1d(np.arange(N), lost)
+    bad = pos.copy()
+    for k, i in enumerate(lost):
+        bad[i, k % 3] = (np.nan, np.inf, -np.inf)[(k // 3) % 3]
+    mp = R.md_params(sigma=0.6, eps=1.0, sigma_wall=0.5, eps_wall=1.0)
+    slab = gpu_slab(R, w, precision)
+    slab.set_kset(slab.draw_kset(w.seed))
+    calls = [lambda p, c: slab.short_forces(p, c, mp)]
+    if precision == "fp64":
+        calls.append(lambda p, c: slab.forces(p, c, flags=R.REAL))
+    for f in calls:
+        F = f(to_dev(torch, bad), to_dev(torch, q)).cpu().numpy()[kept]
+        ref = f(to_dev(torch, pos[kept]), to_dev(torch, q[kept])).cpu().numpy()
+        assert np.isfinite(F).all()
+        assert rel_rms(F, ref) <= 1e-12
