@@ -675,11 +675,16 @@ rbe2d_status check_arrays(rbe2d_ctx *h, const double *pos, const double *q) {
 // 62 | 70, 4000 FP32 71 | 79, 16000 FP64 76 | 87, 24000 FP32 86 | 88 and
 // 122 | 124, 48000 FP32 122 | 121 and 185 | 172, 90000 FP64 203 | 215 and
 // 256 | 259.  Energy and gradient, whose caller waits for each: 4000 ions
-// 173 | 232, 90000 FP64 380 | 454, 90000 FP32 380 | 391.
-constexpr int64_t kOneStreamForces32 = 24576, kOneStream = 98304;
+// 173 | 232, 90000 FP64 380 | 454, 90000 FP32 380 | 391.  With many wave vectors
+// (of all systems) the assembly fills the chip by itself and gains by the pair
+// kernel beside it: FP64, 4096 slabs of 16 ions with 32 each 368 | 339, 16 slabs
+// of 500 with 4000 287 | 275, 64 of 300 with 500 167 | 162, but 1024 of 16 with
+// 32 126 | 145.
+constexpr int64_t kOneStreamForces32 = 24576, kOneStream = 98304, kOneStreamItems = 32768;
 bool on_one_stream(const rbe2d_ctx *h, bool energy) {
     return h->one_stream ||
-           h->n_total <= (!energy && h->precision == RBE2D_PREC_FP32_PHASE ? kOneStreamForces32 : kOneStream);
+           (h->n_total <= (!energy && h->precision == RBE2D_PREC_FP32_PHASE ? kOneStreamForces32 : kOneStream) &&
+            (int64_t)h->n_sys * h->P <= kOneStreamItems);
 }
 
 // On one stream the structure factors and the assembly ride along with the

@@ -125,6 +125,22 @@ def counts_after_failed_calls():
     assert left > 0
 
 
+def own_launch(log, name):
+    """Blocks and threads of the launches of a kernel of this very name."""
+    return [(g, b) for n, g, b, _ in log if f"{len(name)}{name}" in n]
+
+
+def many_wave_vectors():
+    """The k-space chain runs beside the pair sums where its wave vectors fill the
+    chip by themselves, and rides along where they do not."""
+    for precision, sf in ((FP64, "k_sf64"), (FP32, "k_sf32")):
+        for n_sys, N, P, rides in ((1024, 16, 32, True), (1025, 16, 32, False), (16, 500, 4000, False), (1, 500, 32768, True),
+                                   (1, 500, 32769, False)):
+            s = Host(precision, N, P, n_sys)
+            st, log = s.call("batch" if n_sys > 1 else "forces")
+            assert st == 0 and bool(own_launch(log, sf)) != rides, (precision, n_sys, P)
+
+
 @pytest.fixture(scope="module")
 def runtime(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("runtime") / "libhost_runtime.so")
@@ -133,7 +149,7 @@ def runtime(tmp_path_factory):
     return so
 
 
-@pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls"])
+@pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
