@@ -287,6 +287,14 @@ __global__ __launch_bounds__(kBlock) void k_cell_rank(CellArgs a, SfArgs sf, int
 constexpr int kSmallThreads = 1024;
 constexpr size_t kSmallLds = 60 << 10;
 constexpr int kSmallN = 4096;
+// More than kManySystems systems: blocks of kBlock threads up to kNarrowN
+// particles each, since several share a CU then and most threads of 1024 have
+// nothing to do; and up to kTinyN, with nothing riding along, the four launches,
+// which take less of the chip from the k-space chain beside them.  Velocity-
+// Verlet steps with 1024 | 256 threads | four launches: 16384 slabs of 8 ions
+// FP32 1054 | 954 | 950 us, 1024 of 16 116 | 119 | 109, 256 of 100 108 | 108 |
+// 103, 1024 of 200 325 | 244 | 343, 300 of 1000 340 | 344 | 373.
+constexpr int kManySystems = 128, kNarrowN = 512, kTinyN = 128;
 template <SfKind SF>
 __global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a, SfArgs sf) {
     extern __shared__ __align__(16) int lds[];
@@ -295,19 +303,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a, SfArg
     if constexpr (SF != kNoSf) {
         if (r >= a.n_sys) {
             const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x / kBlock);
-            SfRide<SF>::run(sf, (r - a.n_sys) * (kSmallThreads / kBlock) + sub, threadIdx.x % kBlock,
+            SfRide<SF>::run(sf, (r - a.n_sys) * (int)(blockDim.x / kBlock) + sub, threadIdx.x % kBlock,
                             (char *)lds + sub * SfRide<SF>::kLds);
             return;
         }
     }
+    const int nt = blockDim.x;
     const SysDesc &d = a.sys[r];
     const int off = a.lay.off[r], N = a.lay.off[r + 1] - off;
     const int c0 = d.cbase, nc = d.ncx * d.ncy * d.ncz;
     int *start = lds;                                             // positions within the system
     int *tmp = lds + nc + 1;                                      // cell lists: indices within the system
-    const int per = (nc + kSmallThreads - 1) / kSmallThreads;
+    const int per = (nc + nt - 1) / nt;
     const int lo = min(nc, (int)threadIdx.x * per), hi = min(nc, lo + per);
-    for (int c = threadIdx.x; c < nc; c += kSmallThreads) {
+    for (int c = threadIdx.x; c < nc; c += nt) {
         start[c] = a.count[c0 + c];
         a.count[c0 + c] = 0;                                      // the next build counts from zero
     }
@@ -323,14 +332,14 @@ __global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a, SfArg
     if (threadIdx.x == 0) start[nc] = N;
     __syncthreads();
     // (the next system's first start equals this one's end)
-    for (int c = threadIdx.x; c < nc; c += kSmallThreads) a.start[c0 + c] = off + start[c];
+    for (int c = threadIdx.x; c < nc; c += nt) a.start[c0 + c] = off + start[c];
     if (r == a.n_sys - 1 && threadIdx.x == 0) a.start[c0 + nc] = off + N;
-    for (int i = threadIdx.x; i < N; i += kSmallThreads) {
+    for (int i = threadIdx.x; i < N; i += nt) {
         const int c = a.cell[off + i];
         tmp[start[c - c0] + a.slot[off + i]] = i;
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < N; j += kSmallThreads) {
+    for (int j = threadIdx.x; j < N; j += nt) {
         const int g = off + tmp[j], c = a.cell[g];
         place_particle(a, d, r, make_int2(g, c), off + start[c - c0], off + start[c - c0 + 1],
                        [&](int k) { return off + tmp[k - off]; });
@@ -870,9 +879,10 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     const SfArgs sf = sf_args(h);
     const int n_sf = SF == kNoSf ? 0 : SfRide<SF>::parts(sf);
     const size_t lds = (h->max_cells + 1 + (size_t)h->max_n) * sizeof(int);
-    if (h->max_n <= kSmallN && lds <= kSmallLds) {
-        constexpr int per = kSmallThreads / kBlock;
-        hipLaunchKernelGGL(k_cells_small<SF>, dim3(h->n_sys + (n_sf + per - 1) / per), dim3(kSmallThreads),
+    const bool many = h->n_sys > kManySystems;
+    if (h->max_n <= kSmallN && lds <= kSmallLds && !(many && SF == kNoSf && h->max_n <= kTinyN)) {
+        const int threads = many && h->max_n <= kNarrowN ? kBlock : kSmallThreads, per = threads / kBlock;
+        hipLaunchKernelGGL(k_cells_small<SF>, dim3(h->n_sys + (n_sf + per - 1) / per), dim3(threads),
                            std::max<size_t>(lds, per * SfRide<SF>::kLds), s, c, sf);
         prof_end(h, 3, s);
         return built();

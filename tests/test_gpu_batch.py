@@ -331,3 +331,37 @@ def test_force_variance_single_batch_of_one_k(torch, R):
     s.set_kset(s.draw_kset(1, 0))
     var = s.force_variance(to_dev(torch, pos), to_dev(torch, q)).cpu().numpy()
     assert np.array_equal(var, np.zeros(w.N))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n_sys, N, P", [(129, 16, 9), (130, 128, 300), (130, 129, 300), (129, 512, 9), (129, 513, 9),
+                                         (2100, 15, 16)])
+def test_many_small_systems(torch, R, orc, precision, n_sys, N, P):
+    """The forms of the cell list for many systems, of unlike sizes and boxes:
+    every call again, and some systems against the oracle."""
+    ws = [inputs.small_random(500 + r % 7, N - r % 3, L=9.0 + 0.5 * (r % 5), H=5.0, gamma_top=0.6, gamma_bot=-0.5,
+                              alpha=0.9, r_c=3.0 + 0.2 * (r % 3), P=P, M=2) for r in range(n_sys)]
+    pos, q, counts = batch_inputs(ws)
+    b = make_batch(R, ws, precision)
+    off = b.offsets(counts)
+    b.sample_kset(3, 0)
+    kset = b.get_kset()
+    P_, Q_ = to_dev(torch, pos), to_dev(torch, q)
+    F = b.forces(off, P_, Q_)
+    for _ in range(2):
+        assert torch.equal(b.forces(off, P_, Q_), F)
+    F = F.cpu().numpy()
+    for r in (0, 1, n_sys // 2, n_sys - 1):
+        s = slice(off[r], off[r + 1])
+        ref = orc.evaluate(oracle_slab(orc, ws[r], b.Lz_ext[r]), pos[s], q[s], kset[r])
+        assert rel_rms(F[s], ref.F) <= TOL[precision], r
+    # and in an MD step, whose k-space chain runs beside them: positions
+    # hardly move, the k-set is the step's
+    V_, G_ = torch.zeros_like(P_), to_dev(torch, F)
+    b.md_run(off, P_, V_, Q_, G_, 1e-9, 0.05, 3, 0, 1)
+    kset, pos, G = b.get_kset(), P_.cpu().numpy(), G_.cpu().numpy()
+    for r in (0, n_sys // 2, n_sys - 1):
+        s = slice(off[r], off[r + 1])
+        ref = orc.evaluate(oracle_slab(orc, ws[r], b.Lz_ext[r]), pos[s], q[s], kset[r])
+        assert rel_rms(G[s], ref.F) <= TOL[precision], r
+    b.check()

@@ -141,6 +141,17 @@ def many_wave_vectors():
             assert st == 0 and bool(own_launch(log, sf)) != rides, (precision, n_sys, P)
 
 
+def many_systems():
+    """The cell list of many systems: narrow blocks, or none per system where
+    nothing rides along."""
+    for n_sys, N, P, threads in ((128, 16, 32, 1024), (129, 16, 32, 256), (129, 512, 8, 256), (129, 513, 8, 1024),
+                                 (2048, 16, 32, None), (2048, 128, 32, None), (2048, 129, 32, 256)):
+        s = Host(FP64, N, P, n_sys)
+        st, log = s.call("batch")
+        cells = [l for l in log if "k_cells_small" in l[0]]
+        assert st == 0 and [b for _, _, b, _ in cells] == ([threads] if threads else []), (n_sys, N, P, cells)
+
+
 @pytest.fixture(scope="module")
 def runtime(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("runtime") / "libhost_runtime.so")
@@ -149,7 +160,8 @@ def runtime(tmp_path_factory):
     return so
 
 
-@pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors"])
+@pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors",
+                                      "many_systems"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
