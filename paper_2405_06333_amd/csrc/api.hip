@@ -438,6 +438,7 @@ void plan_workspace(rbe2d_ctx *h, size_t cdf_total, bool own_kset, Alloc &&A) {
     A(&w.krec, (size_t)n * h->P * kKRec);
     A(&w.kf32, 3 * (size_t)n * h->P);
     A(&w.kf64, kKF64 * (size_t)n * h->P);
+    A(&w.fpart, h->P > kLongP ? std::min<int64_t>(kMaxForceRows * cap_blocks, kMaxRowBlocks) * kBlock : 0);
     const int64_t nc = std::max<int64_t>(h->n_cap, 1);
     A(&w.cell, nc); A(&w.slot, nc); A(&w.tmp, nc);
     A(&w.count, cells); A(&w.start, cells + 1); A(&w.scanbuf, cells / 1024 + 2);

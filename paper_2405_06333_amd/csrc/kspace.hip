@@ -439,6 +439,9 @@ struct ForceArgs {
     EnergyArgs en;
     const int *err;
     int32_t *err_out;
+    double4 *part;           // kRows: sums of the block rows, cap_particles apart
+    int64_t part_stride;
+    int rows;
 };
 
 // f: the sums over k (times q_i and with the real-space part: force_terms)
@@ -487,16 +490,24 @@ __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64
     }
 }
 
-// Blocks of the force pass.  SPLIT (too few particles to fill the chip): the
-// waves of a block share 64 particles and take the parts of the k-range in
-// turn, and their sums meet in LDS: 32 KB at most, where sums kept in memory
-// for a second launch cost that launch (6 us of a call of 60 to 100 us).
-constexpr int kMaxForceWaves = 16;
-template <bool SPLIT, typename Sum>
+// Blocks of the force pass.  kWhole: one thread per particle takes all k.
+// kWaves (too few particles to fill the chip): the waves of a block share 64
+// particles and take the parts of the k-range in turn, and their sums meet in
+// LDS: 32 KB at most, where sums kept in memory for a second launch cost that
+// launch (6 us of a call of 60 to 100 us).  kRows: with many wave vectors (P
+// beyond kLongP) the parts are what a call lasts, on the N / 64 CUs that hold
+// those blocks; rows of blocks of 4 waves then take one part each, over the
+// whole chip, and a second launch adds the rows.  K-space forces, kWaves |
+// kRows: 500 ions, P = 4096 FP64 148 | 75 and FP32 79 | 44 us, 4000 ions, P =
+// 2000 89 | 58 and 49 | 39, P = 1024 53 | 40 and 32 | 30, P = 600 37 | 34 and
+// 25 | 27.
+enum ForceSplit { kWhole, kWaves, kRows };
+constexpr int kMaxForceWaves = 16, kRowWaves = 4;
+template <ForceSplit SPLIT, typename Sum>
 __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
     extern __shared__ __align__(16) double fsh[];
-    if constexpr (SPLIT) {
-        if ((int)blockIdx.x >= a.n_groups) {
+    if constexpr (SPLIT != kWhole) {
+        if (SPLIT == kWaves && (int)blockIdx.x >= a.n_groups) {
             energy_block(a.en, blockIdx.x - a.n_groups, fsh);
             return;
         }
@@ -514,22 +525,22 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
         const double qi = a.q[g];
         // the parts of the real-space forces too are dealt to the waves
         double4 real = make_double4(0.0, 0.0, 0.0, 0.0), f = real;
-        if (a.add_real)
+        if (SPLIT == kWaves && a.add_real)
             for (int p = wid; p < a.real.n; p += nw) {
                 const double4 v = a.real.f[p * a.real.stride + g];
                 real.x += v.x; real.y += v.y; real.z += v.z; real.w += v.w;
             }
-        if (a.add_real && a.real.more && wid == 0) {
+        if (SPLIT == kWaves && a.add_real && a.real.more && wid == 0) {
             const double4 v = a.real.more[g];
             real.x += v.x; real.y += v.y; real.z += v.z;
         }
         if (a.do_kspace)
-            for (int k = wid; k < a.split; k += nw)
+            for (int k = wid + (SPLIT == kRows ? (int)blockIdx.y * nw : 0); k < a.split; k += SPLIT == kRows ? a.rows * nw : nw)
                 sum(r, ii, k * a.k_per_split, min(a.P, (k + 1) * a.k_per_split), f);
         // (stores only from here on: the loads above stay scalar)
-        if (a.err_out && blockIdx.x == 0 && threadIdx.x == 0) *a.err_out = *a.err;
+        if (SPLIT == kWaves && a.err_out && blockIdx.x == 0 && threadIdx.x == 0) *a.err_out = *a.err;
         double4 *part = reinterpret_cast<double4 *>(fsh);
-        f = force_terms(a, qi, f, real);
+        if (SPLIT == kWaves) f = force_terms(a, qi, f, real);
         part[threadIdx.x] = f;
         __syncthreads();
         if (wid != 0 || !on) return;
@@ -537,7 +548,8 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
             const double4 v = part[w * kWave + lane];
             f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
         }
-        finish_particle(a, r, g, qi, f);
+        if (SPLIT == kRows) a.part[blockIdx.y * a.part_stride + ii] = f;
+        else finish_particle(a, r, g, qi, f);
     } else {
         const int b = blockIdx.x;
         const int r = find_sys(a.lay.bbase, a.n_sys, b);
@@ -551,10 +563,32 @@ __device__ __forceinline__ void force_block(const ForceArgs &a, Sum sum) {
     }
 }
 
+// The rows' sums of a force pass in rows, in their order, and what ends the pass
+__global__ __launch_bounds__(kBlock) void k_force_rows(ForceArgs a, int n_blocks) {
+    __shared__ double sh[kBlock / kWave];
+    if ((int)blockIdx.x >= n_blocks) {
+        energy_block(a.en, blockIdx.x - n_blocks, sh);
+        return;
+    }
+    const int b = blockIdx.x;
+    const int r = find_sys(a.lay.bbase, a.n_sys, b);
+    const int iloc = (b - a.lay.bbase[r]) * kBlock + threadIdx.x;
+    if (iloc >= a.lay.off[r + 1] - a.lay.off[r]) return;
+    const double4 *p = a.part + a.lay.pbase[r] + iloc;
+    double4 f = p[0];
+    for (int y = 1; y < a.rows; y++) {
+        const double4 v = p[y * a.part_stride];
+        f.x += v.x; f.y += v.y; f.z += v.z; f.w += v.w;
+    }
+    const int64_t g = (int64_t)a.lay.off[r] + iloc;
+    const double qi = a.q[g];
+    finish_particle(a, r, g, qi, force_terms(a, qi, f, a.add_real ? a.real.sum(g) : make_double4(0, 0, 0, 0)));
+}
+
 // MODE 0: forces; 1: forces and potentials (adjoint); 2: forces and the sum
 // of the squared per-k force terms (variance estimate)
-template <int MODE, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? kMaxForceWaves * kWave : kBlock) void k_force32(ForceArgs a) {
+template <int MODE, ForceSplit SPLIT>
+__global__ __launch_bounds__(SPLIT == kWaves ? kMaxForceWaves * kWave : kBlock) void k_force32(ForceArgs a) {
     force_block<SPLIT>(a, [&](int r, int64_t ii, int l0, int l1, double4 &F) {
         const float4 pa = a.p32[2 * ii];
         const float4 pb = a.p32[2 * ii + 1];
@@ -619,9 +653,9 @@ __global__ __launch_bounds__(SPLIT ? kMaxForceWaves * kWave : kBlock) void k_for
 // per-k records took 112 bytes from two arrays.  Bound by VALU issue, 40
 // instructions per (particle, k), two sines; 1e6 ions, P = 500: 0.61 ms
 // instead of 0.72 (46 instructions).
-template <int MODE, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? kMaxForceWaves * kWave : kBlock) void k_force64(ForceArgs a) {
-    using Record = std::conditional_t<SPLIT, ConstDouble, double>;
+template <int MODE, ForceSplit SPLIT>
+__global__ __launch_bounds__(SPLIT == kWaves ? kMaxForceWaves * kWave : kBlock) void k_force64(ForceArgs a) {
+    using Record = std::conditional_t<SPLIT != kWhole, ConstDouble, double>;
     __shared__ double2 tab[MODE == 1 ? kParts : 1];
     if (MODE == 1) {
         if (threadIdx.x < kParts)
@@ -692,13 +726,18 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
         while (a.split > 1 && (int64_t)a.split * h->n_blocks > h->split_blocks) a.split >>= 1;
     }
     a.k_per_split = (h->P + a.split - 1) / a.split;
-    const bool split = a.split > 1, energies = x.energy || x.dEdgamma;
+    const bool energies = x.energy || x.dEdgamma;
+    const ForceSplit split = a.split == 1 ? kWhole : a.split > kMaxForceWaves && h->P > kLongP ? kRows : kWaves;
     if (energies) a.en = energy_args(h, x.energy, flags, gE, x.dEdgamma);
     a.err = h->w.err; a.err_out = x.err_out;
     a.n_groups = h->n_blocks * (kBlock / kWave);
-    const int waves = std::min(a.split, kMaxForceWaves);
-    const dim3 g(split ? a.n_groups + (energies ? h->n_sys : 0) : h->n_blocks), b(split ? waves * kWave : kBlock);
-    const int lds = split ? waves * kWave * (int)sizeof(double4) : 0;
+    a.part = h->w.fpart; a.part_stride = (int64_t)h->n_blocks * kBlock;
+    a.rows = split == kRows ? (a.split + kRowWaves - 1) / kRowWaves : 1;
+    const int waves = split == kRows ? kRowWaves : std::min(a.split, kMaxForceWaves);
+    const int energy_blocks = energies ? h->n_sys : 0;
+    const dim3 g(split == kWhole ? h->n_blocks : a.n_groups + (split == kWaves ? energy_blocks : 0), a.rows);
+    const dim3 b(split == kWhole ? kBlock : waves * kWave);
+    const int lds = split == kWhole ? 0 : waves * kWave * (int)sizeof(double4);
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
     const int mode = x.var ? 2 : want_pot ? 1 : 0;
     prof_begin(h, 5, s);
@@ -707,16 +746,17 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
         if (fp32) hipLaunchKernelGGL((k_force32<M, S>), g, b, lds, s, a);              \
         else hipLaunchKernelGGL((k_force64<M, S>), g, b, lds, s, a);                   \
     }
-    RBE2D_FORCE(0, false) RBE2D_FORCE(1, false) RBE2D_FORCE(2, false)
-    RBE2D_FORCE(0, true) RBE2D_FORCE(1, true) RBE2D_FORCE(2, true)
+    RBE2D_FORCE(0, kWhole) RBE2D_FORCE(1, kWhole) RBE2D_FORCE(2, kWhole)
+    RBE2D_FORCE(0, kWaves) RBE2D_FORCE(1, kWaves) RBE2D_FORCE(2, kWaves)
+    RBE2D_FORCE(0, kRows) RBE2D_FORCE(1, kRows) RBE2D_FORCE(2, kRows)
 #undef RBE2D_FORCE
+    if (split == kRows)
+        hipLaunchKernelGGL(k_force_rows, dim3(h->n_blocks + energy_blocks), dim3(kBlock), 0, s, a, h->n_blocks);
     prof_end(h, 5, s);
     hipError_t e = hipGetLastError();
-    if (!split) {
-        // a launch of its own: the energies of an unsplit pass are a small part of the call
-        if (e == hipSuccess && energies) e = launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
-        if (e == hipSuccess && x.err_out) e = launch_copy_err(h, x.err_out, s);
-    }
+    // a launch of its own: the energies of an unsplit pass are a small part of the call
+    if (split == kWhole && e == hipSuccess && energies) e = launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
+    if (split != kWaves && e == hipSuccess && x.err_out) e = launch_copy_err(h, x.err_out, s);
     return e;
 }
 

@@ -26,6 +26,9 @@ constexpr int kKChunk64 = 8;         // k-vectors per structure-factor block, FP
 constexpr int kPPad = 16;            // P is padded to a multiple of this
 constexpr int kMaxFamilies = 128;    // real-space image families (order, side) per system
 constexpr int kWave = 64;
+// force pass: P beyond which parts of the k-range are summed in memory, in at
+// most kMaxForceRows rows and (rows x particle blocks) kMaxRowBlocks
+constexpr int kLongP = 1024, kMaxForceRows = 16, kMaxRowBlocks = 1024;
 constexpr int kMaxRealSplit = 5;     // FP32 real space: column groups a target's pair work may be split into
 constexpr int kMaxFamilySplit = 3;   // ... and its image families into further groups, for at most
 constexpr int64_t kFamilySplitMax = 49152;   // this many targets
@@ -148,6 +151,7 @@ struct Workspace {
     float4 *kf32 = nullptr;     // per k: (kx, ky, kz, kx^2 + ky^2), (cAr, cAi, cBr, cBi),
                                 // (|cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi)
     double *kf64 = nullptr;     // per k: kKF64 doubles (FP64)
+    double4 *fpart = nullptr;   // force pass in rows: sums of the rows (P > kLongP)
     // real space
     int *cell = nullptr, *slot = nullptr, *count = nullptr, *start = nullptr;
     int2 *tmp = nullptr;        // unordered cell lists: (caller index, global cell)

@@ -129,3 +129,56 @@ def test_two_streams_from_a_first_call_on(torch, R, precision, N):
     G = slab.forces(pd, qd, flags=R.REAL) + slab.forces(pd, qd, flags=R.KSPACE | R.IBC)
     assert rel_rms(G.cpu().numpy(), F.cpu().numpy()) <= 1e-13
     slab.check()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N, P", [(1, 1025), (64, 1024), (65, 1030), (500, 4099), (4097, 1500), (17000, 1025)])
+def test_many_wave_vectors(torch, R, orc, precision, N, P):
+    """P about and beyond 1024: force passes in rows, with the energies, the
+    potentials and the variances that end them."""
+    w = wl(N, P)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    kset = slab.draw_kset(w.seed)
+    slab.set_kset(kset)
+    pd, qd = to_dev(torch, pos), to_dev(torch, q)
+    t = None if N <= 500 else np.random.default_rng(0).choice(N, 64, replace=False)
+    o = oracle_slab(orc, w, slab.Lz_ext)
+    ref = orc.evaluate(o, pos, q, kset, targets=t)
+    at = np.arange(N) if t is None else t
+    tol = TOL[precision]
+    F, E = slab.forces(pd, qd, want_energy=True)
+    assert torch.equal(slab.forces(pd, qd), F)
+    assert rel_rms(F.cpu().numpy()[at], ref.F) <= tol
+    if t is None:
+        for eg, er in zip(E.cpu().numpy(), ref.energies()):
+            assert abs(eg - er) <= tol * energy_scale(ref)
+    # half of it on top of something: the sum of both calls
+    H = torch.full_like(F, 0.5)
+    slab.forces(pd, qd, out=H, flags=R.KSPACE | R.ACCUMULATE)
+    G = slab.forces(pd, qd, flags=R.REAL | R.IBC)
+    assert torch.allclose(G + H - 0.5, F, rtol=0, atol=1e-13 * float(F.abs().max()) + 1e-13)
+    e = slab.energy(pd, qd)
+    one = torch.ones((), dtype=torch.float64, device="cuda")
+    dr, dq, _ = slab.energy_backward(pd, qd, one)
+    # (the adjoint's FP32 sums go by sines and cosines, the forces' by polar amplitudes)
+    assert rel_rms(-dr.cpu().numpy()[at], ref.F) <= tol
+    assert rel_rms(dq.cpu().numpy()[at], ref.phi) <= tol
+    assert abs(float(e[0]) - float(E[0])) <= 1e-12 * energy_scale_of(E)
+    slab.check()
+
+
+def energy_scale_of(E):
+    return float(E[1:].abs().sum()) + 1e-300
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_variance_of_many_wave_vectors(torch, R, orc, precision):
+    w = wl(300, 1100)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    kset = slab.draw_kset(w.seed)
+    slab.set_kset(kset)
+    var = slab.force_variance(to_dev(torch, pos), to_dev(torch, q)).cpu().numpy()
+    ref = orc.force_variance_estimate(oracle_slab(orc, w, slab.Lz_ext), pos, q, kset)
+    assert rel_rms(var, ref) <= TOL[precision]

@@ -84,9 +84,9 @@ COUNTING = ["forces_energy", "real", "energy", "backward", "md", "md_ex"]
 
 def lost_errors():
     """Every launch of every call, failed in turn, makes the call fail."""
-    for precision, N in SYSTEMS:
-        s = Host(precision, N)
-        for name in ["forces", *COUNTING, "variance", "short", "short_off"] + (["noalloc"] if N <= 32768 else []):
+    for precision, N, P in [(p, n, 8) for p, n in SYSTEMS] + [(FP64, 500, 1100), (FP32, 500, 1100)]:
+        s = Host(precision, N, P)
+        for name in ["forces", *COUNTING, "variance", "short", "short_off"] + (["noalloc"] if N <= 32768 and P <= 1024 else []):
             st, log = s.call(name)
             assert st == 0 and log, (precision, N, name)
             for i in range(len(log)):
@@ -141,6 +141,17 @@ def many_wave_vectors():
             assert st == 0 and bool(own_launch(log, sf)) != rides, (precision, n_sys, P)
 
 
+def long_force_passes():
+    """Few ions and many wave vectors: the force pass in rows, over the chip."""
+    for precision, N, P, rows in ((FP64, 500, 1024, 0), (FP64, 500, 1025, 2), (FP32, 500, 1025, 2), (FP64, 20000, 1025, 80),
+                                  (FP64, 40000, 1025, 0)):
+        s = Host(precision, N, P)
+        for name, energies in (("forces", 0), ("forces_energy", 1), ("variance", 0), ("backward", 1)):
+            st, log = s.call(name)
+            assert st == 0 and [g for g, _ in own_launch(log, "k_force_rows")] == ([rows + energies] if rows else []), \
+                (precision, N, P, name, log)
+
+
 def many_systems():
     """The cell list of many systems: narrow blocks, or none per system where
     nothing rides along."""
@@ -161,7 +172,7 @@ def runtime(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors",
-                                      "many_systems"])
+                                      "many_systems", "long_force_passes"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
