@@ -680,12 +680,14 @@ rbe2d_status check_arrays(rbe2d_ctx *h, const double *pos, const double *q) {
 // (of all systems) the assembly fills the chip by itself and gains by the pair
 // kernel beside it: FP64, 4096 slabs of 16 ions with 32 each 368 | 339, 16 slabs
 // of 500 with 4000 287 | 275, 64 of 300 with 500 167 | 162, but 1024 of 16 with
-// 32 126 | 145.
+// 32 126 | 145.  (A structure-factor launch of its own deals
+// whole tiles to the XCDs and wants two for each at least: 500 ions with 65536
+// wave vectors 968 | 2447, energy of 40000 with 40000 1808 | 2588.)
 constexpr int64_t kOneStreamForces32 = 24576, kOneStream = 98304, kOneStreamItems = 32768;
 bool on_one_stream(const rbe2d_ctx *h, bool energy) {
     return h->one_stream ||
            (h->n_total <= (!energy && h->precision == RBE2D_PREC_FP32_PHASE ? kOneStreamForces32 : kOneStream) &&
-            (int64_t)h->n_sys * h->P <= kOneStreamItems);
+            ((int64_t)h->n_sys * h->P <= kOneStreamItems || h->n_tiles < 16));
 }
 
 // On one stream the structure factors and the assembly ride along with the

@@ -134,8 +134,8 @@ def many_wave_vectors():
     """The k-space chain runs beside the pair sums where its wave vectors fill the
     chip by themselves, and rides along where they do not."""
     for precision, sf in ((FP64, "k_sf64"), (FP32, "k_sf32")):
-        for n_sys, N, P, rides in ((1024, 16, 32, True), (1025, 16, 32, False), (16, 500, 4000, False), (1, 500, 32768, True),
-                                   (1, 500, 32769, False)):
+        for n_sys, N, P, rides in ((1024, 16, 32, True), (1025, 16, 32, False), (16, 500, 4000, False), (1, 500, 32769, True),
+                                   (1, 90000, 32769, False)):
             s = Host(precision, N, P, n_sys)
             st, log = s.call("batch" if n_sys > 1 else "forces")
             assert st == 0 and bool(own_launch(log, sf)) != rides, (precision, n_sys, P)
