@@ -31,7 +31,7 @@ namespace rbe2d {
 
 struct TableArgs {
     SampleArgs sample;       // the k-set, and how to draw it when `draw` is set
-    int draw, P_pad;
+    int draw, P_pad, chunk;
     float4 *kn32;
     double4 *kn64;
 };
@@ -54,23 +54,26 @@ __device__ __forceinline__ void table32(const TableArgs &a, int blk) {
     a.kn32[kg] = make_float4((float)n.x, (float)n.y, (float)n.z, 0.0f);
 }
 
-// FP64: the k-vectors of system r sorted by |nz|, (nx, ny, |nz|, +-(1 + index
-// in the k-set) with the sign of nz), by a counting sort in LDS, one block.
-// |nz| beyond the last bucket are left unsorted: the structure-factor pass
-// compares neighbours and only saves less.  (The order within a bucket is
-// that of the LDS atomics; no sum depends on it.)
+// FP64: the k-vectors of system r sorted by |nz| in chunks (z_chunk), (nx, ny,
+// |nz|, +-(1 + index in the k-set) with the sign of nz), by a counting sort in
+// LDS, one block per chunk.  |nz| beyond the last bucket are left unsorted: the
+// structure-factor pass compares neighbours and only saves less, as it does at
+// the ends of a chunk.  (The order within a bucket is that of the LDS atomics;
+// no sum depends on it.)
 constexpr int kZBuckets = 2048;
-__device__ void table64(const TableArgs &a, int r) {
+__device__ __forceinline__ int z_bucket(int nz) { return min(abs(nz), kZBuckets - 1); }
+__device__ void table64(const TableArgs &a, int blk) {
     __shared__ int count[kZBuckets];
     __shared__ int sh[kBlock / 64];
-    const int P = a.sample.P;
-    const int32_t *k = a.sample.kset + 3 * (int64_t)r * P;
+    const int chunks = (a.P_pad + a.chunk - 1) / a.chunk;
+    const int r = blk / chunks, l0 = (blk - r * chunks) * a.chunk;
+    const int l1 = min(a.sample.P, l0 + a.chunk), pad1 = min(a.P_pad, l0 + a.chunk);
+    const int32_t *k = a.sample.kset + 3 * (int64_t)r * a.sample.P;
     constexpr int kPer = kZBuckets / kBlock;
 #pragma unroll
     for (int b = 0; b < kPer; b++) count[b * kBlock + threadIdx.x] = 0;
     __syncthreads();
-    for (int l = threadIdx.x; l < P; l += kBlock)
-        atomicAdd(&count[min(abs(table_kvec(a, r, l).z), kZBuckets - 1)], 1);
+    for (int l = l0 + threadIdx.x; l < l1; l += kBlock) atomicAdd(&count[z_bucket(table_kvec(a, r, l).z)], 1);
     __syncthreads();
     int v[kPer], t = 0;
 #pragma unroll
@@ -80,11 +83,11 @@ __device__ void table64(const TableArgs &a, int r) {
     for (int b = 0; b < kPer; b++) { count[kPer * threadIdx.x + b] = run; run += v[b]; }
     __syncthreads();
     double4 *o = a.kn64 + (int64_t)r * a.P_pad;
-    for (int l = threadIdx.x; l < a.P_pad; l += kBlock) {
-        if (l < P) {
+    for (int l = l0 + threadIdx.x; l < pad1; l += kBlock) {
+        if (l < l1) {
             // (a drawn k-vector was written by this thread)
             const int nx = k[3 * l], ny = k[3 * l + 1], nz = k[3 * l + 2];
-            const int at = atomicAdd(&count[min(abs(nz), kZBuckets - 1)], 1);
+            const int at = l0 + atomicAdd(&count[z_bucket(nz)], 1);
             o[at] = make_double4((double)nx, (double)ny, fabs((double)nz), nz < 0 ? -1.0 - l : 1.0 + l);
         } else {
             o[l] = make_double4(0.0, 0.0, 0.0, 0.0);
@@ -239,16 +242,26 @@ __global__ __launch_bounds__(kBlock) void k_prep(PrepArgs a) {
 
 __global__ __launch_bounds__(64) void k_scalars(ScalArgs a) { ibc_scalars(a, blockIdx.x, threadIdx.x); }
 
-static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q) {
+// Wave vectors per block of the FP64 table.  One block for all of a system is a
+// chain that every other launch waits for, 11 us per 256 draws; every block more
+// takes sines from the structure-factor pass (sorted by 512 instead of 1024: 2
+// to 3 % of it).  Velocity-Verlet steps by all | 1024 | 512: 500 ions, P = 4096
+// 142 | 110 | 104 us, P = 1000 88 | 88 | 82, 4000 ions, P = 16000 611 | 333 |
+// 331, 40000 ions, P = 1000 193 | 193 | 188, 300000 ions 944 | 945 | 958.
+static int z_chunk(const rbe2d_ctx *h, bool draw) { return draw && h->n_total <= 100000 ? 512 : 1024; }
+
+static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q, bool draw) {
     PrepArgs a{};
     a.pos = pos; a.q = q; a.sys = h->w.sys; a.lay = h->w.lay; a.n_sys = h->n_sys;
     a.p32 = h->w.p32; a.p64 = h->w.p64; a.bpart = h->w.bpart; a.err = h->w.err;
     a.cell = h->w.cell; a.slot = h->w.slot;
-    // (the call without a handle may go without a k-set, and then without k-space)
-    if (h->w.kset)
-        a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock : h->n_sys;
     a.tab.sample = sample_args(h, 0, 0, nullptr);
     a.tab.P_pad = h->P_pad; a.tab.kn32 = h->w.kn32; a.tab.kn64 = h->w.kn64;
+    a.tab.draw = draw; a.tab.chunk = z_chunk(h, draw);
+    // (the call without a handle may go without a k-set, and then without k-space)
+    if (h->w.kset)
+        a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock
+                                                            : h->n_sys * ((h->P_pad + a.tab.chunk - 1) / a.tab.chunk);
     return a;
 }
 
@@ -273,7 +286,7 @@ static void launch_prep_kernel(rbe2d_ctx *h, const PrepArgs &a, hipStream_t s) {
 
 hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s, bool scalars, bool count) {
     prof_begin(h, 0, s);
-    PrepArgs a = prep_args(h, pos, q);
+    PrepArgs a = prep_args(h, pos, q, false);
     if (count) a.count = h->w.count;
     launch_prep_kernel<0>(h, a, s);
     if (count) {
@@ -288,14 +301,13 @@ hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStre
 hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const double *F, const double *q, double dt,
                           double zlo, double zhi_from_top, const MdExtra *mx, uint64_t seed, uint64_t stream_base,
                           const long long *dev_step, hipStream_t s) {
-    PrepArgs a = prep_args(h, pos, q);
+    PrepArgs a = prep_args(h, pos, q, true);
     a.pos_md = pos; a.vel = vel; a.F = F; a.real = real_parts(h);
     a.dt = dt; a.zlo = zlo; a.zhi_from_top = zhi_from_top;
     // a force evaluation with real space follows: count the particles per
     // cell here, where their new positions are at hand
     a.count = h->w.count;
     a.tab.sample = sample_args(h, seed, stream_base, dev_step);
-    a.tab.draw = 1;
     if (md == 3) {
         a.c1 = mx->c1; a.c2 = mx->c2; a.seed = seed; a.stream_base = stream_base; a.dev_step = dev_step;
     }

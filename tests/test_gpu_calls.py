@@ -182,3 +182,24 @@ def test_variance_of_many_wave_vectors(torch, R, orc, precision):
     var = slab.force_variance(to_dev(torch, pos), to_dev(torch, q)).cpu().numpy()
     ref = orc.force_variance_estimate(oracle_slab(orc, w, slab.Lz_ext), pos, q, kset)
     assert rel_rms(var, ref) <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N, P", [(300, 512), (300, 513), (300, 1300), (100001, 520)])
+def test_drawn_tables(torch, R, orc, precision, N, P):
+    """k-sets drawn in MD steps, whose tables are sorted in chunks: the forces of
+    the last step are those of its k-set at its positions."""
+    w = wl(N, P, M=2)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    slab.sample_kset(5, 0)
+    P_, Q_ = to_dev(torch, pos), to_dev(torch, q)
+    F_, V_ = slab.forces(P_, Q_), torch.zeros_like(P_)
+    slab.md_run(P_, V_, Q_, F_, 1e-4, 0.2, w.H - 0.2, 5, 7, 3)
+    slab.check()
+    kset = slab.draw_kset(5, 9)
+    assert np.array_equal(slab.get_kset(), kset)
+    t = None if N <= 500 else np.random.default_rng(0).choice(N, 48, replace=False)
+    ref = orc.evaluate(oracle_slab(orc, w, slab.Lz_ext), P_.cpu().numpy(), q, kset, targets=t)
+    F = F_.cpu().numpy()
+    assert rel_rms(F if t is None else F[t], ref.F) <= TOL[precision]

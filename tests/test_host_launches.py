@@ -152,6 +152,18 @@ def long_force_passes():
                 (precision, N, P, name, log)
 
 
+def k_tables():
+    """FP64 tables of many wave vectors by many blocks (those of the particle
+    pass beyond the particles' own)."""
+    for N, P, forces, md in ((256, 1024, 1, 2), (256, 1025, 2, 3), (256, 65536, 64, 128), (110592, 1025, 2, 2)):
+        s = Host(FP64, N, P)
+        for name, blocks in (("forces", forces), ("md", md), ("md_ex", md)):
+            st, log = s.call(name)
+            tile = 4096 if N > 256 or P > 32768 else 256
+            particles = (N + tile - 1) // tile * tile // 256
+            assert st == 0 and own_launch(log, "k_prep")[0][0] == blocks + particles, (N, P, name, log[0])
+
+
 def many_systems():
     """The cell list of many systems: narrow blocks, or none per system where
     nothing rides along."""
@@ -172,7 +184,7 @@ def runtime(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors",
-                                      "many_systems", "long_force_passes"])
+                                      "many_systems", "long_force_passes", "k_tables"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
