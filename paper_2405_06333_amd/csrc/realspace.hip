@@ -289,12 +289,13 @@ constexpr size_t kSmallLds = 60 << 10;
 constexpr int kSmallN = 4096;
 // More than kManySystems systems: blocks of kBlock threads up to kNarrowN
 // particles each, since several share a CU then and most threads of 1024 have
-// nothing to do; and up to kTinyN, with nothing riding along, the four launches,
-// which take less of the chip from the k-space chain beside them.  Velocity-
-// Verlet steps with 1024 | 256 threads | four launches: 16384 slabs of 8 ions
-// FP32 1054 | 954 | 950 us, 1024 of 16 116 | 119 | 109, 256 of 100 108 | 108 |
-// 103, 1024 of 200 325 | 244 | 343, 300 of 1000 340 | 344 | 373.
-constexpr int kManySystems = 128, kNarrowN = 512, kTinyN = 128;
+// nothing to do; and from kTinySystems systems of up to kTinyN on, with nothing
+// riding along, the four launches, which take less of the chip from the k-space
+// chain beside them.  Velocity-Verlet steps with 1024 | 256 threads | four
+// launches: 16384 slabs of 8 ions FP32 1054 | 954 | 950 us, 1024 of 16 116 | 119 |
+// 109, 256 of 100 108 | 108 | 103, 200 of 16 59 | 59 | 69, 1024 of 200 325 | 244 |
+// 343, 300 of 1000 340 | 344 | 373.
+constexpr int kManySystems = 128, kNarrowN = 512, kTinySystems = 256, kTinyN = 128;
 template <SfKind SF>
 __global__ __launch_bounds__(kSmallThreads) void k_cells_small(CellArgs a, SfArgs sf) {
     extern __shared__ __align__(16) int lds[];
@@ -880,7 +881,7 @@ static hipError_t build_cells(rbe2d_ctx *h, const double *pos, const double *q, 
     const int n_sf = SF == kNoSf ? 0 : SfRide<SF>::parts(sf);
     const size_t lds = (h->max_cells + 1 + (size_t)h->max_n) * sizeof(int);
     const bool many = h->n_sys > kManySystems;
-    if (h->max_n <= kSmallN && lds <= kSmallLds && !(many && SF == kNoSf && h->max_n <= kTinyN)) {
+    if (h->max_n <= kSmallN && lds <= kSmallLds && !(SF == kNoSf && h->n_sys >= kTinySystems && h->max_n <= kTinyN)) {
         const int threads = many && h->max_n <= kNarrowN ? kBlock : kSmallThreads, per = threads / kBlock;
         hipLaunchKernelGGL(k_cells_small<SF>, dim3(h->n_sys + (n_sf + per - 1) / per), dim3(threads),
                            std::max<size_t>(lds, per * SfRide<SF>::kLds), s, c, sf);

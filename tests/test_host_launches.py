@@ -173,6 +173,9 @@ def many_systems():
         st, log = s.call("batch")
         cells = [l for l in log if "k_cells_small" in l[0]]
         assert st == 0 and [b for _, _, b, _ in cells] == ([threads] if threads else []), (n_sys, N, P, cells)
+    for n_sys, blocks in ((255, 1), (256, 0)):
+        s = Host(FP32, 120, 8, n_sys)               # (30600 ions: two streams)
+        assert len([l for l in s.call("batch")[1] if "k_cells_small" in l[0]]) == blocks
 
 
 @pytest.fixture(scope="module")
