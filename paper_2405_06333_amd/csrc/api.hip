@@ -647,6 +647,13 @@ rbe2d_status set_layout(rbe2d_ctx *h, const int64_t *counts, hipStream_t s) {
                                     hipMemcpyHostToDevice, s), "layout upload");
     RBE2D_TRY(h, hipEventRecord(h->lay_ev, s), "layout event");
     h->lay_ev_pending = true;
+    h->neighbours = 0.0;
+    for (int r = 0; r < n && h->n_total > 0; r++) {
+        const rbe2d_params &p = h->sys[r].p;
+        const double c = (double)counts[r], ball = 4.0 / 3.0 * kPi * p.r_c * p.r_c * p.r_c;
+        h->neighbours += c * c / h->n_total / (p.Lx * p.Ly * p.H) *
+                         (h->sys[r].d.nfam > 0 ? ball : std::min(ball, kPi * p.r_c * p.r_c * p.H));
+    }
     h->lay_host = lay;
     h->lay_valid = true;
     return RBE2D_OK;
@@ -699,11 +706,19 @@ bool rides_along(const rbe2d_ctx *h, bool one_stream) { return one_stream && h->
 // the pair kernel, and not on the chip before it.  us per call with the fork
 // before | after the cell list: energy and gradient of 150000 ions FP32 631 |
 // 557, FP64 693 | 533; forces of 150000 ions FP64 450 | 377, FP32 484 | 447 and
-// 281 | 258, of 250000 FP32 662 | 511 and 383 | 403; but of 100000 FP32, where
-// the pair work is split over more waves, 284 | 270 and 197 | 214.
+// 281 | 258, of 250000 FP32 662 | 511; but of 100000 FP32, where the pair work is
+// split over more waves, 284 | 270 and 197 | 214.  With FP32 phases it takes more
+// pairs than the k-space chain has wave vectors to last longer than it, per ion
+// 0.6 neighbours for each (forces: two passes) or 0.3 (energies: one).  Forces of
+// 200000 ions, neighbours for each wave vector: 0.17 139 | 161, 0.27 294 | 310,
+// 0.44 170 | 185, 0.64 456 | 423, 0.70 206 | 207, 1.05 251 | 242; energies of
+// 200000, 0.11 189 | 206, 0.17 129 | 145, 0.27 271 | 255, 0.44 172 | 170, 0.70
+// 208 | 195.  Where the pair kernel leaves half of the chip, up to 2304 waves,
+// forces take less: 140000 ions, 0.17 110 | 128, 0.27 248 | 225.
 bool pairs_first(const rbe2d_ctx *h, bool energy) {
-    return h->n_swaves <= 4096 &&
-           (energy || h->precision != RBE2D_PREC_FP32_PHASE || h->n_swaves > 2048);
+    if (h->n_swaves > 4096) return false;
+    if (h->precision != RBE2D_PREC_FP32_PHASE) return true;
+    return (energy || h->n_swaves > 2048) && h->neighbours >= (energy ? 0.3 : h->n_swaves <= 2304 ? 0.25 : 0.6) * h->P;
 }
 
 // `to` waits for what `from` has been given so far

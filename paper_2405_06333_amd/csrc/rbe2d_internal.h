@@ -220,6 +220,7 @@ struct rbe2d_ctx {
     int per = 0;                     // particles per thread of the structure-factor tiles
     int64_t n_total = 0;
     int max_n = 0, max_cells = 0;    // of one system
+    double neighbours = 0.0;         // ions and images within r_c of an ion, spread evenly
     int n_blocks = 0, n_tiles = 0, n_swaves = 0;
     int *lay_stage = nullptr;        // pinned staging of layout uploads
     hipEvent_t lay_ev = nullptr;

@@ -1,5 +1,5 @@
 // A HIP runtime without a GPU for tests of the library's host side: memory is
-// host memory, launches are only noted (kernel name, grid and block), and one
+// host memory, launches and waits are only noted (kernel name, grid and block), and one
 // chosen call or launch can be made to fail.  An error stays until
 // hipGetLastError takes it, as in the real runtime.
 #include <cstdint>
@@ -72,7 +72,10 @@ int hipDeviceSynchronize() { return 0; }
 int hipStreamCreateWithFlags(void **s, unsigned) { *s = some_pointer(); return 0; }
 int hipStreamDestroy(void *) { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
-int hipStreamWaitEvent(void *, void *, unsigned) { return outcome("hipStreamWaitEvent"); }
+int hipStreamWaitEvent(void *, void *, unsigned) {
+    g_log += "hipStreamWaitEvent 0 0 0\n";
+    return outcome("hipStreamWaitEvent");
+}
 int hipStreamBeginCapture(void *, int) { return outcome("hipStreamBeginCapture"); }
 int hipStreamEndCapture(void *, void **g) { *g = some_pointer(); return outcome("hipStreamEndCapture"); }
 int hipGraphInstantiate(void **x, void *, void **, char *, size_t) {

@@ -22,10 +22,10 @@ BUF = 1 << 16   # stands for every device array: kernels do not run
 class Host:
     """A handle and its calls on the stand-in runtime."""
 
-    def __init__(self, precision, N, P=8, n_sys=1):
+    def __init__(self, precision, N, P=8, n_sys=1, L=40.0):
         self.fake, self.L, self.N = ctypes.CDLL(sys.argv[2]), R.lib(), N
         self.fake.fake_log.restype = ctypes.c_char_p
-        p = R.Params(Lx=40.0, Ly=40.0, H=6.0, Lz_ext=0.0, eps_lz=0.0, gamma_top=0.7, gamma_bot=-0.5, alpha=1.0,
+        p = R.Params(Lx=L, Ly=L, H=6.0, Lz_ext=0.0, eps_lz=0.0, gamma_top=0.7, gamma_bot=-0.5, alpha=1.0,
                      r_c=3.0, P=P, M=2, precision=precision, reserved=0, n_max=N, coulomb_prefactor=1.0)
         self.params = p
         self.h = ctypes.c_void_p()
@@ -63,7 +63,8 @@ class Host:
                                                       None),
         }[name]()
         log = [l.split() for l in self.fake.fake_log().decode().splitlines()]
-        return st, [(n, int(g), int(b), int(e)) for n, g, b, e in log]
+        self.order = [l[0] for l in log]                  # launches and stream waits
+        return st, [(n, int(g), int(b), int(e)) for n, g, b, e in log if n != "hipStreamWaitEvent"]
 
 
 def counts(log, clears=("k_cells_small", "k_cell_scatter", "k_fill"), pending=False):
@@ -164,6 +165,21 @@ def k_tables():
             assert st == 0 and own_launch(log, "k_prep")[0][0] == blocks + particles, (N, P, name, log[0])
 
 
+def fork_of_the_k_space_chain():
+    """It starts after the cell list only beside a longer pair kernel."""
+    for precision, N, rho, P, forces, energy in (
+            (FP32, 200000, 0.5, 128, False, True), (FP32, 200000, 0.8, 128, True, True), (FP32, 200000, 0.5, 500, False, False),
+            (FP32, 200000, 1.2, 500, False, False), (FP32, 200000, 1.4, 500, False, True), (FP32, 200000, 2.7, 500, True, True),
+            (FP32, 270000, 2.7, 500, False, False), (FP32, 140000, 1.2, 500, True, False),
+            (FP32, 140000, 0.8, 500, False, False), (FP32, 130000, 2.7, 500, False, True), (FP64, 200000, 0.5, 500, True, True)):
+        s = Host(precision, N, P, L=(N / (6.0 * rho)) ** 0.5)      # r_c = 3: 113 rho neighbours
+        for name, late in (("forces", forces), ("energy", energy)):
+            assert s.call(name)[0] == 0
+            fork = s.order.index("hipStreamWaitEvent")
+            cells = [i for i, n in enumerate(s.order) if "k_cell_rank" in n][0]
+            assert (fork > cells) == late, (precision, N, rho, P, name)
+
+
 def many_systems():
     """The cell list of many systems: narrow blocks, or none per system where
     nothing rides along."""
@@ -187,7 +203,8 @@ def runtime(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors",
-                                      "many_systems", "long_force_passes", "k_tables"])
+                                      "many_systems", "long_force_passes", "k_tables",
+                                      "fork_of_the_k_space_chain"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
