@@ -301,7 +301,12 @@ hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStre
 hipError_t launch_prep_md(rbe2d_ctx *h, int md, double *pos, double *vel, const double *F, const double *q, double dt,
                           double zlo, double zhi_from_top, const MdExtra *mx, uint64_t seed, uint64_t stream_base,
                           const long long *dev_step, hipStream_t s) {
-    PrepArgs a = prep_args(h, pos, q, true);
+    const bool draw = !timed(h, 8);
+    if (!draw) {
+        const hipError_t e = launch_sample(h, seed, stream_base, dev_step, s);
+        if (e != hipSuccess) return e;
+    }
+    PrepArgs a = prep_args(h, pos, q, draw);
     a.pos_md = pos; a.vel = vel; a.F = F; a.real = real_parts(h);
     a.dt = dt; a.zlo = zlo; a.zhi_from_top = zhi_from_top;
     // a force evaluation with real space follows: count the particles per
@@ -746,7 +751,8 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
     a.part = h->w.fpart; a.part_stride = (int64_t)h->n_blocks * kBlock;
     a.rows = split == kRows ? (a.split + kRowWaves - 1) / kRowWaves : 1;
     const int waves = split == kRows ? kRowWaves : std::min(a.split, kMaxForceWaves);
-    const int energy_blocks = energies ? h->n_sys : 0;
+    const bool energies_ride = energies && split != kWhole && !timed(h, 6);
+    const int energy_blocks = energies_ride ? h->n_sys : 0;
     const dim3 g(split == kWhole ? h->n_blocks : a.n_groups + (split == kWaves ? energy_blocks : 0), a.rows);
     const dim3 b(split == kWhole ? kBlock : waves * kWave);
     const int lds = split == kWhole ? 0 : waves * kWave * (int)sizeof(double4);
@@ -767,7 +773,7 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
     prof_end(h, 5, s);
     hipError_t e = hipGetLastError();
     // a launch of its own: the energies of an unsplit pass are a small part of the call
-    if (split == kWhole && e == hipSuccess && energies) e = launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
+    if (e == hipSuccess && energies && !energies_ride) e = launch_energy(h, x.energy, flags, gE, x.dEdgamma, s);
     if (split != kWaves && e == hipSuccess && x.err_out) e = launch_copy_err(h, x.err_out, s);
     return e;
 }

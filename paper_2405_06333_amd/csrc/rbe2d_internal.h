@@ -349,15 +349,18 @@ hipError_t launch_fill(void *p, int64_t nbytes_multiple_of_4, hipStream_t s);
 int choose_tile(int64_t N_total, int n_kchunks);
 int choose_ksplit(int64_t n_blocks, int P);
 
+// whether launches of kernel class `slot` are timed: its work then has launches
+// of its own where it is part of others' otherwise
+inline bool timed(const rbe2d_ctx *h, int slot) { return h->prof.n > 0 && ((h->prof.mask >> slot) & 1u); }
 // bracket a launch of kernel class `slot` with profiling events (no-op when off)
 inline void prof_begin(rbe2d_ctx *h, int slot, hipStream_t s) {
     Profiler &p = h->prof;
-    if (p.n > 0 && ((p.mask >> slot) & 1u) && p.used[slot] < p.n)
+    if (timed(h, slot) && p.used[slot] < p.n)
         (void)hipEventRecord(p.ev[slot][0][p.used[slot]], s);
 }
 inline void prof_end(rbe2d_ctx *h, int slot, hipStream_t s) {
     Profiler &p = h->prof;
-    if (p.n > 0 && ((p.mask >> slot) & 1u) && p.used[slot] < p.n)
+    if (timed(h, slot) && p.used[slot] < p.n)
         (void)hipEventRecord(p.ev[slot][1][p.used[slot]++], s);
 }
 

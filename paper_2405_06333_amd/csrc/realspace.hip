@@ -996,12 +996,14 @@ __global__ __launch_bounds__(kBlock) void k_add_real(int64_t n, RealParts real, 
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s, double *energy,
                            uint32_t energy_flags) {
     if (h->n_total == 0) return hipSuccess;
+    const bool ride = energy && !timed(h, 6);
     prof_begin(h, 10, s);
     const int nb = (int)((h->n_total + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_add_real, dim3(nb + (energy ? h->n_sys : 0)), dim3(kBlock), 0, s, h->n_total, real_parts(h), F,
+    hipLaunchKernelGGL(k_add_real, dim3(nb + (ride ? h->n_sys : 0)), dim3(kBlock), 0, s, h->n_total, real_parts(h), F,
                        vel, half_dt, nb, energy_args(h, energy, energy_flags, nullptr, nullptr));
     prof_end(h, 10, s);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && energy && !ride ? launch_energy(h, energy, energy_flags, nullptr, nullptr, s) : e;
 }
 
 }  // namespace rbe2d

@@ -180,6 +180,29 @@ def fork_of_the_k_space_chain():
             assert (fork > cells) == late, (precision, N, rho, P, name)
 
 
+def timed_classes():
+    """Every class that a call has work of is timed by launches of its own."""
+    for precision, N, P in ((FP64, 500, 64), (FP64, 500, 1100), (FP64, 100000, 8), (FP64, 300000, 8), (FP32, 500, 64),
+                            (FP32, 140000, 8)):
+        s = Host(precision, N, P)
+        n = (ctypes.c_int64 * len(R.PROF_SLOTS))()
+        for mask in (0x7ff, 0x10):
+            assert s.L.rbe2d_profile_enable(s.h, 8) == 0 and s.L.rbe2d_profile_classes(s.h, ctypes.c_uint32(mask)) == 0
+            for name, want in (("forces_energy", {"prep": 1, "sf_pass": 1, "assemble": 1, "cell_build": 1, "real_pairs": 1,
+                                                  "force_scatter": 1, "energy": 1, "ksample": 0}),
+                               ("energy", {"sf_pass": 1, "energy": 1}), ("backward", {"force_scatter": 1, "energy": 1}),
+                               ("md", {"integrator": 2, "ksample": 2, "sf_pass": 2, "energy": 0}),
+                               ("md_ex", {"integrator": 2, "ksample": 2, "short_range": 2})):
+                st, log = s.call(name)
+                assert st == 0 and s.L.rbe2d_profile_read(s.h, None, n, len(n)) == 0
+                got = {c: n[R.PROF_SLOTS.index(c)] for c in want}
+                if mask == 0x7ff:
+                    assert got == want, (precision, N, P, name, got)
+                elif name in ("forces_energy", "md"):
+                    # (the timing of one class leaves the others as they are)
+                    assert not own_launch(log, "k_sample") and not own_launch(log, "k_energy"), (precision, N, name)
+
+
 def many_systems():
     """The cell list of many systems: narrow blocks, or none per system where
     nothing rides along."""
@@ -204,7 +227,7 @@ def runtime(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["lost_errors", "counts_after_failed_calls", "many_wave_vectors",
                                       "many_systems", "long_force_passes", "k_tables",
-                                      "fork_of_the_k_space_chain"])
+                                      "fork_of_the_k_space_chain", "timed_classes"])
 def test_host_side(runtime, scenario):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario, runtime], cwd=ROOT, capture_output=True,
                        text=True, timeout=300)
