@@ -225,3 +225,36 @@ def test_ion_depletion_near_insulating_interfaces(torch, R):
     cm, am = _wall_fractions(torch, R, -0.939)
     assert cp < 0.75 * c0 and cm > 1.4 * c0, (c0, cp, cm)
     assert ap < a0 < am, (a0, ap, am)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [17000, 24576, 24577, 60000, 140000])
+def test_langevin_step_forces_of_large_systems(torch, R, precision, N):
+    """The short-range forces of a step, by tiles of 12, 4, 2 or 1 waves or one
+    thread per ion, beside the pair sums or after them: the forces that a step
+    leaves are those of the force call and the short-range call at its positions
+    and k-set, to the order of FP64 sums, and graph replays equal eager steps."""
+    n = int(np.ceil((N / 6) ** 0.5))
+    L = 0.9 * n
+    w = inputs.small_random(71, N, L=L, H=6.0, gamma_top=0.6, gamma_bot=-0.4, alpha=1.0, r_c=3.0, P=24, M=2)
+    rng = np.random.default_rng(N)
+    k = np.arange(N)
+    pos = 0.9 * np.stack([k % n, k // n % n, k // (n * n)], axis=1) + [0.4, 0.4, 0.5] + rng.uniform(-0.08, 0.08, (N, 3))
+    q = np.where(k % 2 == 0, 1.0, -1.0)
+    md = R.md_params(gamma=1.0, kT=1.0, sigma=0.95, eps=1.0, sigma_wall=0.5, eps_wall=1.0, wall_margin=0.05)
+    s = R.Slab(**w.slab_kwargs(), precision=precision, n_max=N)
+    Q_, runs = to_dev(torch, q), []
+    for use_graph in (False, True):
+        s.sample_kset(9, 0)
+        P_, V_ = to_dev(torch, pos), to_dev(torch, rng.normal(0.0, 1.0, (N, 3)) if not runs else runs[0][3])
+        v0 = V_.cpu().numpy()
+        F_ = s.short_forces(P_, Q_, md, F=s.forces(P_, Q_))
+        s.md_run_ex(P_, V_, Q_, F_, 1e-4, md, 9, 1, 2, use_graph=use_graph)
+        s.check()
+        G_ = s.short_forces(P_, Q_, md, F=s.forces(P_, Q_))     # (the k-set of the last step)
+        F, short = F_.cpu().numpy(), (G_ - s.forces(P_, Q_)).cpu().numpy()
+        assert np.abs(short).max() > 1.0                         # the ions overlap
+        assert rel_rms(F, G_.cpu().numpy()) <= 1e-12
+        runs.append((P_.cpu().numpy(), V_.cpu().numpy(), F, v0))
+    for x, y in zip(*runs):
+        assert np.array_equal(x, y)
