@@ -733,9 +733,8 @@ rbe2d_status stream_wait(rbe2d_ctx *h, hipStream_t to, hipStream_t from, hipEven
 // assembly) runs on the side stream while the cell list and the pair kernel
 // run on `s`; `s` waits for both.  The cell build is latency- and
 // atomic-bound and the pair kernel latency-limited, so the VALU-bound
-// structure-factor pass fills their idle issue slots (1.79 instead of
-// 1.93 ms per step of the 1e6-ion slab).  The fork and join are events, so
-// the pattern is also captured into graphs.
+// structure-factor pass fills their idle issue slots.  The fork and join are
+// events, so the pattern is also captured into graphs.
 rbe2d_status run_common(rbe2d_ctx *h, const double *pos, const double *q, uint32_t flags, bool want_dg,
                         hipStream_t s) {
     const bool kside = (flags & (RBE2D_KSPACE | RBE2D_IBC)) != 0;
@@ -751,9 +750,8 @@ rbe2d_status run_common(rbe2d_ctx *h, const double *pos, const double *q, uint32
     }
     // real space is enqueued first: its cell list starts ahead of the structure factors
     const bool ride = rides_along(h, sc_asm && real && !two);
-    const RideAlong ra;
     if (real)
-        RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s, ride ? &ra : nullptr, late ? h->fork_ev : nullptr),
+        RBE2D_TRY(h, launch_real(h, pos, q, want_dg, s, ride, late ? h->fork_ev : nullptr),
                   "real-space launch");
     if (late) RBE2D_TRY(h, hipStreamWaitEvent(h->side, h->fork_ev, 0), "stream wait");
     if (sc_asm && !ride) RBE2D_TRY(h, launch_kcoef_sf(h, two ? h->side : s, true, want_dg), "structure-factor launch");
@@ -796,15 +794,13 @@ rbe2d_status compute_forces(rbe2d_ctx *h, const double *pos, const double *q, do
     // real space first: its latency-bound cell list then starts ahead of the
     // structure factors (also in a captured graph, whose nodes follow this order)
     const bool ride = rides_along(h, sc_asm && real && !two);
-    RideAlong ra;
-    ra.step = job.step;
     // (an MD step: two streams)  The short-range kernel needs the cell list
     // only: after the k-space chain on the side stream, beside the pair kernel,
     // or, where that chain is the longer one, after the pair kernel.
     const bool shortr = two && job.mx;
     const bool short_side = h->precision != RBE2D_PREC_FP32_PHASE || h->n_total <= kShortTiles32;
     if (real)
-        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride ? &ra : nullptr, late ? h->fork_ev : shortr && short_side ? h->cells_ev : nullptr),
+        RBE2D_TRY(h, launch_real(h, pos, q, false, s, ride, late ? h->fork_ev : shortr && short_side ? h->cells_ev : nullptr),
                   "real-space launch");
     if (late) RBE2D_TRY(h, hipStreamWaitEvent(ks, h->fork_ev, 0), "stream wait");
     if (shortr && !short_side)

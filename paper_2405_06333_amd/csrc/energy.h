@@ -30,9 +30,9 @@ __device__ __forceinline__ void energy_block(const EnergyArgs &a, int r, double 
     if (a.do_k)
         for (int l = threadIdx.x; l < a.P; l += (int)blockDim.x) {
             const double *rec = a.krec + ((int64_t)r * a.P + l) * kKRec;
-            ek += rec[7];
-            dkt += rec[8];
-            dkb += rec[9];
+            ek += rec[0];
+            dkt += rec[1];
+            dkb += rec[2];
         }
     const bool has_real = a.do_real && a.lay.off[r + 1] > a.lay.off[r];
     if (has_real)

@@ -448,10 +448,8 @@ struct ForceArgs {
     double *var;             // force-variance estimate per particle (variance mode)
     const double *gE;        // scale of the backward outputs (device scalar) or null
     int accumulate, add_real, want_pot, want_var, do_kspace, do_ibc;
-    double *vel;             // closing half kick of an MD step, or null
-    double half_dt;
-    // SPLIT: blocks from n_groups on form the systems' energies; *err goes to
-    // err_out when set
+    // kWaves: blocks from n_groups on form the systems' energies (k_force_rows:
+    // from n_blocks on); *err goes to err_out when set
     int n_groups;
     EnergyArgs en;
     const int *err;
@@ -501,9 +499,7 @@ __device__ __forceinline__ void finish_particle(const ForceArgs &a, int r, int64
     }
     const double o[3] = {Fx, Fy, Fz};
     for (int c = 0; c < 3; c++) {
-        const double v = a.accumulate ? a.F[3 * g + c] + o[c] : o[c];
-        a.F[3 * g + c] = v;
-        if (a.vel) a.vel[3 * g + c] = fma(a.half_dt, v, a.vel[3 * g + c]);
+        a.F[3 * g + c] = a.accumulate ? a.F[3 * g + c] + o[c] : o[c];
     }
 }
 
@@ -733,7 +729,7 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
     a.kf32 = h->w.kf32; a.kf64 = h->w.kf64; a.lay = h->w.lay; a.sys = h->w.sys;
     a.n_sys = h->n_sys; a.P = h->P; a.P_pad = h->P_pad;
     a.pos = pos; a.q = q; a.scal = h->w.scal; a.real = real_parts(h);
-    a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = x.var; a.vel = x.vel; a.half_dt = x.half_dt;
+    a.F = F; a.dEdq = dEdq; a.gE = gE; a.var = x.var;
     a.accumulate = accumulate; a.add_real = add_real; a.want_pot = want_pot; a.want_var = x.var != nullptr;
     a.do_kspace = (flags & RBE2D_KSPACE) != 0; a.do_ibc = (flags & RBE2D_IBC) != 0;
     a.split = 1;

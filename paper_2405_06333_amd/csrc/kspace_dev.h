@@ -362,12 +362,7 @@ __device__ __forceinline__ void assemble_wave(const AssembleArgs &a, int item, i
         }
     }
     double *rec = a.krec + kg * kKRec;
-    rec[0] = kx; rec[1] = ky; rec[2] = kz;
-    rec[3] = c * Ar; rec[4] = c * Ai; rec[5] = c * Br; rec[6] = c * Bi;
-    rec[7] = e; rec[8] = de[0]; rec[9] = de[1];
-    rec[10] = nx; rec[11] = ny; rec[12] = nz;
-    rec[13] = rr; rec[14] = ri; rec[15] = kx * kx + ky * ky;
-    rec[16] = magA; rec[17] = argA; rec[18] = magB; rec[19] = argB;
+    rec[0] = e; rec[1] = de[0]; rec[2] = de[1];
     if (a.kf64) {
         double *f = a.kf64 + kg * kKF64;
         f[0] = nx; f[1] = ny; f[2] = nz;

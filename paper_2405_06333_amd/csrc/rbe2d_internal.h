@@ -101,15 +101,14 @@ struct SysDesc {
 // Per-system scalars of the IBC and surface terms (kspace.hip: ibc_scalars)
 constexpr int kScal = 20;
 
-// Per-k record written by the reduce/assemble kernel (FP64):
-//   [0..2] kx, ky, kz      [3..6] c*A (re, im), c*B (re, im)
-//   [7] e_l = c Re(rho conj(rho^M))   [8..9] d e_l / d gamma_{top,bot}
-//   [10..12] nx, ny, nz (as doubles)  [13..14] rho (re, im)  [15] kx^2 + ky^2
-//   [16..19] polar form |cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi
-constexpr int kKRec = 20;
+// Per-k record of the energies: [0] e_l = c Re(rho conj(rho^M))
+//   [1..2] d e_l / d gamma_{top,bot}
+constexpr int kKRec = 3;
 
-// Per-k record of the FP64 force pass: [0..2] nx, ny, nz  [4..7] polar form
-// [8..11] c*A, c*B, as above; 128 bytes apart.
+// Per-k record of the FP64 force pass, 128 bytes apart:
+//   [0..2] nx, ny, nz (as doubles)
+//   [4..7] polar form |cA|, arg cA / 2 pi, |cB|, arg cB / 2 pi
+//   [8..11] c*A (re, im), c*B (re, im)
 constexpr int kKF64 = 16;
 
 // Layout of the particles of all systems in the internal arrays (device
@@ -206,7 +205,9 @@ struct rbe2d_ctx {
     int total_cells = 0;
     bool iso = false;                // every system has the isotropic fixed-point frame
     int64_t split_cap = 0;           // targets per split of the partial real-space outputs
-    int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most
+    int64_t split_blocks = 0;        // k-range parts x particle blocks of the force pass at most (its rows'
+                                     // sums hold a quarter; also where the parts meet in LDS: the FP32 sums
+                                     // are grouped by them)
     bool one_stream = false;         // run the k-space chain on the caller's stream too (no side stream)
     bool short_part = false;         // fshort belongs to the forces of this cell list
     int real_stride = 0;             // waves per part in rpart_s
@@ -301,12 +302,10 @@ hipError_t launch_prep(rbe2d_ctx *h, const double *pos, const double *q, hipStre
 hipError_t launch_kcoef_sf(rbe2d_ctx *h, hipStream_t s, bool with_scalars = false, bool want_dg = false,
                            long long *step = nullptr);
 // What a force pass may do besides forces: per-particle variances instead,
-// the closing half kick of an MD step, and where all parts precede it on its
-// stream, the energies (energy), the gamma derivatives (dEdgamma) and a copy
-// of the error word
+// and where all parts precede it on its stream, the energies (energy), the
+// gamma derivatives (dEdgamma) and a copy of the error word
 struct ForceExtra {
-    double *var = nullptr, *vel = nullptr;
-    double half_dt = 0.0;
+    double *var = nullptr;
     double *energy = nullptr, *dEdgamma = nullptr;
     int32_t *err_out = nullptr;
 };
@@ -315,13 +314,10 @@ hipError_t launch_kforce(rbe2d_ctx *h, const double *pos, const double *q, doubl
                          hipStream_t s, const ForceExtra &x = ForceExtra());
 // Cell list and pair sums.  With `ride` the structure factors and the per-k
 // assembly (with the IBC scalars) are blocks of these launches: for calls on
-// one stream, instead of launch_kcoef_sf.
-struct RideAlong {
-    long long *step = nullptr;   // as in launch_kcoef_sf
-};
-// after_cells: recorded between the two when set
+// one stream, instead of launch_kcoef_sf.  after_cells: recorded between the
+// two when set
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
-                       const RideAlong *ride = nullptr, hipEvent_t after_cells = nullptr);
+                       bool ride = false, hipEvent_t after_cells = nullptr);
 hipError_t launch_cells(rbe2d_ctx *h, const double *pos, const double *q, hipStream_t s);   // the cell list alone
 // F += F_real (and v += half_dt F); also the energies when energy is set
 hipError_t launch_add_real(rbe2d_ctx *h, double *F, double *vel, double half_dt, hipStream_t s,

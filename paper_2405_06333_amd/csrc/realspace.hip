@@ -956,7 +956,7 @@ static bool launch_pairs(rbe2d_ctx *h, bool want_dg, const AssembleArgs *as, hip
 }
 
 hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool want_dg, hipStream_t s,
-                       const RideAlong *ride, hipEvent_t after_cells) {
+                       bool ride, hipEvent_t after_cells) {
     if (h->n_total == 0) return hipSuccess;
     const bool fp32 = h->precision == RBE2D_PREC_FP32_PHASE;
     hipError_t e = !ride ? build_cells<kNoSf>(h, pos, q, s)
@@ -964,7 +964,7 @@ hipError_t launch_real(rbe2d_ctx *h, const double *pos, const double *q, bool wa
     if (e == hipSuccess && after_cells) e = hipEventRecord(after_cells, s);
     if (e != hipSuccess) return e;
     if (ride) {
-        const AssembleArgs as = assemble_args(h, true, ride->step);
+        const AssembleArgs as = assemble_args(h, true, nullptr);
         if (!launch_pairs(h, want_dg, &as, s)) e = launch_assemble(h, as, want_dg, s);
     } else {
         launch_pairs(h, want_dg, nullptr, s);
