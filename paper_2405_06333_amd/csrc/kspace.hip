@@ -31,7 +31,7 @@ namespace rbe2d {
 
 struct TableArgs {
     SampleArgs sample;       // the k-set, and how to draw it when `draw` is set
-    int draw, P_pad, chunk;
+    int draw, P_pad, chunk, chunks;
     float4 *kn32;
     double4 *kn64;
 };
@@ -65,8 +65,7 @@ __device__ __forceinline__ int z_bucket(int nz) { return min(abs(nz), kZBuckets 
 __device__ void table64(const TableArgs &a, int blk) {
     __shared__ int count[kZBuckets];
     __shared__ int sh[kBlock / 64];
-    const int chunks = (a.P_pad + a.chunk - 1) / a.chunk;
-    const int r = blk / chunks, l0 = (blk - r * chunks) * a.chunk;
+    const int r = a.chunks == 1 ? blk : blk / a.chunks, l0 = (blk - r * a.chunks) * a.chunk;
     const int l1 = min(a.sample.P, l0 + a.chunk), pad1 = min(a.P_pad, l0 + a.chunk);
     const int32_t *k = a.sample.kset + 3 * (int64_t)r * a.sample.P;
     constexpr int kPer = kZBuckets / kBlock;
@@ -257,11 +256,11 @@ static PrepArgs prep_args(rbe2d_ctx *h, const double *pos, const double *q, bool
     a.cell = h->w.cell; a.slot = h->w.slot;
     a.tab.sample = sample_args(h, 0, 0, nullptr);
     a.tab.P_pad = h->P_pad; a.tab.kn32 = h->w.kn32; a.tab.kn64 = h->w.kn64;
-    a.tab.draw = draw; a.tab.chunk = z_chunk(h, draw);
+    a.tab.draw = draw; a.tab.chunk = z_chunk(h, draw); a.tab.chunks = (h->P_pad + a.tab.chunk - 1) / a.tab.chunk;
     // (the call without a handle may go without a k-set, and then without k-space)
     if (h->w.kset)
         a.n_tblocks = h->precision == RBE2D_PREC_FP32_PHASE ? (h->n_sys * h->P_pad + kBlock - 1) / kBlock
-                                                            : h->n_sys * ((h->P_pad + a.tab.chunk - 1) / a.tab.chunk);
+                                                            : h->n_sys * a.tab.chunks;
     return a;
 }
 
