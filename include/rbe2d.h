@@ -44,6 +44,8 @@
  *     A z outside that range sets a device error word that the next
  *     rbe2d_check reports as RBE2D_E_RANGE; the results of that call are
  *     then undefined (but the kernels stay in bounds).
+ *   - Two ions at the very same place: with FP32 phases their pair is left
+ *     out, in FP64 its terms (and the sums they enter) are not numbers.
  *   - A handle is not thread-safe; distinct handles are independent.
  *     Overlapping calls on one handle from different streams race.
  */

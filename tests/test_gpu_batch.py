@@ -335,7 +335,7 @@ def test_force_variance_single_batch_of_one_k(torch, R):
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("n_sys, N, P", [(129, 16, 9), (130, 128, 300), (130, 129, 300), (129, 512, 9), (129, 513, 9),
-                                         (2100, 15, 16)])
+                                         (2100, 15, 16), (5, 500, 1100)])
 def test_many_small_systems(torch, R, orc, precision, n_sys, N, P):
     """The forms of the cell list for many systems, of unlike sizes and boxes:
     every call again, and some systems against the oracle."""

@@ -203,3 +203,37 @@ def test_drawn_tables(torch, R, orc, precision, N, P):
     ref = orc.evaluate(oracle_slab(orc, w, slab.Lz_ext), P_.cpu().numpy(), q, kset, targets=t)
     F = F_.cpu().numpy()
     assert rel_rms(F if t is None else F[t], ref.F) <= TOL[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N, P", [(300, 40), (300, 1100), (5000, 40), (30000, 40), (140000, 17)])
+def test_captured_calls(torch, R, precision, N, P):
+    """Force calls, energies and steps captured by the caller: every replay, with
+    eager work between them, equals the eager call."""
+    w = wl(N, P, M=2)
+    pos, q = inputs.sample(w)
+    slab = gpu_slab(R, w, precision)
+    slab.set_kset(slab.draw_kset(w.seed))
+    pd, qd, p2 = to_dev(torch, pos), to_dev(torch, q), to_dev(torch, pos[::-1])
+    one = torch.ones((), dtype=torch.float64, device="cuda")
+    F, E = torch.empty_like(pd), torch.empty(5, dtype=torch.float64, device="cuda")
+
+    def call():
+        slab.forces(pd, qd, out=F, energy_out=E, want_energy=True)
+        e = slab.energy(pd, qd)
+        return (F, E, e) + tuple(slab.energy_backward(pd, qd, one))
+
+    want = [t.clone() for t in call()]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = call()
+    for _ in range(3):
+        for t in out:
+            t.fill_(7.0)
+        slab.forces(p2, qd)                 # eager work on other positions
+        g.replay()
+        torch.cuda.synchronize()
+        for t, u in zip(out, want):
+            assert torch.equal(t, u)
+    slab.check()
