@@ -453,7 +453,7 @@ struct ForceArgs {
     EnergyArgs en;
     const int *err;
     int32_t *err_out;
-    double4 *part;           // kRows: sums of the block rows, cap_particles apart
+    double4 *part;           // kRows: sums of the block rows, part_stride apart
     int64_t part_stride;
     int rows;
 };
